@@ -176,31 +176,229 @@ __device__ __forceinline__ void write_cos_tile(float* tri, const float* rinv, co
   }
 }
 
-// Algorithm 1's pick chain (Eq. 2-3) on one wave, for a head whose cosines sit in the packed
-// triangle `tri` (element (i,j), j <= i, at i(i+1)/2 + j, +inf on the diagonal) and whose scores
-// sit in s_l (-inf for padding).  A single wave issues one instruction every few cycles, so the
-// time of a pick is its instruction count: tokens lane, lane + 64, .. live in lane `lane` (see
-// first_of_slots); pick u of a
-// 64-pick chunk is parked in lane u of two registers (v_writelane) and the chunk is written to
-// order_l / gain_l once; nothing is checked per pick.  Non-finite input is detected afterwards
-// from the logged gains: the picks before the first one without a finite gain are kept and the
-// list is filled up with the lowest tokens < n_live not yet in it.  `diverse` false is the
-// lambda = 0 branch (top-b, the triangle is not read).  Returns the gain of the last pick.
+// The race: Algorithm 1's picks (Eq. 2-3) on one wave, over the 64*NQ tokens whose cosines sit in a triangle in LDS.
+// Token lane + 64*q lives in slot q of lane `lane`: its score s[q], its running maximum m[q] and the LDS address
+// row[q] of its row of the triangle.  Element (i, j) sits at max(row(i) + 4j, row(j) + 4i), the diagonal holds +inf, so
+// reading the row of a pick retires it.  Picks number u .. cnt-1 (cnt <= 64, cnt > u) are made; pick u is parked in
+// lane u of rec_i (4 x its token) and rec_g (its gain).  With BOUND the race stops before the first pick whose gain is
+// not above gout; amax and the returned reference i4 then describe that pick, which is not applied.  Returns the number
+// of picks made.  Ties go to the lowest token.  Nothing is branched on non-finite gains: a maximum that equals no
+// token (NaN) retires lane 63's token, which callers replace afterwards (see pick_chain).
+//
+// What bounds it is the issue rate of a single wave, four cycles an instruction, plus 20 for each value that crosses
+// from the vector to the scalar unit and 50 for the LDS read; so the loop is written out by hand.  The first winning
+// slot of every lane is worked out in the wait states of the reduction's DPP steps, which leaves one comparison, one
+// s_ff1 and two lane reads after it, whatever NQ is; lanes are in order, but tokens of several lanes with the same
+// gain are not, so more than one winning lane takes a slow path that goes through the slots in token order.  That check,
+// the logging and the loop control run while the LDS read is on its way.  Measured in cycles per pick for 1 / 2 / 3 / 4
+// slots: 240 / 255 / 280 / 300, against 262 / 304 / 384 / 440 for the compiler's loop over ballots of every slot; one
+// decode-time event (112 heads, n = 256, b = 128) 37.9 -> 30.0 us.  Also measured: narrowing exec to the winning lane
+// and v_readfirstlane instead of s_ff1 and v_readlane (8 cycles slower), one or two copies of the loop instead of four
+// (10 and 5 cycles slower), picking the second-best token ahead of the row of the best one (more instructions than the
+// LDS read it hides).
+#ifdef KVR_BOUNDS
+template <int NQ, bool BOUND>
+__device__ __forceinline__ int race_loop(float (&m)[NQ], const float (&s)[NQ], const int (&row)[NQ], int lane, float nlam,
+                                         int u, int cnt, float gout, int& rec_i, int& rec_g, float& amax, int& i4,
+                                         int tri0, int tri_floats) {
+  // (debug build: the same picks from plain code, with every address checked)
+  typedef __attribute__((address_space(3))) const float* lds_fp;
+  while (u < cnt) {
+    float av[NQ], best = -INFINITY;
+#pragma unroll
+    for (int q = 0; q < NQ; ++q) { av[q] = fmaf(nlam, m[q], s[q]); best = hw_max(best, av[q]); }
+    amax = wave_max_uniform(best);
+    int i = 63;
+#pragma unroll
+    for (int q = NQ - 1; q >= 0; --q) {
+      const unsigned long long e = __ballot(av[q] == amax);
+      if (e) i = __ffsll(static_cast<long long>(e)) - 1 + 64 * q;
+    }
+    i4 = i * 4;
+    if (BOUND && !(amax > gout)) return u;
+    write_lane2(rec_i, rec_g, i4, __float_as_int(amax), u);
+    ++u;
+    int ri = 0;
+#pragma unroll
+    for (int q = 0; q < NQ; ++q) {
+      const int r = __builtin_amdgcn_readlane(row[q], i & 63);
+      if ((i >> 6) == q) ri = r;
+    }
+#pragma unroll
+    for (int q = 0; q < NQ; ++q) {
+      const int x0 = ri + (lane + 64 * q) * 4, x1 = row[q] + i4;
+      const int xa = kvr_ix(((x0 > x1 ? x0 : x1) - tri0) >> 2, tri_floats, KVR_BOUNDS_FILE * 100 + 5) * 4 + tri0;   // x05: triangle element of the race
+      m[q] = hw_max(m[q], *reinterpret_cast<lds_fp>(static_cast<uintptr_t>(static_cast<unsigned>(xa))));
+    }
+  }
+  return u;
+}
+#else
+#define KVR_RACE_MAX(ctrl, rmask) "v_max_f32_dpp %[rd], %[rd], %[rd] " ctrl " row_mask:" rmask " bank_mask:0xf\n\t"
+#define KVR_RACE_S1 KVR_RACE_MAX("row_shr:1", "0xf")
+#define KVR_RACE_S2 KVR_RACE_MAX("row_shr:2", "0xf")
+#define KVR_RACE_S3 KVR_RACE_MAX("row_shr:4", "0xf")
+#define KVR_RACE_S4 KVR_RACE_MAX("row_shr:8", "0xf")
+#define KVR_RACE_S5 KVR_RACE_MAX("row_bcast:15", "0xa")
+#define KVR_RACE_S6 KVR_RACE_MAX("row_bcast:31", "0xc")
+#define KVR_RACE_FMA(q, d) "v_fma_f32 %[" d "], %[nl], %[m" #q "], %[s" #q "]\n\t"
+// (gfx950 wants two wait states between a VALU write of vcc and the v_cndmask that reads it, and before a DPP read)
+#define KVR_RACE_EQ(q) "v_cmp_eq_f32 vcc, %[bs], %[a" #q "]\n\t"
+#define KVR_RACE_SR(o, q) "v_cndmask_b32 %[sr], %[" o "], %[r" #q "], vcc\n\t"
+#define KVR_RACE_SI(o, q) "v_cndmask_b32 %[si], %[" o "], %[j" #q "], vcc\n\t"
+#define KVR_RACE_WIN(best, sr, si)                                                                             \
+  "v_readlane_b32 %[am], %[rd], 63\n\ts_nop 1\n\tv_cmp_eq_f32 vcc, %[am], %[" best "]\n\ts_ff1_i32_b64 %[L], vcc\n\t" \
+  "v_readlane_b32 %[R], %[" sr "], %[L]\n\tv_readlane_b32 %[I], %[" si "], %[L]\n\ts_nop 0\n\t"
+#define KVR_RACE_ADR(q) "v_add_u32 %[x" #q "], %[I], %[t" #q "]\n\tv_max_u32 %[x" #q "], %[x" #q "], %[ad]\n\t"
+#define KVR_RACE_RD(q, off) "ds_read_b32 %[x" #q "], %[x" #q "] offset:" off "\n\t"
+#define KVR_RACE_UPD(q) "v_max_f32 %[m" #q "], %[m" #q "], %[x" #q "]\n\t"
+// A pick is written out KVR_RACE_COPIES times (c is the copy's number, which its labels carry): a taken branch costs 25
+// cycles, one that falls through 12.  Winner -> addresses -> reads; while they travel: tie check, bound check, log, loop
+// control; the next copy starts by waiting for the reads.
+#define KVR_RACE_TIE(c, q)                                                                                     \
+  "v_cmp_eq_f32 vcc, %[am], %[a" #q "]\n\ts_cmp_lg_u64 vcc, 0\n\ts_cbranch_scc0 5" #c #q "f\n\ts_ff1_i32_b64 %[L], vcc\n\t" \
+  "v_readlane_b32 %[R], %[r" #q "], %[L]\n\tv_readlane_b32 %[I], %[j" #q "], %[L]\n5" #c #q ":\n\t"
+#define KVR_RACE_PICK(c, find, adrs, reads, bound, upds)                                                        \
+  "6" #c ":\n\t" find "2" #c ":\n\tv_add_u32 %[ad], %[R], %[j0]\n\t" adrs reads                                 \
+  "s_bcnt1_i32_b64 %[L], vcc\n\ts_cmp_gt_u32 %[L], 1\n\ts_cbranch_scc1 4" #c "f\n\t" bound                       \
+  "v_writelane_b32 %[ri], %[I], m0\n\tv_writelane_b32 %[rg], %[am], m0\n\ts_add_u32 m0, m0, 1\n\t"               \
+  "s_cmp_ge_u32 m0, %[cnt]\n\ts_cbranch_scc1 8f\n\ts_waitcnt lgkmcnt(0)\n\t" upds
+#define KVR_RACE_TIED(c, ties) "4" #c ":\n\ts_waitcnt lgkmcnt(0)\n\t" ties "s_mov_b64 vcc, 0\n\ts_nop 1\n\ts_branch 2" #c "b\n"
+#define KVR_RACE_ASM(find, adrs, reads, bound, upds, ties)                                                       \
+  "s_mov_b32 m0, %[u]\n" KVR_RACE_PICK(0, find, adrs, reads, bound, upds) KVR_RACE_PICK(1, find, adrs, reads, bound, upds) \
+  KVR_RACE_PICK(2, find, adrs, reads, bound, upds) KVR_RACE_PICK(3, find, adrs, reads, bound, upds) "s_branch 60b\n"        \
+  KVR_RACE_TIED(0, ties(0)) KVR_RACE_TIED(1, ties(1)) KVR_RACE_TIED(2, ties(2)) KVR_RACE_TIED(3, ties(3))                   \
+  "8:\n\ts_waitcnt lgkmcnt(0)\n\t" upds "3:\n\ts_waitcnt lgkmcnt(0)\n\ts_mov_b32 %[u], m0"
+#define KVR_RACE_BOUND "v_cmp_gt_f32 vcc, %[am], %[go]\n\ts_cbranch_vccz 3f\n\t"
+#define KVR_RACE_TMP [rd] "=&v"(rd), [ad] "=&v"(ad), [am] "=&s"(am), [L] "=&s"(L), [R] "=&s"(R), [I] "=&s"(I), \
+                     [ri] "+v"(rec_i), [rg] "+v"(rec_g), [u] "+s"(u)
+#define KVR_RACE_IN [nl] "s"(nlam), [cnt] "s"(cnt), [go] "v"(gout)
+
+#define KVR_RACE_FIND1 \
+  KVR_RACE_FMA(0, "rd") KVR_RACE_FMA(0, "a0") "s_nop 0\n\t" KVR_RACE_S1 "s_nop 1\n\t" KVR_RACE_S2 "s_nop 1\n\t" \
+  KVR_RACE_S3 "s_nop 1\n\t" KVR_RACE_S4 "s_nop 1\n\t" KVR_RACE_S5 "s_nop 1\n\t" KVR_RACE_S6 "s_nop 0\n\t" \
+  KVR_RACE_WIN("a0", "r0", "j0")
+#define KVR_RACE_TIES1(c) KVR_RACE_TIE(c, 0)
+#define KVR_RACE_RUN1(bound) \
+  asm volatile(KVR_RACE_ASM(KVR_RACE_FIND1, KVR_RACE_ADR(0), \
+                            KVR_RACE_RD(0, "0"), bound, \
+                            KVR_RACE_UPD(0), KVR_RACE_TIES1) \
+               : KVR_RACE_TMP, \
+                 [a0] "=&v"(a[0]), \
+                 [x0] "=&v"(x[0]), \
+                 [m0] "+v"(m[0]) \
+               : KVR_RACE_IN, [s0] "v"(s[0]), \
+                 [r0] "v"(row[0]), \
+                 [t0] "v"(t[0]), \
+                 [j0] "v"(j[0]) \
+               : "vcc", "scc", "m0", "memory")
+#define KVR_RACE_FIND2 \
+  KVR_RACE_FMA(0, "a0") KVR_RACE_FMA(1, "a1") "v_max_f32 %[rd], %[a0], %[a1]\n\tv_max_f32 %[bs], %[a0], %[a1]\n\t" \
+  KVR_RACE_EQ(0) KVR_RACE_S1 "s_nop 0\n\t" KVR_RACE_SR("r1", 0) KVR_RACE_S2 KVR_RACE_SI("j1", 0) "s_nop 0\n\t" \
+  KVR_RACE_S3 "s_nop 1\n\t" KVR_RACE_S4 "s_nop 1\n\t" KVR_RACE_S5 "s_nop 1\n\t" KVR_RACE_S6 "s_nop 0\n\t" \
+  KVR_RACE_WIN("bs", "sr", "si")
+#define KVR_RACE_TIES2(c) KVR_RACE_TIE(c, 1) KVR_RACE_TIE(c, 0)
+#define KVR_RACE_RUN2(bound) \
+  asm volatile(KVR_RACE_ASM(KVR_RACE_FIND2, KVR_RACE_ADR(0) KVR_RACE_ADR(1), \
+                            KVR_RACE_RD(0, "0") KVR_RACE_RD(1, "256"), bound, \
+                            KVR_RACE_UPD(0) KVR_RACE_UPD(1), KVR_RACE_TIES2) \
+               : KVR_RACE_TMP, [bs] "=&v"(bs), [sr] "=&v"(sr), [si] "=&v"(si), \
+                 [a0] "=&v"(a[0]), [a1] "=&v"(a[1]), \
+                 [x0] "=&v"(x[0]), [x1] "=&v"(x[1]), \
+                 [m0] "+v"(m[0]), [m1] "+v"(m[1]) \
+               : KVR_RACE_IN, [s0] "v"(s[0]), [s1] "v"(s[1]), \
+                 [r0] "v"(row[0]), [r1] "v"(row[1]), \
+                 [t0] "v"(t[0]), [t1] "v"(t[1]), \
+                 [j0] "v"(j[0]), [j1] "v"(j[1]) \
+               : "vcc", "scc", "m0", "memory")
+#define KVR_RACE_FIND3 \
+  KVR_RACE_FMA(0, "a0") KVR_RACE_FMA(1, "a1") \
+  KVR_RACE_FMA(2, "a2") "v_max3_f32 %[rd], %[a0], %[a1], %[a2]\n\tv_max3_f32 %[bs], %[a0], %[a1], %[a2]\n\t" \
+  KVR_RACE_EQ(1) KVR_RACE_S1 "s_nop 0\n\t" KVR_RACE_SR("r2", 1) KVR_RACE_S2 KVR_RACE_SI("j2", 1) KVR_RACE_EQ(0) \
+  KVR_RACE_S3 "s_nop 0\n\t" KVR_RACE_SR("sr", 0) KVR_RACE_S4 KVR_RACE_SI("si", 0) "s_nop 0\n\t" \
+  KVR_RACE_S5 "s_nop 1\n\t" KVR_RACE_S6 "s_nop 0\n\t" KVR_RACE_WIN("bs", "sr", "si")
+#define KVR_RACE_TIES3(c) KVR_RACE_TIE(c, 2) KVR_RACE_TIE(c, 1) KVR_RACE_TIE(c, 0)
+#define KVR_RACE_RUN3(bound) \
+  asm volatile(KVR_RACE_ASM(KVR_RACE_FIND3, KVR_RACE_ADR(0) KVR_RACE_ADR(1) KVR_RACE_ADR(2), \
+                            KVR_RACE_RD(0, "0") KVR_RACE_RD(1, "256") KVR_RACE_RD(2, "512"), bound, \
+                            KVR_RACE_UPD(0) KVR_RACE_UPD(1) KVR_RACE_UPD(2), KVR_RACE_TIES3) \
+               : KVR_RACE_TMP, [bs] "=&v"(bs), [sr] "=&v"(sr), [si] "=&v"(si), \
+                 [a0] "=&v"(a[0]), [a1] "=&v"(a[1]), [a2] "=&v"(a[2]), \
+                 [x0] "=&v"(x[0]), [x1] "=&v"(x[1]), [x2] "=&v"(x[2]), \
+                 [m0] "+v"(m[0]), [m1] "+v"(m[1]), [m2] "+v"(m[2]) \
+               : KVR_RACE_IN, [s0] "v"(s[0]), [s1] "v"(s[1]), [s2] "v"(s[2]), \
+                 [r0] "v"(row[0]), [r1] "v"(row[1]), [r2] "v"(row[2]), \
+                 [t0] "v"(t[0]), [t1] "v"(t[1]), [t2] "v"(t[2]), \
+                 [j0] "v"(j[0]), [j1] "v"(j[1]), [j2] "v"(j[2]) \
+               : "vcc", "scc", "m0", "memory")
+#define KVR_RACE_FIND4 \
+  KVR_RACE_FMA(0, "a0") KVR_RACE_FMA(1, "a1") KVR_RACE_FMA(2, "a2") \
+  KVR_RACE_FMA(3, "a3") "v_max3_f32 %[bs], %[a0], %[a1], %[a2]\n\tv_max_f32 %[rd], %[bs], %[a3]\n\tv_max_f32 %[bs], %[bs], %[a3]\n\t" \
+  KVR_RACE_EQ(2) KVR_RACE_S1 "s_nop 0\n\t" KVR_RACE_SR("r3", 2) KVR_RACE_S2 KVR_RACE_SI("j3", 2) KVR_RACE_EQ(1) \
+  KVR_RACE_S3 "s_nop 0\n\t" KVR_RACE_SR("sr", 1) KVR_RACE_S4 KVR_RACE_SI("si", 1) KVR_RACE_EQ(0) \
+  KVR_RACE_S5 "s_nop 0\n\t" KVR_RACE_SR("sr", 0) KVR_RACE_S6 KVR_RACE_SI("si", 0) KVR_RACE_WIN("bs", "sr", "si")
+#define KVR_RACE_TIES4(c) KVR_RACE_TIE(c, 3) KVR_RACE_TIE(c, 2) KVR_RACE_TIE(c, 1) KVR_RACE_TIE(c, 0)
+#define KVR_RACE_RUN4(bound) \
+  asm volatile(KVR_RACE_ASM(KVR_RACE_FIND4, KVR_RACE_ADR(0) KVR_RACE_ADR(1) KVR_RACE_ADR(2) KVR_RACE_ADR(3), \
+                            KVR_RACE_RD(0, "0") KVR_RACE_RD(1, "256") KVR_RACE_RD(2, "512") KVR_RACE_RD(3, "768"), bound, \
+                            KVR_RACE_UPD(0) KVR_RACE_UPD(1) KVR_RACE_UPD(2) KVR_RACE_UPD(3), KVR_RACE_TIES4) \
+               : KVR_RACE_TMP, [bs] "=&v"(bs), [sr] "=&v"(sr), [si] "=&v"(si), \
+                 [a0] "=&v"(a[0]), [a1] "=&v"(a[1]), [a2] "=&v"(a[2]), [a3] "=&v"(a[3]), \
+                 [x0] "=&v"(x[0]), [x1] "=&v"(x[1]), [x2] "=&v"(x[2]), [x3] "=&v"(x[3]), \
+                 [m0] "+v"(m[0]), [m1] "+v"(m[1]), [m2] "+v"(m[2]), [m3] "+v"(m[3]) \
+               : KVR_RACE_IN, [s0] "v"(s[0]), [s1] "v"(s[1]), [s2] "v"(s[2]), [s3] "v"(s[3]), \
+                 [r0] "v"(row[0]), [r1] "v"(row[1]), [r2] "v"(row[2]), [r3] "v"(row[3]), \
+                 [t0] "v"(t[0]), [t1] "v"(t[1]), [t2] "v"(t[2]), [t3] "v"(t[3]), \
+                 [j0] "v"(j[0]), [j1] "v"(j[1]), [j2] "v"(j[2]), [j3] "v"(j[3]) \
+               : "vcc", "scc", "m0", "memory")
+
+template <int NQ, bool BOUND>
+__device__ __forceinline__ int race_loop(float (&m)[NQ], const float (&s)[NQ], const int (&row)[NQ], int lane, float nlam,
+                                         int u, int cnt, float gout, int& rec_i, int& rec_g, float& amax, int& i4,
+                                         int, int) {
+  float rd, bs, a[NQ], x[NQ];
+  int ad, am, L, R, I, sr, si;
+  int j[NQ], t[NQ];                                    // 4 x token; row address less 256 q (slot q is read at offset 256 q)
+#pragma unroll
+  for (int q = 0; q < NQ; ++q) { j[q] = (lane + 64 * q) * 4; t[q] = row[q] - 256 * q; }
+  u = __builtin_amdgcn_readfirstlane(u);
+  cnt = __builtin_amdgcn_readfirstlane(cnt);
+  nlam = __int_as_float(__builtin_amdgcn_readfirstlane(__float_as_int(nlam)));
+  if constexpr (NQ == 1) {
+    if constexpr (BOUND) KVR_RACE_RUN1(KVR_RACE_BOUND); else KVR_RACE_RUN1("");
+  } else if constexpr (NQ == 2) {
+    if constexpr (BOUND) KVR_RACE_RUN2(KVR_RACE_BOUND); else KVR_RACE_RUN2("");
+  } else if constexpr (NQ == 3) {
+    if constexpr (BOUND) KVR_RACE_RUN3(KVR_RACE_BOUND); else KVR_RACE_RUN3("");
+  } else {
+    static_assert(NQ == 4, "one to four tokens per lane");
+    if constexpr (BOUND) KVR_RACE_RUN4(KVR_RACE_BOUND); else KVR_RACE_RUN4("");
+  }
+  amax = __int_as_float(am);
+  i4 = I;
+  return u;
+}
+#endif
+
+// Algorithm 1's pick chain on one wave, for a head whose cosines sit in the packed triangle `tri` (element (i,j),
+// j <= i, at i(i+1)/2 + j, +inf on the diagonal) and whose scores sit in s_l (-inf for padding): the race in chunks of 64
+// picks, each written to order_l / gain_l once.  Nothing is checked per pick.  Non-finite input is detected afterwards
+// from the logged gains: the picks before the first one without a finite gain are kept and the list is filled up with
+// the lowest tokens < n_live not yet in it.  DIVERSE false is the lambda = 0 branch (top-b, the triangle is not read).
+// Returns the gain of the last pick.
 template <int NQ, bool DIVERSE>
 __device__ __forceinline__ float pick_chain_impl(const float* s_l, const float* tri, int32_t* order_l, float* gain_l,
                                                  int n_live, int b, float lambda, int lane) {
-  typedef __attribute__((address_space(3))) const float* lds_fp;
   const int tri0 = static_cast<int>(reinterpret_cast<uintptr_t>(
       (__attribute__((address_space(3))) const char*)reinterpret_cast<const char*>(tri)));
   float sreg[NQ], mreg[NQ];
-  int ja[NQ], tja[NQ];
+  int tja[NQ];
 #pragma unroll
   for (int q = 0; q < NQ; ++q) {
     const int j = lane + 64 * q;
     sreg[q] = s_l[j];
     mreg[q] = 0.f;
-    ja[q] = j * 4 + tri0;                              // column offset of the token
-    tja[q] = j * (j + 1) * 2 + tri0;                   // start of its row
+    tja[q] = j * (j + 1) * 2 + tri0;                   // start of the token's row
   }
   const float nlam = -lambda;
   int bad_t = b;                                       // first pick without a finite gain
@@ -208,32 +406,22 @@ __device__ __forceinline__ float pick_chain_impl(const float* s_l, const float* 
   for (int c0 = 0; c0 < b; c0 += 64) {
     const int cnt = __builtin_amdgcn_readfirstlane(b - c0 < 64 ? b - c0 : 64);
     int rec_i = 0, rec_g = 0;
-    for (int u = 0; u < cnt; ++u) {
-      float av[NQ];
+    if constexpr (DIVERSE) {
+      float amax; int i4;
+      race_loop<NQ, false>(mreg, sreg, tja, lane, nlam, 0, cnt, 0.f, rec_i, rec_g, amax, i4, tri0,
+                           NQ * 32 * (NQ * 64 + 1));
+      rec_i >>= 2;
+    } else {
+      for (int u = 0; u < cnt; ++u) {
+        float best = sreg[0];
 #pragma unroll
-      for (int q = 0; q < NQ; ++q) av[q] = fmaf(nlam, mreg[q], sreg[q]);
-      float best = av[0];
+        for (int q = 1; q < NQ; ++q) best = hw_max(best, sreg[q]);
+        const float amax = wave_max_uniform(best);
+        unsigned long long e[NQ];
 #pragma unroll
-      for (int q = 1; q < NQ; ++q) best = hw_max(best, av[q]);
-      const float amax = wave_max_uniform(best);
-      unsigned long long e[NQ];
-#pragma unroll
-      for (int q = 0; q < NQ; ++q) e[q] = __ballot(av[q] == amax);
-      const int i = first_of_slots<NQ>(e);             // negative when nothing compares equal (NaN)
-      write_lane2(rec_i, rec_g, i, __float_as_int(amax), u);
-      if constexpr (DIVERSE) {
-        // element (i,j) sits at max(T(i)+j, T(j)+i); the diagonal entry (+inf) retires the pick.
-        // For any i in [-1, 64*NQ) both addresses stay inside the triangle.
-        const int ti4 = i * (i + 1) * 2, i4 = i * 4;
-        float c[NQ];
-#pragma unroll
-        for (int q = 0; q < NQ; ++q) {
-          const int a0 = ti4 + ja[q], a1 = tja[q] + i4;
-          c[q] = *reinterpret_cast<lds_fp>(static_cast<uintptr_t>(static_cast<unsigned>(a0 > a1 ? a0 : a1)));
-        }
-#pragma unroll
-        for (int q = 0; q < NQ; ++q) mreg[q] = hw_max(mreg[q], c[q]);
-      } else {
+        for (int q = 0; q < NQ; ++q) e[q] = __ballot(sreg[q] == amax);
+        const int i = first_of_slots<NQ>(e);           // negative when nothing compares equal (NaN)
+        write_lane2(rec_i, rec_g, i, __float_as_int(amax), u);
 #pragma unroll
         for (int q = 0; q < NQ; ++q) sreg[q] = (lane + 64 * q == i) ? -INFINITY : sreg[q];
       }

@@ -597,18 +597,16 @@ __global__ __launch_bounds__(64 * W, (W <= 4 ? 2 : 1)) void select_lazy_kernel(L
         // Pool slots lane, lane + 64, .. live in lane `lane` (slots are in token order, so the lowest
         // slot is the lowest token; the mapping keeps the triangle reads free of bank conflicts).  A pick is parked in lane np of two registers; the
         // pick lists and the pending-row tables are written once, after the loop.
-        typedef __attribute__((address_space(3))) const float* lds_fp;
         const int tri0 = static_cast<int>(reinterpret_cast<uintptr_t>(
             (__attribute__((address_space(3))) const char*)reinterpret_cast<const char*>(tri)));
         float sq[NQ], mq[NQ];
-        int ja[NQ], tja[NQ];
+        int tja[NQ];
 #pragma unroll
         for (int q = 0; q < NQ; ++q) {
           const int p = lane + 64 * q;
           sq[q] = pool_s[p];
           mq[q] = pool_m[p];
-          ja[q] = p * 4 + tri0;                        // column offset of the slot
-          tja[q] = lz_row_start(p) * 4 + tri0;         // start of its row
+          tja[q] = lz_row_start(p) * 4 + tri0;         // start of the slot's row
         }
         const int jb = __builtin_amdgcn_readfirstlane(jout < 0 ? 0x7fffffff : jout);
         const float gout_u = __int_as_float(__builtin_amdgcn_readfirstlane(__float_as_int(gout)));
@@ -616,42 +614,19 @@ __global__ __launch_bounds__(64 * W, (W <= 4 ? 2 : 1)) void select_lazy_kernel(L
         const int room = __builtin_amdgcn_readfirstlane(min(b - t, kLzMaxPend));
         int np = 0, stop = 0;                        // stop: 1 = bound wins, 2 = nothing finite left
         int rec_i = 0, rec_g = 0;
+        int until = room;
+        float bound = gout_u;
         while (np < room) {
-          float av[NQ];
-#pragma unroll
-          for (int q = 0; q < NQ; ++q) av[q] = fmaf(nlam, mq[q], sq[q]);
-          float best = av[0];
-#pragma unroll
-          for (int q = 1; q < NQ; ++q) best = hw_max(best, av[q]);
-          const float amax = wave_max_uniform(best);
-          unsigned long long e[NQ];
-#pragma unroll
-          for (int q = 0; q < NQ; ++q) e[q] = __ballot(av[q] == amax);
-          const int i = first_of_slots<NQ>(e);       // negative when nothing compares equal (NaN)
-          if (!(amax > gout_u)) {                    // rare: the bound wins, a tie with it, or nothing finite
-            if (!(amax > -INFINITY)) { stop = no_out ? 2 : 1; break; }
-            const int ti = __builtin_amdgcn_readfirstlane(pool_tok[i < 0 ? 0 : i]);
-            if (!(amax == gout_u && ti < jb)) { stop = 1; break; }
-          }
-          write_lane2(rec_i, rec_g, i, __float_as_int(amax), np);
-          np = __builtin_amdgcn_readfirstlane(np + 1);   // keeps the loop control on the scalar unit
-          // element (i,j) of the triangle sits at max(start(i)+j, start(j)+i); the diagonal (+inf) retires i.
-          // For any i in [-1, 64*NQ) the larger address stays inside the triangle.
-          const int ti4 = lz_row_start(i) * 4, i4 = i * 4;
-          float c[NQ];
-#pragma unroll
-          for (int q = 0; q < NQ; ++q) {
-            const int x0 = ti4 + ja[q], x1 = tja[q] + i4;
-#ifdef KVR_BOUNDS
-            const int xa = kvr_ix(((x0 > x1 ? x0 : x1) - tri0) >> 2, Cfg::kTriBytes / 4, 105) * 4 + tri0;   // 105: triangle element of the race
-#else
-            const int xa = x0 > x1 ? x0 : x1;
-#endif
-            c[q] = *reinterpret_cast<lds_fp>(static_cast<uintptr_t>(static_cast<unsigned>(xa)));
-          }
-#pragma unroll
-          for (int q = 0; q < NQ; ++q) mq[q] = hw_max(mq[q], c[q]);
+          float amax; int i4;
+          np = race_loop<NQ, true>(mq, sq, tja, lane, nlam, np, until, bound, rec_i, rec_g, amax, i4, tri0, Cfg::kTriBytes / 4);
+          if (np == until) { until = room; bound = gout_u; continue; }
+          // rare: the bound wins, a tie with it, or nothing finite
+          if (!(amax > -INFINITY)) { stop = no_out ? 2 : 1; break; }
+          if (!(amax == gout_u && __builtin_amdgcn_readfirstlane(pool_tok[i4 >> 2]) < jb)) { stop = 1; break; }
+          until = np + 1;                            // a tie that the pool's lower token wins: this one pick passes
+          bound = -INFINITY;
         }
+        rec_i >>= 2;
 #pragma unroll
         for (int q = 0; q < NQ; ++q) pool_m[lane + 64 * q] = mq[q];   // the pool's m is authoritative
         if (lane < np) {

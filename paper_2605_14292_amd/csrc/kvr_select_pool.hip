@@ -354,41 +354,31 @@ __global__ __launch_bounds__(64 * W, (W <= 4 ? 2 : 1)) void select_pool_kernel(P
         // is parked in lane np of two registers; the pick lists and the pending-row tables are written
         // once, after the loop.
         const int p0 = lane, p1 = lane + 64;
-        const float s0 = pool_s[p0], s1 = pool_s[p1];
-        float m0 = pool_m[p0], m1 = pool_m[p1];
-        typedef __attribute__((address_space(3))) const float* lds_fp;
+        const float sq[2] = {pool_s[p0], pool_s[p1]};
+        float mq[2] = {pool_m[p0], pool_m[p1]};
         const int tri0 = static_cast<int>(reinterpret_cast<uintptr_t>(
             (__attribute__((address_space(3))) const char*)reinterpret_cast<const char*>(tri)));
-        const int ja0 = p0 * 4 + tri0, ja1 = p1 * 4 + tri0;
-        const int tja0 = p0 * (p0 + 1) * 2 + tri0, tja1 = p1 * (p1 + 1) * 2 + tri0;
+        const int tja[2] = {p0 * (p0 + 1) * 2 + tri0, p1 * (p1 + 1) * 2 + tri0};
         const int jb = __builtin_amdgcn_readfirstlane(jout < 0 ? 0x7fffffff : jout);
         const float gout_u = __int_as_float(__builtin_amdgcn_readfirstlane(__float_as_int(gout)));
         const bool no_out = __builtin_amdgcn_readfirstlane(jout) < 0;
         const int room = __builtin_amdgcn_readfirstlane(min(b - t, kPoolMaxPend));
         int np = 0, stop = 0;                        // stop: 1 = bound wins, 2 = nothing finite left
         int rec_i = 0, rec_g = 0;
+        int until = room;
+        float bound = gout_u;
         while (np < room) {
-          const float a0 = fmaf(nlam, m0, s0), a1 = fmaf(nlam, m1, s1);
-          const float amax = wave_max_uniform(hw_max(a0, a1));
-          const unsigned long long e0 = __ballot(a0 == amax), e1 = __ballot(a1 == amax);
-          const unsigned long long e01[2] = {e0, e1};
-          const int i = first_of_slots<2>(e01);
-          if (!(amax > gout_u)) {                    // rare: the bound wins, a tie with it, or nothing finite
-            if (!(amax > -INFINITY)) { stop = no_out ? 2 : 1; break; }
-            const int ti = __builtin_amdgcn_readfirstlane(pool_tok[i < 0 ? 0 : i]);
-            if (!(amax == gout_u && ti < jb)) { stop = 1; break; }
-          }
-          write_lane2(rec_i, rec_g, i, __float_as_int(amax), np);
-          np = __builtin_amdgcn_readfirstlane(np + 1);   // keeps the loop control on the scalar unit
-          // element (i,j) of the triangle sits at max(T(i)+j, T(j)+i); the diagonal (+inf) retires i
-          const int ti4 = i * (i + 1) * 2, i4 = i * 4;
-          const int x00 = ti4 + ja0, x01 = tja0 + i4, x10 = ti4 + ja1, x11 = tja1 + i4;
-          const float c0 = *reinterpret_cast<lds_fp>(static_cast<uintptr_t>(static_cast<unsigned>(x00 > x01 ? x00 : x01)));
-          const float c1 = *reinterpret_cast<lds_fp>(static_cast<uintptr_t>(static_cast<unsigned>(x10 > x11 ? x10 : x11)));
-          m0 = hw_max(m0, c0);
-          m1 = hw_max(m1, c1);
+          float amax; int i4;
+          np = race_loop<2, true>(mq, sq, tja, lane, nlam, np, until, bound, rec_i, rec_g, amax, i4, tri0, kPool * (kPool + 1) / 2);
+          if (np == until) { until = room; bound = gout_u; continue; }
+          // rare: the bound wins, a tie with it, or nothing finite
+          if (!(amax > -INFINITY)) { stop = no_out ? 2 : 1; break; }
+          if (!(amax == gout_u && __builtin_amdgcn_readfirstlane(pool_tok[i4 >> 2]) < jb)) { stop = 1; break; }
+          until = np + 1;                            // a tie that the pool's lower token wins: this one pick passes
+          bound = -INFINITY;
         }
-        pool_m[p0] = m0; pool_m[p1] = m1;            // the pool's m is authoritative
+        rec_i >>= 2;
+        pool_m[p0] = mq[0]; pool_m[p1] = mq[1];          // the pool's m is authoritative
         if (lane < np) {
           const int ri = kvr_ix(rec_i, kPool, 206);      // 206: pool slot of a pick
           const int tp = kvr_ix(t + lane, bcap, 207);    // 207: number of a pick
