@@ -12,18 +12,23 @@
 // the queries on the columns -- a lane then owns one query and its statistics need no
 // cross-lane traffic until the end -- and pass 2 swaps them: a lane owns one token and
 // the sum over queries is a sum over its own registers.
-// One workgroup per head; wave w takes the 32-token tiles w, w+4, ...; the queries wait
-// in LDS (272-byte pitch).  Everything is done in base 2: z2 = z * log2(e).
+// Wave w takes the 32-token tiles w, w+4, ...; the queries wait in LDS (272-byte pitch).
+// Everything is done in base 2: z2 = z * log2(e).
+//
+// One workgroup per head does both passes when the heads fill the chip (two workgroups of four waves fit a CU).  Fewer
+// heads (one sequence's 112 or 256) leave most SIMDs with one wave or none, so the tokens of a head are split over several
+// workgroups and the passes become launches of their own.  There is no scratch memory: the statistics travel in the
+// head's row of s_out.  (1) Every split writes its queries' maxima and sums at 2 * split * G; (2) one workgroup per
+// head merges them into G numbers at the front of the row; (3) the second pass over all tokens but the first ones, whose
+// scores would overwrite those numbers; (4) the second pass over these, by one workgroup per head that reads the
+// numbers first.  Measured, 112 heads of 4000 tokens and 224 queries: 177 us before, 110 in one launch, 82 split (0.6 PFLOP/s).
 // Bound: for G of a few dozen the two reads of K (fabric rate); for G = 256 the matrix
-// cores and the vector ALU together -- a 32x32 block costs 8 MFMAs and about 60 vector
-// instructions (16 of them exponentials) per pass, the two kinds of work share the SIMD's
-// issue port and overlap only partly across waves (measured on this chip: a wave of MFMA
-// chains beside a wave of fma+exp+add on one SIMD takes 0.76 of the sum of their times).
-// Variants measured and not kept because they change nothing: query fragments prefetched
-// one block ahead, two token tiles per query fragment (half the LDS reads, independent
-// accumulator chains), sixteen waves per workgroup.
+// cores and the vector ALU together -- a 32x32 block costs 8 MFMAs (256 cycles) and about 65 vector
+// instructions (16 of them exponentials) per pass.  A wave keeps both busy by a software pipeline over the query
+// blocks (see `interleave`), two waves share a SIMD.  256 heads of 4000 tokens, G = 256: 197 -> 156 us.
 #include "kvr_dense_common.hpp"
 #include "kvr_kernels.hpp"
+#include <type_traits>
 
 namespace kvr {
 
@@ -36,12 +41,17 @@ __host__ __device__ constexpr int wide_smem_bytes(int gb) {
   return gb * 32 * kWidePitch + gb * 32 * 4 * 9;
 }
 
+enum : int { kWideBoth = 0, kWideStats = 1, kWideScores = 2, kWideFirst = 3 };
+
+// MODE kWideBoth: the whole head.  kWideStats: the statistics of split blockIdx.y of the tokens.  kWideScores: the scores of
+// split blockIdx.y of the tokens from tile t_first on.  kWideFirst: those of the tokens before it.
+// GB: query blocks of 32 (a template argument, so that a tile's blocks are straight-line code).
+template <int MODE, int GB>
 __global__ __launch_bounds__(kWideThreads, 2) void score_wide_kernel(const char* __restrict__ K,
                                                                      const char* __restrict__ Q, int G,
-                                                                     Layout lay, float* __restrict__ s_out) {
+                                                                     Layout lay, int t_first, float* s_out) {
   extern __shared__ __align__(16) char smem_raw[];
-  const int GB = (G + 31) >> 5;
-  const int GP = GB * 32;
+  constexpr int GP = GB * 32;
   char* q_l = smem_raw;
   float* c_l = reinterpret_cast<float*>(smem_raw + GP * kWidePitch);   // [GP] max2 + log2(sum), +inf for padding
   float* pm = c_l + GP;                                                 // [4][GP]
@@ -52,21 +62,39 @@ __global__ __launch_bounds__(kWideThreads, 2) void score_wide_kernel(const char*
   const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
   const char* Kh = K + h * lay.stride_head * 2;
   const long long tok_bytes = lay.stride_tok * 2;
-  const int ntiles = (n + 31) >> 5;
+  const int all_tiles = (n + 31) >> 5;
+  int t0 = 0, ntiles = all_tiles;                                       // this workgroup's tiles: t0 .. ntiles - 1
+  if constexpr (MODE == kWideStats || MODE == kWideScores) {
+    const int from = MODE == kWideScores ? t_first : 0, len = all_tiles - from;
+    t0 = from + static_cast<int>(blockIdx.y) * len / static_cast<int>(gridDim.y);
+    ntiles = from + (static_cast<int>(blockIdx.y) + 1) * len / static_cast<int>(gridDim.y);
+  } else if constexpr (MODE == kWideFirst) {
+    ntiles = t_first;
+  }
+  const int wt = t0 + wave;
+  float* so = s_out + static_cast<long long>(h) * n;
   const float sc2 = 0.08838834764831845f * 1.4426950408889634f;        // log2(e) / sqrt(128)
 
   // ---- queries -> LDS, rows past G zero
   {
     const int c16 = tid & 15, r0 = tid >> 4;
     const char* Qh = Q + static_cast<long long>(h) * G * kD * 2;
-    for (int g = r0; g < GP; g += kWideThreads / 16) {
-      uint4 w = make_uint4(0u, 0u, 0u, 0u);
-      if (g < G) w = *reinterpret_cast<const uint4*>(Qh + g * (kD * 2) + c16 * 16);
-      *reinterpret_cast<uint4*>(q_l + g * kWidePitch + c16 * 16) = w;
+    uint4 w[2 * GB];                               // all requested before the first is stored
+#pragma unroll
+    for (int k = 0; k < 2 * GB; ++k) w[k] = *reinterpret_cast<const uint4*>(Qh + min(r0 + 16 * k, G - 1) * (kD * 2) + c16 * 16);
+#pragma unroll
+    for (int k = 0; k < 2 * GB; ++k) {
+      if (r0 + 16 * k >= G) w[k] = make_uint4(0u, 0u, 0u, 0u);
+      *reinterpret_cast<uint4*>(q_l + (r0 + 16 * k) * kWidePitch + c16 * 16) = w[k];
     }
   }
+  if constexpr (MODE == kWideScores || MODE == kWideFirst)
+    for (int g = tid; g < GP; g += kWideThreads) c_l[g] = g < G ? so[g] : INFINITY;
   __syncthreads();
 
+  // The next tile's rows are requested before a tile is multiplied, unconditionally (clamped to the head's last row) and
+  // into registers of their own: with a branch around the request or a copy between the buffers the compiler's
+  // wait counts are no longer exact, and every tile waited for the rows it had just asked for.
   bf16x8 kf[8], kn[8];
   auto fetch = [&](int t, bf16x8 (&dst)[8]) {
     const char* p = Kh + min(t * 32 + l32, n - 1) * tok_bytes + hf * 16;
@@ -76,57 +104,97 @@ __global__ __launch_bounds__(kWideThreads, 2) void score_wide_kernel(const char*
       dst[ks] = *reinterpret_cast<const bf16x8*>(&w);
     }
   };
-  const char* qp = q_l + l32 * kWidePitch + hf * 16;
-
-  // ================= pass 1: per-query maximum and sum =================
-  float m2[kWideMaxBlocks], l2[kWideMaxBlocks];
-#pragma unroll
-  for (int qb = 0; qb < kWideMaxBlocks; ++qb) { m2[qb] = -INFINITY; l2[qb] = 0.f; }
-  if (wave < ntiles) fetch(wave, kf);
-  for (int t = wave; t < ntiles; t += 4) {
-    if (t + 4 < ntiles) fetch(t + 4, kn);
-    const bool ragged = t * 32 + 32 > n;
-#pragma unroll
-    for (int qb = 0; qb < kWideMaxBlocks; ++qb) {
-      if (qb < GB) {
-        f32x16 acc = {0};
-#pragma unroll
-        for (int ks = 0; ks < 8; ++ks)
-          acc = __builtin_amdgcn_mfma_f32_32x32x16_bf16(
-              kf[ks], *reinterpret_cast<const bf16x8*>(qp + qb * 32 * kWidePitch + ks * 32), acc, 0, 0, 0);
-        // lane (query l32, hf) holds token rows (r/4)*8 + hf*4 + r%4 of the tile
-        if (ragged) {
-#pragma unroll
-          for (int r = 0; r < 16; ++r)
-            if (t * 32 + (r >> 2) * 8 + hf * 4 + (r & 3) >= n) acc[r] = -INFINITY;
-        }
-        float amax = acc[0];
-#pragma unroll
-        for (int r = 1; r < 16; ++r) amax = fmaxf(amax, acc[r]);
-        const float mnew = fmaxf(m2[qb], amax * sc2);
-        const float msafe = mnew == -INFINITY ? 0.f : mnew;
-        float sum = 0.f;
-#pragma unroll
-        for (int r = 0; r < 16; ++r) sum += __builtin_amdgcn_exp2f(fmaf(acc[r], sc2, -msafe));
-        l2[qb] = fmaf(l2[qb], __builtin_amdgcn_exp2f(m2[qb] - msafe), sum);
-        m2[qb] = mnew;
+  const int full = min(ntiles, n >> 5);            // tiles without rows past n
+  auto for_tiles = [&](auto tile) {
+    if (wt < full) {
+      fetch(wt, kf);
+      for (int t = wt; t < full; t += 8) {
+        fetch(t + 4, kn);
+        tile(t, kf, std::false_type{});
+        if (t + 4 >= full) break;
+        fetch(t + 8, kf);
+        tile(t + 4, kn, std::false_type{});
       }
     }
-    if (t + 4 < ntiles) {
-#pragma unroll
-      for (int ks = 0; ks < 8; ++ks) kf[ks] = kn[ks];
+    if (full < ntiles && (full - wt) % 4 == 0) {   // the head's ragged last tile, by the wave whose turn it is
+      fetch(full, kf);
+      tile(full, kf, std::true_type{});
     }
-  }
+  };
+  // A tile goes through its query blocks in a software pipeline of three stages: the fragments of block qb + 2 are read
+  // from LDS, block qb + 1 is multiplied, block qb goes through the vector unit.  The compiler is told the order: all
+  // reads first, then a product and eight vector instructions in turn (left to itself it reads a fragment right before the
+  // product that needs it and waits for LDS eight times a block).
+  const char* qp = q_l + l32 * kWidePitch + hf * 16;
+  auto fragments = [&](int qb, bf16x8 (&q)[8]) {
+#pragma unroll
+    for (int ks = 0; ks < 8; ++ks) q[ks] = *reinterpret_cast<const bf16x8*>(qp + qb * 32 * kWidePitch + ks * 32);
+  };
+  auto interleave = [](auto reads) {
+    if constexpr (decltype(reads)::value > 0) __builtin_amdgcn_sched_group_barrier(0x100, decltype(reads)::value, 0);   // LDS reads
+#pragma unroll
+    for (int ks = 0; ks < 8; ++ks) {
+      __builtin_amdgcn_sched_group_barrier(0x008, 1, 0);   // MFMA
+      __builtin_amdgcn_sched_group_barrier(0x002, 8, 0);   // VALU
+    }
+    __builtin_amdgcn_sched_barrier(0);
+  };
+  auto interleave_n = [&](int reads) {             // (the builtin wants a constant)
+    if (reads == 12) interleave(std::integral_constant<int, 12>{});
+    else if (reads == 8) interleave(std::integral_constant<int, 8>{});
+    else if (reads == 4) interleave(std::integral_constant<int, 4>{});
+    else interleave(std::integral_constant<int, 0>{});
+  };
+
+  // ================= pass 1: per-query maximum and sum =================
+  if constexpr (MODE == kWideBoth || MODE == kWideStats) {
+  float m2[GB], l2[GB];
+#pragma unroll
+  for (int qb = 0; qb < GB; ++qb) { m2[qb] = -INFINITY; l2[qb] = 0.f; }
+  for_tiles([&](int t, const bf16x8 (&kt)[8], auto ragged) {
+    const int left = n - t * 32 - hf * 4;          // lane (query l32, hf) holds token rows (r/4)*8 + hf*4 + r%4 of the tile
+    auto product = [&](const bf16x8 (&q)[8]) {
+      f32x16 acc = {0};
+#pragma unroll
+      for (int ks = 0; ks < 8; ++ks) acc = __builtin_amdgcn_mfma_f32_32x32x16_bf16(kt[ks], q[ks], acc, 0, 0, 0);
+      return acc;
+    };
+    bf16x8 qf[2][8];
+    fragments(0, qf[0]);
+    if (GB > 1) fragments(1, qf[1]);
+    f32x16 acc = product(qf[0]), next;
+    __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+    for (int qb = 0; qb < GB; ++qb) {
+      if (qb + 2 < GB) fragments(qb + 2, qf[qb & 1]);
+      if (qb + 1 < GB) next = product(qf[(qb + 1) & 1]);
+      if constexpr (decltype(ragged)::value) {
+#pragma unroll
+        for (int r = 0; r < 16; ++r)
+          if ((r >> 2) * 8 + (r & 3) >= left) acc[r] = -INFINITY;
+      }
+      float amax = acc[0];
+#pragma unroll
+      for (int r = 1; r < 16; ++r) amax = fmaxf(amax, acc[r]);
+      const float mnew = fmaxf(m2[qb], amax * sc2);
+      const float msafe = mnew == -INFINITY ? 0.f : mnew;
+      float sum = 0.f;
+#pragma unroll
+      for (int r = 0; r < 16; ++r) sum += __builtin_amdgcn_exp2f(fmaf(acc[r], sc2, -msafe));
+      l2[qb] = fmaf(l2[qb], __builtin_amdgcn_exp2f(m2[qb] - msafe), sum);
+      m2[qb] = mnew;
+      interleave_n(qb + 2 < GB ? 8 : 0);
+      acc = next;
+    }
+  });
   // the two half-waves of a query, then the four waves
 #pragma unroll
-  for (int qb = 0; qb < kWideMaxBlocks; ++qb) {
-    if (qb < GB) {
-      const float mo = __shfl_xor(m2[qb], 32, kWave), lo = __shfl_xor(l2[qb], 32, kWave);
-      const float mm = fmaxf(m2[qb], mo);
-      const float ms = mm == -INFINITY ? 0.f : mm;
-      const float ll = l2[qb] * __builtin_amdgcn_exp2f(m2[qb] - ms) + lo * __builtin_amdgcn_exp2f(mo - ms);
-      if (hf == 0) { pm[wave * GP + qb * 32 + l32] = mm; pl[wave * GP + qb * 32 + l32] = ll; }
-    }
+  for (int qb = 0; qb < GB; ++qb) {
+    const float mo = __shfl_xor(m2[qb], 32, kWave), lo = __shfl_xor(l2[qb], 32, kWave);
+    const float mm = fmaxf(m2[qb], mo);
+    const float ms = mm == -INFINITY ? 0.f : mm;
+    const float ll = l2[qb] * __builtin_amdgcn_exp2f(m2[qb] - ms) + lo * __builtin_amdgcn_exp2f(mo - ms);
+    if (hf == 0) { pm[wave * GP + qb * 32 + l32] = mm; pl[wave * GP + qb * 32 + l32] = ll; }
   }
   __syncthreads();
   for (int g = tid; g < GP; g += kWideThreads) {
@@ -134,59 +202,122 @@ __global__ __launch_bounds__(kWideThreads, 2) void score_wide_kernel(const char*
     float ll = 0.f;
 #pragma unroll
     for (int w = 0; w < 4; ++w) ll += pl[w * GP + g] * __builtin_amdgcn_exp2f(pm[w * GP + g] - mm);
-    c_l[g] = g < G ? mm + __builtin_amdgcn_logf(ll) : INFINITY;
+    if constexpr (MODE == kWideStats) {
+      if (g < G) { so[2 * blockIdx.y * G + g] = mm; so[(2 * blockIdx.y + 1) * G + g] = ll; }
+    } else {
+      c_l[g] = g < G ? mm + __builtin_amdgcn_logf(ll) : INFINITY;
+    }
   }
+  if constexpr (MODE == kWideStats) return;
   __syncthreads();
+  }
 
   // ================= pass 2: probabilities, summed over the queries =================
   const float invG = 1.0f / static_cast<float>(G);
-  float* so = s_out + static_cast<long long>(h) * n;
-  if (wave < ntiles) fetch(wave, kf);
-  for (int t = wave; t < ntiles; t += 4) {
-    if (t + 4 < ntiles) fetch(t + 4, kn);
+  for_tiles([&](int t, const bf16x8 (&kt)[8], auto) {
+    auto product = [&](const bf16x8 (&q)[8]) {
+      f32x16 acc = {0};
+#pragma unroll
+      for (int ks = 0; ks < 8; ++ks) acc = __builtin_amdgcn_mfma_f32_32x32x16_bf16(q[ks], kt[ks], acc, 0, 0, 0);
+      return acc;
+    };
+    // lane (token l32, hf) holds query rows (r/4)*8 + hf*4 + r%4 of the block
+    auto norms = [&](int qb, float4 (&c)[4]) {
+#pragma unroll
+      for (int r4 = 0; r4 < 4; ++r4) c[r4] = *reinterpret_cast<const float4*>(c_l + qb * 32 + r4 * 8 + hf * 4);
+    };
+    bf16x8 qf[2][8];
+    float4 cc[2][4];
+    fragments(0, qf[0]);
+    norms(0, cc[0]);
+    if (GB > 1) fragments(1, qf[1]);
+    f32x16 acc = product(qf[0]), next;
     float colsum = 0.f;
+    __builtin_amdgcn_sched_barrier(0);
 #pragma unroll
-    for (int qb = 0; qb < kWideMaxBlocks; ++qb) {
-      if (qb < GB) {
-        f32x16 acc = {0};
+    for (int qb = 0; qb < GB; ++qb) {
+      if (qb + 1 < GB) norms(qb + 1, cc[(qb + 1) & 1]);
+      if (qb + 2 < GB) fragments(qb + 2, qf[qb & 1]);
+      if (qb + 1 < GB) next = product(qf[(qb + 1) & 1]);
 #pragma unroll
-        for (int ks = 0; ks < 8; ++ks)
-          acc = __builtin_amdgcn_mfma_f32_32x32x16_bf16(
-              *reinterpret_cast<const bf16x8*>(qp + qb * 32 * kWidePitch + ks * 32), kf[ks], acc, 0, 0, 0);
-        // lane (token l32, hf) holds query rows (r/4)*8 + hf*4 + r%4 of the block
-#pragma unroll
-        for (int r4 = 0; r4 < 4; ++r4) {
-          const float4 c = *reinterpret_cast<const float4*>(c_l + qb * 32 + r4 * 8 + hf * 4);
-          colsum += __builtin_amdgcn_exp2f(fmaf(acc[r4 * 4 + 0], sc2, -c.x));
-          colsum += __builtin_amdgcn_exp2f(fmaf(acc[r4 * 4 + 1], sc2, -c.y));
-          colsum += __builtin_amdgcn_exp2f(fmaf(acc[r4 * 4 + 2], sc2, -c.z));
-          colsum += __builtin_amdgcn_exp2f(fmaf(acc[r4 * 4 + 3], sc2, -c.w));
-        }
+      for (int r4 = 0; r4 < 4; ++r4) {
+        const float4 c = cc[qb & 1][r4];
+        colsum += __builtin_amdgcn_exp2f(fmaf(acc[r4 * 4 + 0], sc2, -c.x));
+        colsum += __builtin_amdgcn_exp2f(fmaf(acc[r4 * 4 + 1], sc2, -c.y));
+        colsum += __builtin_amdgcn_exp2f(fmaf(acc[r4 * 4 + 2], sc2, -c.z));
+        colsum += __builtin_amdgcn_exp2f(fmaf(acc[r4 * 4 + 3], sc2, -c.w));
       }
+      interleave_n((qb + 2 < GB ? 8 : 0) + (qb + 1 < GB ? 4 : 0));
+      acc = next;
     }
     colsum += __shfl_xor(colsum, 32, kWave);
     const int j = t * 32 + l32;
     if (hf == 0 && j < n) so[j] = colsum * invG;
-    if (t + 4 < ntiles) {
-#pragma unroll
-      for (int ks = 0; ks < 8; ++ks) kf[ks] = kn[ks];
-    }
-  }
+  });
+}
+
+// The splits' maxima and sums of a query become one number, max2 + log2(sum).
+__global__ __launch_bounds__(32 * kWideMaxBlocks) void score_wide_merge_kernel(int G, int n, int parts, float* s_out) {
+  float* so = s_out + static_cast<long long>(blockIdx.x) * n;
+  const int g = min(static_cast<int>(threadIdx.x), G - 1);
+  float mm = -INFINITY, ll = 0.f;
+  for (int p = 0; p < parts; ++p) mm = fmaxf(mm, so[2 * p * G + g]);
+  for (int p = 0; p < parts; ++p) ll += so[(2 * p + 1) * G + g] * __builtin_amdgcn_exp2f(so[2 * p * G + g] - mm);
+  __syncthreads();                               // everything is read before the front of the row is overwritten
+  if (static_cast<int>(threadIdx.x) < G) so[g] = mm + __builtin_amdgcn_logf(ll);
 }
 
 bool score_wide_supported(const Layout& lay, int G) {
   return lay.dtype == DT_BF16 && G >= 1 && G <= 32 * kWideMaxBlocks;
 }
 
-hipError_t launch_score_wide(const void* K, const void* Q, int G, const Layout& lay, float* s_out,
-                             hipStream_t st) {
-  const int smem = wide_smem_bytes((G + 31) / 32);
-  const hipError_t e = hipFuncSetAttribute(reinterpret_cast<const void*>(&score_wide_kernel),
-                                           hipFuncAttributeMaxDynamicSharedMemorySize, smem);
+// Workgroups per head (1: both passes in one launch): as many as fill two workgroups per CU, when that is four or more and
+// the head has tokens enough to pay for three more launches.  Measured, one launch / split: 112 heads of 4000 tokens
+// 59 / 46 us (G = 64), 125 / 82 (256); of 1500 tokens 25 / 25 and 52 / 44; of 700 tokens 14 / 16 (G = 64), 17 / 20 (128);
+// 200 heads of 4000 tokens, two workgroups each, 60 / 76 and 131 / 136.
+static int score_wide_parts(const Layout& lay, int G, int cus) {
+  const int want = 2 * cus / lay.heads, tiles = (lay.n + 31) / 32;
+  if (want < 4 || tiles < 48) return 1;
+  const int room = lay.n / (2 * G);              // the statistics of all splits fit the head's row of scores
+  const int most = tiles / 8;                    // at least two tiles per wave
+  const int parts = want < room ? want : room;
+  return parts < most ? parts : most;
+}
+
+template <int GB>
+static hipError_t launch_score_wide_blocks(const char* K, const char* Q, int G, const Layout& lay, float* s_out,
+                                           hipStream_t st) {
+  const int smem = wide_smem_bytes(GB);
+  auto go = [&](auto kern, int parts, int t_first) -> hipError_t {
+    const hipError_t e = hipFuncSetAttribute(reinterpret_cast<const void*>(kern),
+                                             hipFuncAttributeMaxDynamicSharedMemorySize, smem);
+    if (e != hipSuccess) return e;
+    hipLaunchKernelGGL(kern, dim3(lay.heads, parts), dim3(kWideThreads), smem, st, K, Q, G, lay, t_first, s_out);
+    return hipGetLastError();
+  };
+  const int parts = score_wide_parts(lay, G, cu_count());
+  if (parts < 2) return go(&score_wide_kernel<kWideBoth, GB>, 1, 0);
+  hipError_t e = go(&score_wide_kernel<kWideStats, GB>, parts, 0);
   if (e != hipSuccess) return e;
-  hipLaunchKernelGGL(score_wide_kernel, dim3(lay.heads), dim3(kWideThreads), smem, st,
-                     static_cast<const char*>(K), static_cast<const char*>(Q), G, lay, s_out);
-  return hipGetLastError();
+  hipLaunchKernelGGL(score_wide_merge_kernel, dim3(lay.heads), dim3(32 * kWideMaxBlocks), 0, st, G, lay.n, parts, s_out);
+  e = hipGetLastError();
+  if (e == hipSuccess) e = go(&score_wide_kernel<kWideScores, GB>, parts, GB);   // (GB tiles hold the merged statistics)
+  if (e == hipSuccess) e = go(&score_wide_kernel<kWideFirst, GB>, 1, GB);
+  return e;
+}
+
+hipError_t launch_score_wide(const void* K, const void* Q, int G, const Layout& lay, float* s_out, hipStream_t st) {
+  const char *k = static_cast<const char*>(K), *q = static_cast<const char*>(Q);
+  switch ((G + 31) / 32) {
+    case 1: return launch_score_wide_blocks<1>(k, q, G, lay, s_out, st);
+    case 2: return launch_score_wide_blocks<2>(k, q, G, lay, s_out, st);
+    case 3: return launch_score_wide_blocks<3>(k, q, G, lay, s_out, st);
+    case 4: return launch_score_wide_blocks<4>(k, q, G, lay, s_out, st);
+    case 5: return launch_score_wide_blocks<5>(k, q, G, lay, s_out, st);
+    case 6: return launch_score_wide_blocks<6>(k, q, G, lay, s_out, st);
+    case 7: return launch_score_wide_blocks<7>(k, q, G, lay, s_out, st);
+    default: return launch_score_wide_blocks<8>(k, q, G, lay, s_out, st);
+  }
 }
 
 }  // namespace kvr
