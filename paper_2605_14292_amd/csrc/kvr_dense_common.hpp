@@ -132,6 +132,47 @@ __device__ __forceinline__ float half_sum_at_31(float v) {
   return v;
 }
 
+typedef __attribute__((ext_vector_type(4))) float f32x4;
+
+// A cosine triangle whose row i (columns 0..i) takes (i + 4) & ~3 floats, so that four neighbouring columns of a row are
+// one aligned 16-byte store: row i = 4g + r starts at float 4 (g + 1)(2g + r).  Element (i, j), j <= i, sits at
+// start(i) + j; start(i) + j >= start(j) + i holds for i > j as in the packed triangle, so the race reads
+// max(start(i) + j, start(j) + i) without knowing which index is the larger.
+__device__ __forceinline__ int padded_row_start(int i) { return 4 * ((i >> 2) + 1) * (2 * (i >> 2) + (i & 3)); }
+__host__ __device__ constexpr int padded_tri_floats(int n) { return 8 * (n / 4) * (n / 4 + 1); }   // n a multiple of 4
+
+// Writes one 32x32 tile of raw dot products as cosines into a padded triangle.  acc comes from the MFMA with the
+// column block J as operand A and the row block I as operand B: lane (row = lane & 31, hf = lane >> 5) holds
+// columns 8R + 4hf .. + 3 of its row in acc[4R .. 4R+3].  The diagonal holds +inf (the row of a pick retires it);
+// what a store writes past the diagonal stays inside the row's padding and is never read.
+__device__ __forceinline__ void write_cos_tile_padded(float* tri, const float* rinv, const f32x16& acc, int I, int J, int lane) {
+  const int hf = lane >> 5;
+  const int row = I * 32 + (lane & 31);
+  const float rrow = rinv[row];
+  float4 rc[4];                                       // the columns' inverse norms, all requested before the first use
+#pragma unroll
+  for (int R = 0; R < 4; ++R) rc[R] = *reinterpret_cast<const float4*>(rinv + J * 32 + 8 * R + 4 * hf);
+  float* dst = tri + padded_row_start(row) + J * 32 + 4 * hf;
+  if (I != J) {                                       // two code paths: no per-element predicate off the diagonal
+#pragma unroll
+    for (int R = 0; R < 4; ++R)
+      *reinterpret_cast<float4*>(dst + 8 * R) = make_float4(acc[4 * R] * rrow * rc[R].x, acc[4 * R + 1] * rrow * rc[R].y,
+                                                            acc[4 * R + 2] * rrow * rc[R].z, acc[4 * R + 3] * rrow * rc[R].w);
+  } else {
+#pragma unroll
+    for (int R = 0; R < 4; ++R) {
+      const int col = J * 32 + 8 * R + 4 * hf;
+      float4 v = make_float4(acc[4 * R] * rrow * rc[R].x, acc[4 * R + 1] * rrow * rc[R].y,
+                             acc[4 * R + 2] * rrow * rc[R].z, acc[4 * R + 3] * rrow * rc[R].w);
+      if (col == row) v.x = INFINITY;
+      if (col + 1 == row) v.y = INFINITY;
+      if (col + 2 == row) v.z = INFINITY;
+      if (col + 3 == row) v.w = INFINITY;
+      if (col <= row) *reinterpret_cast<float4*>(dst + 8 * R) = v;
+    }
+  }
+}
+
 // Scales one 32x32 tile of raw dot products to cosines and writes it into the packed
 // triangle (element (i,j), j <= i, at i(i+1)/2 + j).  The diagonal entry holds +inf: reading
 // the row of a pick drives the pick's own m to +inf and its gain to -inf, which is how a
@@ -381,12 +422,12 @@ __device__ __forceinline__ int race_loop(float (&m)[NQ], const float (&s)[NQ], c
 #endif
 
 // Algorithm 1's pick chain on one wave, for a head whose cosines sit in the packed triangle `tri` (element (i,j),
-// j <= i, at i(i+1)/2 + j, +inf on the diagonal) and whose scores sit in s_l (-inf for padding): the race in chunks of 64
+// j <= i, at i(i+1)/2 + j, or at padded_row_start(i) + j if PADDED, +inf on the diagonal) and whose scores sit in s_l (-inf for padding): the race in chunks of 64
 // picks, each written to order_l / gain_l once.  Nothing is checked per pick.  Non-finite input is detected afterwards
 // from the logged gains: the picks before the first one without a finite gain are kept and the list is filled up with
 // the lowest tokens < n_live not yet in it.  DIVERSE false is the lambda = 0 branch (top-b, the triangle is not read).
 // Returns the gain of the last pick.
-template <int NQ, bool DIVERSE>
+template <int NQ, bool DIVERSE, bool PADDED>
 __device__ __forceinline__ float pick_chain_impl(const float* s_l, const float* tri, int32_t* order_l, float* gain_l,
                                                  int n_live, int b, float lambda, int lane) {
   const int tri0 = static_cast<int>(reinterpret_cast<uintptr_t>(
@@ -398,7 +439,7 @@ __device__ __forceinline__ float pick_chain_impl(const float* s_l, const float* 
     const int j = lane + 64 * q;
     sreg[q] = s_l[j];
     mreg[q] = 0.f;
-    tja[q] = j * (j + 1) * 2 + tri0;                   // start of the token's row
+    tja[q] = (PADDED ? padded_row_start(j) * 4 : j * (j + 1) * 2) + tri0;   // start of the token's row
   }
   const float nlam = -lambda;
   int bad_t = b;                                       // first pick without a finite gain
@@ -409,7 +450,7 @@ __device__ __forceinline__ float pick_chain_impl(const float* s_l, const float* 
     if constexpr (DIVERSE) {
       float amax; int i4;
       race_loop<NQ, false>(mreg, sreg, tja, lane, nlam, 0, cnt, 0.f, rec_i, rec_g, amax, i4, tri0,
-                           NQ * 32 * (NQ * 64 + 1));
+                           PADDED ? padded_tri_floats(NQ * 64) : NQ * 32 * (NQ * 64 + 1));
       rec_i >>= 2;
     } else {
       for (int u = 0; u < cnt; ++u) {
@@ -452,11 +493,11 @@ __device__ __forceinline__ float pick_chain_impl(const float* s_l, const float* 
   return last_g;
 }
 
-template <int NQ>
+template <int NQ, bool PADDED = false>
 __device__ __forceinline__ float pick_chain(const float* s_l, const float* tri, int32_t* order_l, float* gain_l,
                                             int n_live, int b, float lambda, bool diverse, int lane) {
-  return diverse ? pick_chain_impl<NQ, true>(s_l, tri, order_l, gain_l, n_live, b, lambda, lane)
-                 : pick_chain_impl<NQ, false>(s_l, tri, order_l, gain_l, n_live, b, lambda, lane);
+  return diverse ? pick_chain_impl<NQ, true, PADDED>(s_l, tri, order_l, gain_l, n_live, b, lambda, lane)
+                 : pick_chain_impl<NQ, false, PADDED>(s_l, tri, order_l, gain_l, n_live, b, lambda, lane);
 }
 
 // sort(S) on one wave: flags the b picks of order_l (indices < 64*NQ), writes them in ascending
@@ -528,20 +569,7 @@ __device__ __forceinline__ void compact_rows(const char* K, const char* V, char*
   }
 }
 
-// One head's [n,128] bf16 rows: coalesced 16-byte loads into registers (rows beyond n read
-// as zero, so MFMA fragments of padded blocks are zero), then into the padded LDS stage.
-template <int NT>
-__device__ __forceinline__ void load_rows(const char* __restrict__ src, long long stride_tok, int n,
-                                          int tid, uint4 (&reg)[NT * 32 * 16 / kDenseThreads]) {
-  constexpr int kIters = NT * 32 * 16 / kDenseThreads;
-  const int chunk = tid & 15, r0 = tid >> 4;
-#pragma unroll
-  for (int k = 0; k < kIters; ++k) {
-    const int row = r0 + 16 * k;
-    reg[k] = make_uint4(0u, 0u, 0u, 0u);
-    if (row < n) reg[k] = *reinterpret_cast<const uint4*>(src + (row * stride_tok + chunk * 8) * 2);
-  }
-}
+// One head's [n,128] bf16 rows, from registers (16 threads a row) into the padded LDS stage.
 template <int NT>
 __device__ __forceinline__ void store_rows(char* stage, int tid,
                                            const uint4 (&reg)[NT * 32 * 16 / kDenseThreads]) {

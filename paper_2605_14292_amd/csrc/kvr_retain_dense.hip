@@ -1,35 +1,44 @@
-// Fused retention step for heads with n <= 256 bf16 tokens: one workgroup (four
-// wave64s) per head takes the head from HBM to its compacted rows.
+// Fused retention step for heads with n <= 256 bf16 tokens: from HBM to the compacted rows in one launch.
 //
 //   score    (optional, G <= 8)  logits Q K^T on bf16 MFMA, softmax over the
 //            tokens per query, mean over queries             (base-score stand-in)
-//   norms    r_j = 1/(||V_j|| + eps) from the Gram diagonal  (paper Eq. 1)
+//   norms    r_j = 1/(||V_j|| + eps)                         (paper Eq. 1)
 //   Gram     lower-triangular 32x32 tiles of V V^T on bf16 MFMA with fp32
-//            accumulation, scaled to cosines and parked in LDS as a packed
+//            accumulation, scaled to cosines and parked in LDS as a padded
 //            triangle of fp32                                (Algorithm 1, Sims)
 //   greedy   one wave keeps s, m and the alive set in registers (token j lives
-//            in lane j%64); each pick is a DPP max-reduction of the gains, a
-//            ballot for the lowest tied index, and one LDS row read that is
-//            folded into m                                   (Eq. 2-3, Alg. 1)
+//            in lane j%64) and runs the race of kvr_dense_common.hpp   (Eq. 2-3, Alg. 1)
 //   compact  rows at the ascending picks are copied to the dense outputs
 //
 // The raw bf16 rows go through the MFMA un-normalised (bf16 x bf16 products are
 // exact in fp32); the cosine is dot * r_i * r_j in fp32.  Rounding normalised
 // rows to bf16 first would put ~4e-3 on every cosine.
 //
-// LDS: the packed triangle (n=192: 74 KB, n=256: 132 KB) reuses the space the
-// rows were staged in, so two heads fit a CU at n <= 192.
+// Persistent workgroups, each a pipeline over its heads: while wave 0 runs the pick chain of head h, the other waves
+// write out head h-1 and prepare head h+1: its scores (wave 1, K straight into operand registers), its V rows and their
+// inverse norms (the waves after it, rows in registers).  When the chain is done the rows are staged over the dead
+// triangle, all waves compute the Gram tiles and write the next triangle, and the next chain starts.
+//
+// What bounds it is the chain of dependent picks, which uses one wave, times the heads a CU holds at once: one of 256
+// tokens (the triangle takes 133 of the CU's 160 KB of LDS), two of 192 (75 KB), three of 128 and four of 64 tokens
+// (registers).  n = 251, b = 101: 14.1 us of chain and 0.4 of sorting per head, then 0.6 us to stage the rows, 1.8 for the
+// Gram, 1.9 for the triangle (profile by cycle counters).  With one phase after the other a head took the chain plus
+// everything else.  Measured before -> now, scores from 7 queries: 2688 heads, n=251, b=101 339 -> 230 us; 4096 heads:
+// n=192, b=64 212 -> 153, n=128, b=64 175 -> 109; 8192 heads, n=64, b=48 234 -> 122.  Scores far below lambda given: 4096
+// heads, n=128, b=64 153 -> 82.
+// Tried: the Gram beside the chain too, its operands loaded from memory in the MFMA layout (there is no room for a row
+// stage beside the triangle): the 450 gathered loads of a head of 256 tokens take 12 us whatever the prefetch depth or the
+// bytes per row and request, the address unit spending 64 cycles on each; 239 us on the first shape.
+// The roles are separate loops with matching barriers, not one loop with branches: registers of one role are not carried
+// through the other.
 #include "kvr_dense_common.hpp"
 #include "kvr_kernels.hpp"
 
 namespace kvr {
 
-constexpr int kMaxB = 256;
-__host__ __device__ constexpr int dense_smem_bytes(int NT) {
-  // region A | s_l[N32] | rinv[N32] | red[64] | idx_l[kMaxB] | order_l[kMaxB] | gain_l[kMaxB]
-  return dense_region_a(NT) + NT * 32 * 4 * 2 + 64 * 4 + kMaxB * 4 * 3;
-}
+typedef __attribute__((ext_vector_type(2))) __bf16 bf16x2;
 
+constexpr int kMaxB = 256;
 struct DenseArgs {
   const char* K; const char* V; const char* Q; const float* s_in;
   float* s_out; int32_t* idx_sorted; int32_t* pick_order; float* pick_gain;
@@ -41,227 +50,265 @@ struct DenseArgs {
   const int32_t* b_h;                  // per-head budgets <= b (rows of the outputs stay b apart), or null
 };
 
-// Workgroups are persistent: each walks over heads blockIdx.x, blockIdx.x + gridDim.x, ...
-// While one wave runs the pick chain of a head, the rows (and scores) of the workgroup's next
-// head are already on their way from HBM into registers.
-template <int NT>
-__global__ __launch_bounds__(kDenseThreads, (NT <= 6 ? 2 : 1)) void retain_dense_kernel(DenseArgs a) {
-  constexpr int N32 = NT * 32;
-  constexpr int NQ = NT / 2;                         // tokens per lane in the greedy wave
-  constexpr int NTILES = NT * (NT + 1) / 2;
-  constexpr int MAXT = NT + 1;                       // Gram tiles per working wave
-  constexpr int kIters = NT * 32 * 16 / kDenseThreads;
-  extern __shared__ __align__(16) char smem[];
-  char* stage = smem;                                // staged rows (phase 1) ...
-  float* tri = reinterpret_cast<float*>(smem);       // ... later the packed cosine triangle
-  float* s_l = reinterpret_cast<float*>(smem + dense_region_a(NT));
-  float* rinv = s_l + N32;
-  float* red = rinv + N32;
-  int32_t* idx_l = reinterpret_cast<int32_t*>(red + 64);
-  int32_t* order_l = idx_l + kMaxB;
-  float* gain_l = reinterpret_cast<float*>(order_l + kMaxB);
+template <int NT> struct DenseCfg {
+  static constexpr int W = NT == 8 ? 8 : 4;           // waves
+  static constexpr int OCC = NT == 8 ? 1 : (NT == 6 ? 2 : (NT == 4 ? 3 : 4));   // heads per CU; up to 128 tokens the registers set it, above LDS
+  static constexpr int N32 = NT * 32;
+  static constexpr int NTILES = NT * (NT + 1) / 2;
+  static constexpr int MAXT = (NTILES + W - 1) / W;   // Gram tiles per wave
+  static constexpr int ROWS = (N32 * 16 + 64 * (W - 2) - 1) / (64 * (W - 2));   // 16-byte row pieces per thread of waves 2 ..
+  static constexpr int bcap(int b) { return (b + 63) & ~63; }
+  static constexpr int region = N32 * kRowPitch > padded_tri_floats(N32) * 4 ? N32 * kRowPitch : padded_tri_floats(N32) * 4;
+  // triangle or staged rows | s_l[2][N32] | rinv[N32] | lists [2][idx, order, gain][bcap]
+  static constexpr int smem_bytes(int b) { return region + (N32 * 3 + 6 * bcap(b)) * 4; }
+};
 
-  const int tid0 = threadIdx.x;
-  const int wave = __builtin_amdgcn_readfirstlane(tid0 >> 6);
+template <int NT>
+__global__ __launch_bounds__(64 * DenseCfg<NT>::W, DenseCfg<NT>::W * DenseCfg<NT>::OCC / 4) void retain_dense_kernel(DenseArgs a) {
+  using C = DenseCfg<NT>;
+  constexpr int N32 = C::N32, NQ = NT / 2, W = C::W, ROWS = C::ROWS;
+  extern __shared__ __align__(16) char smem[];
+  char* stage = smem;
+  float* tri = reinterpret_cast<float*>(smem);
+  float* s_all = reinterpret_cast<float*>(smem + C::region);   // [2][N32]
+  float* rinv = s_all + 2 * N32;                        // inverse norms of the head being prepared
+  const int bcap = C::bcap(a.b);
+  int32_t* lists = reinterpret_cast<int32_t*>(rinv + N32);   // [2][3][bcap]: ascending indices, picks in order, gains
+
+  int tid = threadIdx.x, lane = tid & 63, hf = lane >> 5, l32 = lane & 31;
+  const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
   const int n = a.n, b = a.b;
   const bool diverse = a.lambda != 0.0f;
   const bool need_v = diverse && b > 1;
-
-  uint4 vpre[kIters];                                // rows of V of the head about to be processed
-  float spre = -INFINITY;                            // its score for token `tid` (scores given)
-  auto prefetch = [&](int hh, int tid) {
-    if (need_v) load_rows<NT>(a.V + hh * a.stride_head * 2, a.stride_tok, n, tid, vpre);
-    if (!a.Q && tid < N32) spre = tid < n ? a.s_in[static_cast<long long>(hh) * n + tid] : -INFINITY;
-  };
-  // First head at or after h0 on this workgroup's stride that is to be processed.  With
-  // only_marked set, an earlier kernel has already finished every head it did not mark; 64
-  // marks are looked at per round trip to memory.
+  // First head at or after h0 on this workgroup's stride that is to be processed.  With only_marked set, an earlier kernel
+  // has already finished every head it did not mark; 64 marks are looked at per round trip to memory.
   auto next_head = [&](int h0) -> int {
     if (!a.only_marked) return h0;
-    const int ln = tid0 & 63;
     for (long long base = h0; base < a.heads; base += 64ll * gridDim.x) {
-      const long long hh = base + static_cast<long long>(ln) * gridDim.x;
-      const bool todo = hh < a.heads && a.idx_sorted[hh * a.b] == -1;
-      const unsigned long long m = __ballot(todo);
+      const long long hh = base + static_cast<long long>(lane) * gridDim.x;
+      const unsigned long long m = __ballot(hh < a.heads && a.idx_sorted[hh * a.b] == -1);
       if (m) return static_cast<int>(base) + (__ffsll(static_cast<long long>(m)) - 1) * static_cast<int>(gridDim.x);
     }
     return a.heads;
   };
-  int h = next_head(blockIdx.x);
-  if (h < a.heads) prefetch(h, tid0);
-
-  while (h < a.heads) {
-    const int h_next = next_head(h + gridDim.x);
-    const long long head_off = h * a.stride_head * 2;  // bytes
-    // The thread index is made opaque once per head: otherwise every per-lane LDS address of
-    // the body is loop-invariant, gets hoisted out of the head loop and lives in registers.
-    int tid = tid0;
-    asm volatile("" : "+v"(tid));
-    const int lane = tid & 63, hf = lane >> 5;
-    // ---------------------------------------------------------------- scores
-    if (a.Q) {
-      {
-        uint4 kreg[kIters];
-        load_rows<NT>(a.K + head_off, a.stride_tok, n, tid, kreg);
-        store_rows<NT>(stage, tid, kreg);
-      }
-      bf16x8 qf[8];
-      {
-        const int g = lane & 31;
-        const char* qp = a.Q + (static_cast<long long>(h) * a.G + g) * kD * 2 + hf * 16;
-#pragma unroll
-        for (int ks = 0; ks < 8; ++ks) {
-          uint4 w = make_uint4(0u, 0u, 0u, 0u);
-          if (g < a.G) w = *reinterpret_cast<const uint4*>(qp + ks * 32);
-          qf[ks] = *reinterpret_cast<bf16x8*>(&w);
-        }
-      }
-      lds_barrier();
-      constexpr int BPW = (NT + 3) / 4;              // token blocks per wave
-      float z[BPW][4];
-      const float scale = 0.08838834764831845f;      // 1/sqrt(128)
-      float zmax[4] = {-INFINITY, -INFINITY, -INFINITY, -INFINITY};
-#pragma unroll
-      for (int k = 0; k < BPW; ++k) {
-        const int I = wave + 4 * k;
-        f32x16 acc = {0};
-        if (I < NT) {
-#pragma unroll
-          for (int ks = 0; ks < 8; ++ks)
-            acc = __builtin_amdgcn_mfma_f32_32x32x16_bf16(qf[ks], frag_at(stage, I, ks, lane), acc, 0, 0, 0);
-        }
-        const bool live = I < NT && (I * 32 + (lane & 31)) < n;
-#pragma unroll
-        for (int r = 0; r < 4; ++r) {
-          z[k][r] = live ? acc[r] * scale : -INFINITY; // rows g = hf*4 + r of the 32x32 tile
-          zmax[r] = fmaxf(zmax[r], z[k][r]);
-        }
-      }
-#pragma unroll
-      for (int r = 0; r < 4; ++r) {
-        const float v = half_max_at_31(zmax[r]);
-        if ((lane & 31) == 31) red[wave * 8 + hf * 4 + r] = v;
-      }
-      lds_barrier();
-      float zsum[4];
-#pragma unroll
-      for (int r = 0; r < 4; ++r) {
-        const int g = hf * 4 + r;
-        zmax[r] = fmaxf(fmaxf(red[g], red[8 + g]), fmaxf(red[16 + g], red[24 + g]));
-        zsum[r] = 0.f;
-      }
-#pragma unroll
-      for (int k = 0; k < BPW; ++k)
-#pragma unroll
-        for (int r = 0; r < 4; ++r) {
-          z[k][r] = __expf(z[k][r] - zmax[r]);       // exp(-inf) = 0 for padded tokens
-          zsum[r] += z[k][r];
-        }
-#pragma unroll
-      for (int r = 0; r < 4; ++r) {
-        const float v = half_sum_at_31(zsum[r]);
-        if ((lane & 31) == 31) red[32 + wave * 8 + hf * 4 + r] = v;
-      }
-      lds_barrier();
-      const float invG = 1.0f / static_cast<float>(a.G);
-      float w[4];
-#pragma unroll
-      for (int r = 0; r < 4; ++r) {
-        const int g = hf * 4 + r;
-        const float tot = red[32 + g] + red[40 + g] + red[48 + g] + red[56 + g];
-        w[r] = g < a.G ? invG / tot : 0.f;
-      }
-#pragma unroll
-      for (int k = 0; k < BPW; ++k) {
-        const int I = wave + 4 * k;
-        float p = 0.f;
-#pragma unroll
-        for (int r = 0; r < 4; ++r) p = fmaf(z[k][r], w[r], p);
-        p += __shfl_xor(p, 32, kWave);               // queries 0-3 live in lanes 0-31, 4-7 in 32-63
-        const int j = I * 32 + (lane & 31);
-        if (I < NT && hf == 0) {
-          s_l[j] = j < n ? p : -INFINITY;             // padding never competes
-          if (j < n && a.s_out) a.s_out[static_cast<long long>(h) * n + j] = p;
-        }
-      }
-      lds_barrier();                                // K fragments are dead; s_l is complete
-    } else {
-      if (tid < N32) s_l[tid] = spre;
-    }
-
-    // ------------------------------------------------ Gram -> packed cosines
+  auto budget = [&](int h) -> int { return a.b_h ? __builtin_amdgcn_readfirstlane(min(max(a.b_h[h], 0), b)) : b; };
+  // Staged rows -> triangle, by all waves.  Wave w takes every W-th share of the lower triangle's tiles, row by row.
+  auto build_triangle = [&]() {
+    lds_barrier();                                      // the rows are staged
+    const int t0 = wave * C::NTILES / W, cnt = (wave + 1) * C::NTILES / W - t0;
+    int I0 = 0;
+    while ((I0 + 1) * (I0 + 2) / 2 <= t0) ++I0;
+    f32x16 acc[C::MAXT];
     if (need_v) {
-      store_rows<NT>(stage, tid, vpre);
-      lds_barrier();
-      // Tile rows are paired so that every working wave owns NT+1 tiles: wave w takes row
-      // NT-1-w (tiles J = 0..NT-1-w) and row w (tiles J = 0..w).  The row block's fragments stay
-      // in registers while the column blocks stream out of LDS.
-      f32x16 acc[MAXT];
-      const bool working = wave < NT / 2;
-      const int n1 = NT - wave;                       // tiles of the first row
-      if (working) {
-        bf16x8 af[8];
+      int I = I0, J = t0 - I0 * (I0 + 1) / 2;
+      bf16x8 fi[8];
 #pragma unroll
-        for (int ks = 0; ks < 8; ++ks) af[ks] = frag_at(stage, NT - 1 - wave, ks, lane);
+      for (int ks = 0; ks < 8; ++ks) fi[ks] = frag_at(stage, I, ks, lane);
 #pragma unroll
-        for (int sl = 0; sl < MAXT; ++sl) {
-          if (sl == n1) {
-#pragma unroll
-            for (int ks = 0; ks < 8; ++ks) af[ks] = frag_at(stage, wave, ks, lane);
-          }
-          const int I = sl < n1 ? NT - 1 - wave : wave;
-          const int J = sl < n1 ? sl : sl - n1;
-          acc[sl] = f32x16{0};
-          __builtin_amdgcn_sched_barrier(0);          // keep one tile's fragment loads in flight, not all of them
+      for (int sl = 0; sl < C::MAXT; ++sl) {
+        acc[sl] = f32x16{0};
+        if (sl < cnt) {
 #pragma unroll
           for (int ks = 0; ks < 8; ++ks)
-            acc[sl] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(af[ks], frag_at(stage, J, ks, lane), acc[sl], 0, 0, 0);
-          __builtin_amdgcn_sched_barrier(0);
-          if (I == J) {                               // squared norms sit on the diagonal
+            acc[sl] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(frag_at(stage, J, ks, lane), fi[ks], acc[sl], 0, 0, 0);
+          if (J == I) {
+            ++I; J = 0;
+            if (sl + 1 < cnt) {
 #pragma unroll
-            for (int r = 0; r < 16; ++r) {
-              const int il = (r >> 2) * 8 + hf * 4 + (r & 3);
-              if (il == (lane & 31)) rinv[I * 32 + il] = acc[sl][r];
+              for (int ks = 0; ks < 8; ++ks) fi[ks] = frag_at(stage, I, ks, lane);
             }
+          } else {
+            ++J;
           }
         }
       }
-      lds_barrier();                                // staged rows are dead from here on
-      for (int j = tid; j < N32; j += kDenseThreads) rinv[j] = 1.0f / (sqrtf(rinv[j]) + a.eps);
-      lds_barrier();
-      if (working) {
+    }
+    lds_barrier();                                      // every wave has read its rows: the triangle takes their place
+    if (need_v) {
+      int I = I0, J = t0 - I0 * (I0 + 1) / 2;
 #pragma unroll
-        for (int sl = 0; sl < MAXT; ++sl) {
-          const int I = sl < n1 ? NT - 1 - wave : wave;
-          const int J = sl < n1 ? sl : sl - n1;
-          write_cos_tile(tri, rinv, acc[sl], I, J, lane);
-        }
+      for (int sl = 0; sl < C::MAXT; ++sl) {
+        if (sl < cnt) write_cos_tile_padded(tri, rinv, acc[sl], I, J, lane);
+        if (J == I) { ++I; J = 0; } else { ++J; }
       }
     }
-    lds_barrier();
-    // the next head of this workgroup starts its trip from HBM now
-    if (h_next < a.heads) prefetch(h_next, tid);
+    lds_barrier();                                      // triangle and scores are complete: the chain starts
+  };
+  int h = next_head(blockIdx.x);
+  if (h >= a.heads) return;                             // (uniform over the workgroup)
 
-    // ---------------------------------------------------------------- greedy
-    // the head's own budget: its picks are the first bh picks of a run for b, so the chain stops there
-    const int bh = a.b_h ? __builtin_amdgcn_readfirstlane(min(max(a.b_h[h], 0), b)) : b;
-    if (wave == 0) {
-      const int brun = bh < 1 ? 1 : bh;
-      pick_chain<NQ>(s_l, tri, order_l, gain_l, n, brun, a.lambda, diverse, lane);
-      sort_picks<NQ>(order_l, idx_l, reinterpret_cast<int32_t*>(rinv), brun, lane, nullptr);   // rinv is dead by now
+  if (wave == 0) {
+    // ---------------------------------------------------------------- the chain
+    build_triangle();
+    for (int par = 0; h < a.heads; par ^= 1) {
+      const int h_next = next_head(h + gridDim.x);
+      const int bh = budget(h), brun = bh < 1 ? 1 : bh;
+      int32_t *idx_l = lists + par * 3 * bcap, *order_l = idx_l + bcap;
+      float* s_l = s_all + par * N32;
+      __builtin_amdgcn_s_setprio(3);                    // the waves that share its SIMD have time to spare
+      pick_chain<NQ, true>(s_l, tri, order_l, reinterpret_cast<float*>(order_l + bcap), n, brun, a.lambda, diverse, lane);
+      sort_picks<NQ>(order_l, idx_l, reinterpret_cast<int32_t*>(s_l), brun, lane, nullptr);   // (the scores are dead by now)
+      __builtin_amdgcn_s_setprio(0);
+      lds_barrier();                                    // the triangle of h is dead
+      h = h_next;
+      if (h < a.heads) build_triangle();
     }
-    lds_barrier();
+    return;
+  }
 
-    // ------------------------------------------------- outputs and compaction
-    const long long ob = static_cast<long long>(h) * b;
-    for (int t = tid; t < b; t += kDenseThreads) {              // entries past the head's budget are padding
+  // ---------------------------------------------------------------- everything else
+  constexpr int nthr = 64 * (W - 1);
+  int t0 = tid - 64;
+  const long long tok_bytes = a.stride_tok * 2;
+  auto score = [&](int hh, float* s_l) {                // wave 1 only
+    if (!a.Q) {
+#pragma unroll
+      for (int k = 0; k < (N32 + 63) / 64; ++k) {
+        const int j = lane + 64 * k;
+        s_l[j] = j < n ? a.s_in[static_cast<long long>(hh) * n + min(j, n - 1)] : -INFINITY;   // padding never competes
+      }
+      return;
+    }
+    const char* Kh = a.K + hh * a.stride_head * 2;
+    auto load_block = [&](int blk, bf16x8 (&f)[8]) {    // rows past n: the last row again (masked below)
+      const char* p = Kh + min(blk * 32 + l32, n - 1) * tok_bytes + hf * 16;
+#pragma unroll
+      for (int ks = 0; ks < 8; ++ks) {
+        const uint4 x = *reinterpret_cast<const uint4*>(p + ks * 32);
+        f[ks] = *reinterpret_cast<const bf16x8*>(&x);
+      }
+    };
+    constexpr int KD = NT <= 4 ? 2 : 4;                 // blocks of K in flight
+    bf16x8 qf[8], kf[KD][8];
+    {
+      const char* qp = a.Q + (static_cast<long long>(hh) * a.G + min(l32, a.G - 1)) * kD * 2 + hf * 16;
+#pragma unroll
+      for (int ks = 0; ks < 8; ++ks) {
+        const uint4 x = *reinterpret_cast<const uint4*>(qp + ks * 32);
+        qf[ks] = *reinterpret_cast<const bf16x8*>(&x);  // (rows past G repeat the last query; their results are not used)
+      }
+    }
+    float z[NT][4];                                     // lane (token l32 of block I, hf): queries hf*4 + r
+#pragma unroll
+    for (int I = 0; I < KD; ++I) load_block(I, kf[I]);
+    const float scale = 0.08838834764831845f;           // 1/sqrt(128)
+    float zmax[4] = {-INFINITY, -INFINITY, -INFINITY, -INFINITY};
+#pragma unroll
+    for (int I = 0; I < NT; ++I) {
+      f32x16 d = {0};
+#pragma unroll
+      for (int ks = 0; ks < 8; ++ks) d = __builtin_amdgcn_mfma_f32_32x32x16_bf16(qf[ks], kf[I % KD][ks], d, 0, 0, 0);
+      if (I + KD < NT) load_block(I + KD, kf[I % KD]);
+#pragma unroll
+      for (int r = 0; r < 4; ++r) {
+        z[I][r] = I * 32 + l32 < n ? d[r] * scale : -INFINITY;
+        zmax[r] = fmaxf(zmax[r], z[I][r]);
+      }
+    }
+    const float invG = 1.0f / static_cast<float>(a.G);
+    float w[4];
+#pragma unroll
+    for (int r = 0; r < 4; ++r) {
+      float v = half_max_at_31(zmax[r]);
+      zmax[r] = __shfl(v, lane | 31, kWave);
+      float sum = 0.f;
+#pragma unroll
+      for (int I = 0; I < NT; ++I) { z[I][r] = __expf(z[I][r] - zmax[r]); sum += z[I][r]; }   // exp(-inf) = 0: padding
+      v = __shfl(half_sum_at_31(sum), lane | 31, kWave);
+      w[r] = hf * 4 + r < a.G ? invG / v : 0.f;
+    }
+#pragma unroll
+    for (int I = 0; I < NT; ++I) {
+      float p = 0.f;
+#pragma unroll
+      for (int r = 0; r < 4; ++r) p = fmaf(z[I][r], w[r], p);
+      p += __shfl_xor(p, 32, kWave);                    // queries 0-3 live in lanes 0-31, 4-7 in 32-63
+      const int j = I * 32 + l32;
+      if (hf == 0) {
+        s_l[j] = j < n ? p : -INFINITY;
+        if (j < n && a.s_out) a.s_out[static_cast<long long>(hh) * n + j] = p;
+      }
+    }
+  };
+  // V rows of head hh: 16 threads a row; rows past n are the last row again (never picked)
+  constexpr int NR = 64 * (W - 2);
+  int r0 = tid - 128;
+  uint4 vrow[ROWS];
+  auto fetch = [&](int hh) {
+    const char* Vh = a.V + hh * a.stride_head * 2 + (r0 & 15) * 16;
+#pragma unroll
+    for (int k = 0; k < ROWS; ++k)
+      vrow[k] = *reinterpret_cast<const uint4*>(Vh + min((r0 >> 4) + k * (NR / 16), n - 1) * tok_bytes);
+  };
+  auto norms = [&]() {                                  // Eq. 1 of the fetched rows
+#pragma unroll
+    for (int k = 0; k < ROWS; ++k) {
+      const uint32_t wds[4] = {vrow[k].x, vrow[k].y, vrow[k].z, vrow[k].w};
+      float ss = 0.f;
+#pragma unroll
+      for (int e = 0; e < 4; ++e) {
+        const bf16x2 y = __builtin_bit_cast(bf16x2, wds[e]);
+        ss = __builtin_amdgcn_fdot2_f32_bf16(y, y, ss, false);
+      }
+      // the 16 lanes of a row form one DPP row: its last lane ends up with the total
+      KVR_DPP_ADD(ss, 0x111, 0xf) KVR_DPP_ADD(ss, 0x112, 0xf) KVR_DPP_ADD(ss, 0x114, 0xf) KVR_DPP_ADD(ss, 0x118, 0xf)
+      const int row = (r0 >> 4) + k * (NR / 16);
+      if ((r0 & 15) == 15 && row < N32) rinv[row] = 1.0f / (sqrtf(ss) + a.eps);
+      __builtin_amdgcn_sched_barrier(0);                // one row at a time: no registers for all of them in flight
+    }
+  };
+  auto store_stage = [&]() {
+    if (!need_v || wave == 1) return;
+#pragma unroll
+    for (int k = 0; k < ROWS; ++k) {
+      const int row = (r0 >> 4) + k * (NR / 16);
+      if (row < N32) *reinterpret_cast<uint4*>(stage + row * kRowPitch + (r0 & 15) * 16) = vrow[k];
+    }
+  };
+  auto output = [&](int hh, int par) {
+    const int bh = budget(hh);
+    const int32_t *idx_l = lists + par * 3 * bcap, *order_l = idx_l + bcap;
+    const long long ob = static_cast<long long>(hh) * b;
+    for (int t = t0; t < b; t += nthr) {                // entries past the head's budget are padding
       a.idx_sorted[ob + t] = t < bh ? idx_l[t] : -1;
       if (a.pick_order) a.pick_order[ob + t] = t < bh ? order_l[t] : -1;
-      if (a.pick_gain) a.pick_gain[ob + t] = t < bh ? gain_l[t] : -INFINITY;
+      if (a.pick_gain) a.pick_gain[ob + t] = t < bh ? reinterpret_cast<const float*>(order_l)[bcap + t] : -INFINITY;
     }
     if ((a.K_out || a.V_out) && bh > 0)
-      compact_rows<4>(a.K, a.V, a.K_out, a.V_out, head_off, a.stride_tok, idx_l, n, bh, ob, tid, kDenseThreads);
-    lds_barrier();                                   // idx_l / s_l are reused by the next head
+      compact_rows<4>(a.K, a.V, a.K_out, a.V_out, hh * a.stride_head * 2, a.stride_tok, idx_l, n, bh, ob, t0, nthr);
+  };
+
+  auto prepare = [&](int hh, float* s_l) {
+    if (wave == 1) {
+      score(hh, s_l);
+      // (defined here by nothing: the row registers are not carried through the scores)
+#pragma unroll
+      for (int k = 0; k < ROWS; ++k) asm volatile("" : "=v"(vrow[k].x), "=v"(vrow[k].y), "=v"(vrow[k].z), "=v"(vrow[k].w));
+    } else if (need_v) {
+      fetch(hh);
+      norms();
+    }
+  };
+  prepare(h, s_all);
+  store_stage();
+  build_triangle();
+  int h_prev = -1;
+  for (int par = 0; h < a.heads; par ^= 1) {
+    const int h_next = next_head(h + gridDim.x);
+    // (opaque once per head: otherwise every per-lane address of the body is loop-invariant and lives in registers)
+    asm volatile("" : "+v"(tid));
+    lane = tid & 63; hf = lane >> 5; l32 = lane & 31; t0 = tid - 64; r0 = tid - 128;
+    if (h_prev >= 0) output(h_prev, par ^ 1);
+    if (h_next < a.heads) {
+      prepare(h_next, s_all + (par ^ 1) * N32);
+      lds_barrier();                                    // the chain of h is done, its triangle dead
+      store_stage();
+      build_triangle();
+    } else {
+      lds_barrier();
+      output(h, par);
+    }
+    h_prev = h;
     h = h_next;
   }
 }
@@ -284,23 +331,22 @@ hipError_t launch_retain_dense(const void* K, const void* V, const void* Q, int 
   a.stride_head = lay.stride_head; a.stride_tok = lay.stride_tok;
   a.n = lay.n; a.b = b; a.G = G; a.heads = lay.heads; a.lambda = lambda; a.eps = eps;
   const int cus = cu_count();
-  dim3 block(kDenseThreads);
-  auto go = [&](auto kern, int smem) -> hipError_t {
+  auto go = [&](auto kern, int smem, int threads, int most) -> hipError_t {
     const hipError_t e = hipFuncSetAttribute(reinterpret_cast<const void*>(kern),
                                              hipFuncAttributeMaxDynamicSharedMemorySize, smem);
     if (e != hipSuccess) return e;
     // persistent workgroups: as many as fit the chip at once (LDS-limited), never more than heads
     int per_cu = 160 * 1024 / smem;
-    per_cu = per_cu < 1 ? 1 : (per_cu > 4 ? 4 : per_cu);
+    per_cu = per_cu < 1 ? 1 : (per_cu > most ? most : per_cu);
     const int blocks = lay.heads < cus * per_cu ? lay.heads : cus * per_cu;
     dim3 grid(blocks);
-    hipLaunchKernelGGL(kern, grid, block, smem, st, a);
+    hipLaunchKernelGGL(kern, grid, dim3(threads), smem, st, a);
     return hipGetLastError();
   };
-  if (lay.n <= 64) return go(&retain_dense_kernel<2>, dense_smem_bytes(2));
-  if (lay.n <= 128) return go(&retain_dense_kernel<4>, dense_smem_bytes(4));
-  if (lay.n <= 192) return go(&retain_dense_kernel<6>, dense_smem_bytes(6));
-  return go(&retain_dense_kernel<8>, dense_smem_bytes(8));
+  if (lay.n <= 64) return go(&retain_dense_kernel<2>, DenseCfg<2>::smem_bytes(b), 64 * DenseCfg<2>::W, DenseCfg<2>::OCC);
+  if (lay.n <= 128) return go(&retain_dense_kernel<4>, DenseCfg<4>::smem_bytes(b), 64 * DenseCfg<4>::W, DenseCfg<4>::OCC);
+  if (lay.n <= 192) return go(&retain_dense_kernel<6>, DenseCfg<6>::smem_bytes(b), 64 * DenseCfg<6>::W, DenseCfg<6>::OCC);
+  return go(&retain_dense_kernel<8>, DenseCfg<8>::smem_bytes(b), 64 * DenseCfg<8>::W, DenseCfg<8>::OCC);
 }
 
 }  // namespace kvr

@@ -41,8 +41,6 @@
 
 namespace kvr {
 
-typedef __attribute__((ext_vector_type(4))) float f32x4;
-
 #ifndef KVR_POOL_WIDE
 #define KVR_POOL_WIDE 128
 #endif
@@ -89,7 +87,7 @@ template <int W, int S, int P, bool F32 = false> struct LazyCfg {
   // per wave, during the pass: row stage | 256-float exchange | 64 squared norms | TPW inverse norms (first pass)
   // (fp32 rows: the inverse norms only)
   static constexpr int kWaveArea = F32 ? TPW * 4 : 2 * kLzStagePlane + 1024 + 256 + TPW * 4;
-  static constexpr int kTriBytes = 8 * (P / 4) * (P / 4 + 1) * 4;    // rows padded to multiples of four floats
+  static constexpr int kTriBytes = padded_tri_floats(P) * 4;
   static constexpr int kRowBytes = P * (F32 ? kLzPitchF : kLzPitch);
   static constexpr int kMax2 = kTriBytes > kRowBytes ? kTriBytes : kRowBytes;
   static constexpr int kUnion = ((W * kWaveArea > kMax2 ? W * kWaveArea : kMax2) + 15) & ~15;
@@ -107,44 +105,6 @@ template <int W, int S, int P, bool F32 = false> struct LazyCfg {
   static constexpr int kKeepBytes = kAlias ? 0 : kRowBytes;
   static constexpr int smem_bytes() { return (kFixedFloats + kListFloats) * 4 + kPickBytes + kKeepBytes + kUnion; }
 };
-
-// The pool's cosine triangle keeps row i (columns 0..i) in (i + 4) & ~3 floats, so that four neighbouring columns of a
-// row are one aligned 16-byte store: row i = 4g + r starts at float 4 (g + 1)(2g + r).  Element (i, j), j <= i, sits
-// at start(i) + j; start(i) + j >= start(j) + i holds for i > j as in the packed triangle, so the race reads
-// max(start(i) + j, start(j) + i) without knowing which index is the larger.
-__device__ __forceinline__ int lz_row_start(int i) { return 4 * ((i >> 2) + 1) * (2 * (i >> 2) + (i & 3)); }
-
-// Writes one 32x32 tile of the pool's Gram matrix as cosines into the triangle.  acc comes from the MFMA with the
-// column block J as operand A and the row block I as operand B: lane (row = lane & 31, hf = lane >> 5) holds
-// columns 8R + 4hf .. + 3 of its row in acc[4R .. 4R+3].  The diagonal holds +inf (the row of a pick retires it);
-// what a store writes past the diagonal stays inside the row's padding and is never read.
-__device__ __forceinline__ void lz_write_cos_tile(float* tri, const float* rinv, const f32x16& acc, int I, int J, int lane) {
-  const int hf = lane >> 5;
-  const int row = I * 32 + (lane & 31);
-  const float rrow = rinv[row];
-  float4 rc[4];                                       // the columns' inverse norms, all requested before the first use
-#pragma unroll
-  for (int R = 0; R < 4; ++R) rc[R] = *reinterpret_cast<const float4*>(rinv + J * 32 + 8 * R + 4 * hf);
-  float* dst = tri + lz_row_start(row) + J * 32 + 4 * hf;
-  if (I != J) {                                       // two code paths: no per-element predicate off the diagonal
-#pragma unroll
-    for (int R = 0; R < 4; ++R)
-      *reinterpret_cast<float4*>(dst + 8 * R) = make_float4(acc[4 * R] * rrow * rc[R].x, acc[4 * R + 1] * rrow * rc[R].y,
-                                                            acc[4 * R + 2] * rrow * rc[R].z, acc[4 * R + 3] * rrow * rc[R].w);
-  } else {
-#pragma unroll
-    for (int R = 0; R < 4; ++R) {
-      const int col = J * 32 + 8 * R + 4 * hf;
-      float4 v = make_float4(acc[4 * R] * rrow * rc[R].x, acc[4 * R + 1] * rrow * rc[R].y,
-                             acc[4 * R + 2] * rrow * rc[R].z, acc[4 * R + 3] * rrow * rc[R].w);
-      if (col == row) v.x = INFINITY;
-      if (col + 1 == row) v.y = INFINITY;
-      if (col + 2 == row) v.z = INFINITY;
-      if (col + 3 == row) v.w = INFINITY;
-      if (col <= row) *reinterpret_cast<float4*>(dst + 8 * R) = v;
-    }
-  }
-}
 
 // BUD: per-head budgets are read from a.b_h.
 template <int W, int S, int P, bool BUD, bool F32 = false>
@@ -587,7 +547,7 @@ __global__ __launch_bounds__(64 * W, (W <= 4 ? 2 : 1)) void select_lazy_kernel(L
             int I = 0;
             while ((I + 1) * (I + 2) / 2 <= tile) ++I;
             const int J = tile - I * (I + 1) / 2;
-            lz_write_cos_tile(tri, pool_r, acc[q], I, J, lane);   // the diagonal holds +inf: the row of a pick retires it
+            write_cos_tile_padded(tri, pool_r, acc[q], I, J, lane);   // the diagonal holds +inf: the row of a pick retires it
           }
         }
       }
@@ -606,7 +566,7 @@ __global__ __launch_bounds__(64 * W, (W <= 4 ? 2 : 1)) void select_lazy_kernel(L
           const int p = lane + 64 * q;
           sq[q] = pool_s[p];
           mq[q] = pool_m[p];
-          tja[q] = lz_row_start(p) * 4 + tri0;         // start of the slot's row
+          tja[q] = padded_row_start(p) * 4 + tri0;         // start of the slot's row
         }
         const int jb = __builtin_amdgcn_readfirstlane(jout < 0 ? 0x7fffffff : jout);
         const float gout_u = __int_as_float(__builtin_amdgcn_readfirstlane(__float_as_int(gout)));
