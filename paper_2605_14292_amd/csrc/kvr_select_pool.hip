@@ -16,10 +16,9 @@
 //      per pick) for as long as the pool's best (gain, lower index) beats the
 //      bound -- the bound can only have dropped since, so such a pick is the
 //      exact argmax of Eq. 2 over all unselected tokens;
-//   4. one pass over V applies the rows picked in the epoch (<= 32, as one or two
-//      16-row MFMA operands, 16x16x32) to every token outside the pool.
-// On the benchmark inputs an epoch serves ~20 picks, so V is streamed ~b/20
-// times.  Nothing is approximated.  lambda = 0 has a kernel of its own (select_topb_kernel);
+//   4. one pass over V applies the rows picked in the epoch (as 16-row MFMA operands,
+//      16x16x32, read from LDS) to every token outside the pool.
+// Nothing is approximated.  lambda = 0 has a kernel of its own (select_topb_kernel);
 // this one would still return the right picks for it, after passes that change nothing.
 //
 // Layout: one workgroup per head, W wave64s, token j = 64*S*w + 64*k + lane in
@@ -37,7 +36,7 @@ typedef __attribute__((ext_vector_type(4))) float f32x4;
 
 constexpr int kPool = 128;          // pool size
 constexpr int kPoolMaxB = 1024;     // largest budget (the pick lists in LDS are sized for the call's b)
-constexpr int kPoolMaxPend = 32;    // picks per epoch (two 16-row MFMA operands)
+constexpr int kPoolMaxPend = kPool; // picks per epoch: as many as the pool serves before the outside bound wins
 constexpr int kPoolPitch = 272;     // bytes per staged row (256 + 16)
 constexpr int kSelBits = 16;        // leading bits of a gain's ordered key used to choose the pool
 constexpr int kPoolChunk = 16;      // tokens staged per step and wave in the pass over V
@@ -56,7 +55,7 @@ template <int W, int S> struct PoolCfg {
   static constexpr int kWaveStage = kPoolChunk * kPoolPitch + 1024 + 256;   // row stage + 256-float scratch + 64 squared norms per wave
   static constexpr int kTriBytes = kPool * (kPool + 1) / 2 * 4;
   static constexpr int kUnion = (W * kWaveStage > kTriBytes ? W * kWaveStage : kTriBytes);
-  // floats: slots 64 | shared 16 | wcount 16 | pool_tok,r,s,m,picked 5*128 | pend 32 | pend_r 32 |
+  // floats: slots 64 | shared 16 | wcount 16 | pool_tok,r,s,m,picked 5*128 | pend 128 x 16 bit |
   //         order,gain,idxs 3*bcap (b rounded up to 64) ; then pool rows ; then the union area (triangle, stages, and at
   //         the end the pick flags of the read-out) ; then score, m, inverse norm and pool slot of the
   //         token slots that do not live in registers
@@ -91,8 +90,8 @@ __global__ __launch_bounds__(64 * W, (W <= 4 ? 2 : 1)) void select_pool_kernel(P
   float* pool_s = smem + 96 + 2 * kPool;
   float* pool_m = smem + 96 + 3 * kPool;
   int32_t* pool_picked = reinterpret_cast<int32_t*>(smem + 96 + 4 * kPool);
-  int32_t* pend_l = reinterpret_cast<int32_t*>(smem + 96 + 5 * kPool);        // [32] pool slots picked this epoch
-  float* pend_r = smem + 96 + 5 * kPool + 32;                                  // [32] their inverse norms
+  int16_t* pend_l = reinterpret_cast<int16_t*>(smem + 96 + 5 * kPool);        // [P] pool slots picked this epoch
+  float* pend_r = pool_s;                                        // [P] their inverse norms, 0 past the last one (the race has the scores in registers)
   int32_t* order_l = reinterpret_cast<int32_t*>(smem + 96 + 5 * kPool + 64);
   const int bcap = (a.b + 63) & ~63;                             // rows of the pick lists
   float* gain_l = smem + 96 + 5 * kPool + 64 + bcap;
@@ -363,29 +362,37 @@ __global__ __launch_bounds__(64 * W, (W <= 4 ? 2 : 1)) void select_pool_kernel(P
         const float gout_u = __int_as_float(__builtin_amdgcn_readfirstlane(__float_as_int(gout)));
         const bool no_out = __builtin_amdgcn_readfirstlane(jout) < 0;
         const int room = __builtin_amdgcn_readfirstlane(min(b - t, kPoolMaxPend));
-        int np = 0, stop = 0;                        // stop: 1 = bound wins, 2 = nothing finite left
-        int rec_i = 0, rec_g = 0;
-        int until = room;
-        float bound = gout_u;
-        while (np < room) {
-          float amax; int i4;
-          np = race_loop<2, true>(mq, sq, tja, lane, nlam, np, until, bound, rec_i, rec_g, amax, i4, tri0, kPool * (kPool + 1) / 2);
-          if (np == until) { until = room; bound = gout_u; continue; }
-          // rare: the bound wins, a tie with it, or nothing finite
-          if (!(amax > -INFINITY)) { stop = no_out ? 2 : 1; break; }
-          if (!(amax == gout_u && __builtin_amdgcn_readfirstlane(pool_tok[i4 >> 2]) < jb)) { stop = 1; break; }
-          until = np + 1;                            // a tie that the pool's lower token wins: this one pick passes
-          bound = -INFINITY;
+        int done = 0, stop = 0;                      // stop: 1 = bound wins, 2 = nothing finite left
+        while (done < room && stop == 0) {           // at most 64 picks a turn: a lane parks one
+          const int turn = __builtin_amdgcn_readfirstlane(min(room - done, 64));
+          int np = 0;
+          int rec_i = 0, rec_g = 0;
+          int until = turn;
+          float bound = gout_u;
+          while (np < turn) {
+            float amax; int i4;
+            np = race_loop<2, true>(mq, sq, tja, lane, nlam, np, until, bound, rec_i, rec_g, amax, i4, tri0, kPool * (kPool + 1) / 2);
+            if (np == until) { until = turn; bound = gout_u; continue; }
+            // rare: the bound wins, a tie with it, or nothing finite
+            if (!(amax > -INFINITY)) { stop = no_out ? 2 : 1; break; }
+            if (!(amax == gout_u && __builtin_amdgcn_readfirstlane(pool_tok[i4 >> 2]) < jb)) { stop = 1; break; }
+            until = np + 1;                          // a tie that the pool's lower token wins: this one pick passes
+            bound = -INFINITY;
+          }
+          rec_i >>= 2;
+          if (lane < np) {
+            const int ri = kvr_ix(rec_i, kPool, 206);             // 206: pool slot of a pick
+            const int tp = kvr_ix(t + done + lane, bcap, 207);    // 207: number of a pick
+            order_l[tp] = pool_tok[ri]; gain_l[tp] = __int_as_float(rec_g);
+            const int pl = kvr_ix(done + lane, kPoolMaxPend, 208);   // 208: picks of one epoch
+            pend_l[pl] = static_cast<int16_t>(ri); pend_r[pl] = pool_r[ri]; pool_picked[ri] = 1;
+          }
+          done += np;
         }
-        rec_i >>= 2;
         pool_m[p0] = mq[0]; pool_m[p1] = mq[1];          // the pool's m is authoritative
-        if (lane < np) {
-          const int ri = kvr_ix(rec_i, kPool, 206);      // 206: pool slot of a pick
-          const int tp = kvr_ix(t + lane, bcap, 207);    // 207: number of a pick
-          order_l[tp] = pool_tok[ri]; gain_l[tp] = __int_as_float(rec_g);
-          const int pl = kvr_ix(lane, kPoolMaxPend, 208);   // 208: picks of one epoch
-          pend_l[pl] = ri; pend_r[pl] = pool_r[ri]; pool_picked[ri] = 1;
-        }
+        if (p0 >= done) pend_r[p0] = 0.f;
+        if (p1 >= done) pend_r[p1] = 0.f;
+        const int np = done;
         t += np;
         if (lane == 0) { shared_i[0] = np; shared_i[1] = t; shared_i[2] = stop; }
       }
@@ -424,25 +431,26 @@ __global__ __launch_bounds__(64 * W, (W <= 4 ? 2 : 1)) void select_pool_kernel(P
       // ================= 4. one pass over V: the epoch's picks against every outside token =================
       if (np > 0) {
         const int kg = lane >> 4;
-        const int tiles = (np + 15) >> 4;            // 1 or 2 A operands of 16 picked rows
-        bf16x8 af[2][4];
-        float pr[2][4];
+        const int tiles = (np + 15) >> 4;            // A operands of 16 picked rows
+        // The picks' rows move to the front of the pool's rows, in pick order and followed by zero rows
+        // up to a whole operand: any number of operands is then read from there, conflict-free.
+        {
+          constexpr int kMov = kPool * 16 / NT;
+          const int kend = (tiles * 256 + NT - 1) / NT;   // (uniform) threads' shares that hold rows of the operands
+          uint4 x[kMov];
 #pragma unroll
-        for (int at = 0; at < 2; ++at) {
-          const int pi = at * 16 + (lane & 15);
-          const int ps = pi < np ? kvr_ix(pend_l[pi], kPool, 209) : -1;   // 209: pool slot of a pending row
-#pragma unroll
-          for (int ks = 0; ks < 4; ++ks) {
-            uint4 x = make_uint4(0u, 0u, 0u, 0u);
-            if (ps >= 0) x = *reinterpret_cast<const uint4*>(prow + ps * kPoolPitch + ks * 64 + kg * 16);
-            af[at][ks] = *reinterpret_cast<bf16x8*>(&x);
+          for (int k = 0; k < kMov; ++k) {
+            const int row = k * (NT / 16) + (tid >> 4);
+            x[k] = make_uint4(0u, 0u, 0u, 0u);
+            if (row < np) x[k] = *reinterpret_cast<const uint4*>(prow + kvr_ix(pend_l[row], kPool, 209) * kPoolPitch + (tid & 15) * 16);   // 209: pool slot of a pending row
           }
+          lds_barrier();
 #pragma unroll
-          for (int i = 0; i < 4; ++i) {
-            const int ri = at * 16 + 4 * kg + i;     // result row i of this lane belongs to pick ri
-            pr[at][i] = ri < np ? pend_r[ri] : 0.f;
-          }
+          for (int k = 0; k < kMov; ++k)
+            if (k < kend) *reinterpret_cast<uint4*>(prow + (k * (NT / 16) + (tid >> 4)) * kPoolPitch + (tid & 15) * 16) = x[k];
+          lds_barrier();
         }
+        const char* const a_row = prow + (lane & 15) * kPoolPitch + kg * 16;
         // Two 64-token groups of this wave are in flight: the registers of a 16-token sub-block
         // are refilled for the group after next as soon as they have been written to the stage.
         // Rows past n are clamped to the last row (their results belong to padding tokens, whose
@@ -481,39 +489,48 @@ __global__ __launch_bounds__(64 * W, (W <= 4 ? 2 : 1)) void select_pool_kernel(P
             if (g < S) fetch(g, sub, g);
 #pragma unroll
         for (int k = 0; k < S; ++k) {
-          float part[4];                             // per 16-token sub-block: max over my four picked rows
+          float part[4];                             // per 16-token sub-block: max over my four picked rows of every operand
 #pragma unroll
-          for (int sub = 0; sub < 4; ++sub) {
-            wave_lds_sync();
+          for (int pair = 0; pair < 2; ++pair) {
+            bf16x8 bfr[2][4];
 #pragma unroll
-            for (int q = 0; q < LPC; ++q) {
-              const uint4 x = (k % kDepth == 0) ? preA[sub][q] : preB[sub][q];
-              *reinterpret_cast<uint4*>(stage + ((lane >> 4) + 4 * q) * kPoolPitch + (lane & 15) * 16) = x;
-              if (!have_r) {                         // row (lane >> 4) + 4q of the sub-block belongs to lane 16*sub + row
-                const float ss = sum_sq(x);
-                if ((lane & 15) == 0) norm_x[sub * 16 + (lane >> 4) + 4 * q] = ss;
+            for (int u = 0; u < 2; ++u) {
+              const int sub = pair * 2 + u;
+              wave_lds_sync();
+#pragma unroll
+              for (int q = 0; q < LPC; ++q) {
+                const uint4 x = (k % kDepth == 0) ? preA[sub][q] : preB[sub][q];
+                *reinterpret_cast<uint4*>(stage + ((lane >> 4) + 4 * q) * kPoolPitch + (lane & 15) * 16) = x;
+                if (!have_r) {                       // row (lane >> 4) + 4q of the sub-block belongs to lane 16*sub + row
+                  const float ss = sum_sq(x);
+                  if ((lane & 15) == 0) norm_x[sub * 16 + (lane >> 4) + 4 * q] = ss;
+                }
               }
+              if (k + kDepth < S) fetch(k + kDepth, sub, k % kDepth);
+              wave_lds_sync();
+              const char* fp = stage + (lane & 15) * kPoolPitch + kg * 16;
+#pragma unroll
+              for (int ks = 0; ks < 4; ++ks) bfr[u][ks] = *reinterpret_cast<const bf16x8*>(fp + ks * 64);
             }
-            if (k + kDepth < S) fetch(k + kDepth, sub, k % kDepth);
-            wave_lds_sync();
-            const char* fp = stage + (lane & 15) * kPoolPitch + kg * 16;
-            bf16x8 bfr[4];
+            float pm0 = 0.f, pm1 = 0.f;              // (m starts at 0: a negative cosine never raises it)
+#pragma unroll 1
+            for (int at = 0; at < tiles; ++at) {
+              const char* ap = a_row + at * (16 * kPoolPitch);
+              bf16x8 af[4];
 #pragma unroll
-            for (int ks = 0; ks < 4; ++ks) bfr[ks] = *reinterpret_cast<const bf16x8*>(fp + ks * 64);
-            f32x4 acc0 = {0.f, 0.f, 0.f, 0.f};
+              for (int ks = 0; ks < 4; ++ks) af[ks] = *reinterpret_cast<const bf16x8*>(ap + ks * 64);
+              const float4 pr = *reinterpret_cast<const float4*>(pend_r + at * 16 + 4 * kg);   // result row i of this lane is pick 4 kg + i
+              f32x4 acc0 = {0.f, 0.f, 0.f, 0.f}, acc1 = {0.f, 0.f, 0.f, 0.f};
 #pragma unroll
-            for (int ks = 0; ks < 4; ++ks) acc0 = __builtin_amdgcn_mfma_f32_16x16x32_bf16(af[0][ks], bfr[ks], acc0, 0, 0, 0);
-            float pm = hw_max(hw_max(acc0[0] * pr[0][0], acc0[1] * pr[0][1]),
-                                   hw_max(acc0[2] * pr[0][2], acc0[3] * pr[0][3]));
-            if (tiles > 1) {
-              f32x4 acc1 = {0.f, 0.f, 0.f, 0.f};
-#pragma unroll
-              for (int ks = 0; ks < 4; ++ks) acc1 = __builtin_amdgcn_mfma_f32_16x16x32_bf16(af[1][ks], bfr[ks], acc1, 0, 0, 0);
-              const float pm1 = hw_max(hw_max(acc1[0] * pr[1][0], acc1[1] * pr[1][1]),
-                                            hw_max(acc1[2] * pr[1][2], acc1[3] * pr[1][3]));
-              pm = hw_max(pm, pm1);
+              for (int ks = 0; ks < 4; ++ks) {
+                acc0 = __builtin_amdgcn_mfma_f32_16x16x32_bf16(af[ks], bfr[0][ks], acc0, 0, 0, 0);
+                acc1 = __builtin_amdgcn_mfma_f32_16x16x32_bf16(af[ks], bfr[1][ks], acc1, 0, 0, 0);
+              }
+              pm0 = hw_max(pm0, hw_max(hw_max(acc0[0] * pr.x, acc0[1] * pr.y), hw_max(acc0[2] * pr.z, acc0[3] * pr.w)));
+              pm1 = hw_max(pm1, hw_max(hw_max(acc1[0] * pr.x, acc1[1] * pr.y), hw_max(acc1[2] * pr.z, acc1[3] * pr.w)));
             }
-            part[sub] = pm;
+            part[pair * 2] = pm0;
+            part[pair * 2 + 1] = pm1;
           }
           // lane (col, kg) holds partial maxima of token col of sub-block 0..3; the owner of token
           // (sub, col) is lane (col, kg = sub).  Exchange through the wave's scratch: [sub][kg][col].
