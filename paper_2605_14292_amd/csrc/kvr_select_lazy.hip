@@ -733,52 +733,51 @@ __global__ __launch_bounds__(64 * W, (W <= 4 ? 2 : 1)) void select_lazy_kernel(L
             for (int sub = 0; sub < GSUB; ++sub)
               if (kg == sub) lrw[gi * GR + sub * 16 + (lane & 15)] = part[sub];
           } else {
+          // The operand rows of a whole group are read once: an operand of picked rows then meets SB sub-blocks.
+          // With one sub-block at a time every operand came from LDS four times per group, 128 KB per wave once
+          // there are 128 picks, and the eight waves of a CU waited for LDS bandwidth.
+          constexpr int SB = 4;
 #pragma unroll
-          for (int sub = 0; sub < 4; ++sub) {
-            wave_lds_sync();
+          for (int s0 = 0; s0 < 4; s0 += SB) {
+            bf16x8 bfr[SB][4];
 #pragma unroll
-            for (int q = 0; q < LPC; ++q) {
-              const uint4 x = pre[sub][q];
-              *reinterpret_cast<uint4*>(stage + ((lane & 15) >> 3) * kLzStagePlane + ((lane >> 4) + 4 * q) * kLzHalf + (lane & 7) * 16) = x;
-              if (!have_r) {                         // row (lane >> 4) + 4q of the sub-block is list entry 16*sub + row of the group
-                const float ss = sum_sq(x);
-                if ((lane & 15) == 15) norm_x[sub * 16 + (lane >> 4) + 4 * q] = ss;
-              }
-            }
-            fetch(gi + 1, sub);
-            wave_lds_sync();
-            const char* fp = stage + (kg & 1) * kLzStagePlane + (lane & 15) * kLzHalf + (kg >> 1) * 16;
-            bf16x8 bfr[4];
+            for (int u = 0; u < SB; ++u) {
+              const int sub = s0 + u;
+              wave_lds_sync();
 #pragma unroll
-            for (int ks = 0; ks < 4; ++ks) bfr[ks] = *reinterpret_cast<const bf16x8*>(fp + ks * 32);
-            float pm = 0.f;                          // the floor of Eq. 2
-            for (int tl = 0; tl < tiles; tl += 2) {    // two operands at a time: their MFMA chains interleave
-              const char* ap = pk + (kg & 1) * kLzPickPlane + (tl * 16 + (lane & 15)) * kLzHalf + (kg >> 1) * 16;
-              bf16x8 a0[4];
-#pragma unroll
-              for (int ks = 0; ks < 4; ++ks) a0[ks] = *reinterpret_cast<const bf16x8*>(ap + ks * 32);
-              const float4 p0 = *reinterpret_cast<const float4*>(pick_r + tl * 16 + 4 * kg);
-              f32x4 acc0 = {0.f, 0.f, 0.f, 0.f};
-              if (tl + 1 < tiles) {
-                bf16x8 a1[4];
-#pragma unroll
-                for (int ks = 0; ks < 4; ++ks) a1[ks] = *reinterpret_cast<const bf16x8*>(ap + 16 * kLzHalf + ks * 32);
-                const float4 p1 = *reinterpret_cast<const float4*>(pick_r + tl * 16 + 16 + 4 * kg);
-                f32x4 acc1 = {0.f, 0.f, 0.f, 0.f};
-#pragma unroll
-                for (int ks = 0; ks < 4; ++ks) {
-                  acc0 = __builtin_amdgcn_mfma_f32_16x16x32_bf16(a0[ks], bfr[ks], acc0, 0, 0, 0);
-                  acc1 = __builtin_amdgcn_mfma_f32_16x16x32_bf16(a1[ks], bfr[ks], acc1, 0, 0, 0);
+              for (int q = 0; q < LPC; ++q) {
+                const uint4 x = pre[sub][q];
+                *reinterpret_cast<uint4*>(stage + ((lane & 15) >> 3) * kLzStagePlane + ((lane >> 4) + 4 * q) * kLzHalf + (lane & 7) * 16) = x;
+                if (!have_r) {                       // row (lane >> 4) + 4q of the sub-block is list entry 16*sub + row of the group
+                  const float ss = sum_sq(x);
+                  if ((lane & 15) == 15) norm_x[sub * 16 + (lane >> 4) + 4 * q] = ss;
                 }
-                pm = hw_max(pm, hw_max(hw_max(acc1[0] * p1.x, acc1[1] * p1.y), hw_max(acc1[2] * p1.z, acc1[3] * p1.w)));
-              } else {
-#pragma unroll
-                for (int ks = 0; ks < 4; ++ks)
-                  acc0 = __builtin_amdgcn_mfma_f32_16x16x32_bf16(a0[ks], bfr[ks], acc0, 0, 0, 0);
               }
-              pm = hw_max(pm, hw_max(hw_max(acc0[0] * p0.x, acc0[1] * p0.y), hw_max(acc0[2] * p0.z, acc0[3] * p0.w)));
+              fetch(gi + 1, sub);
+              wave_lds_sync();
+              const char* fp = stage + (kg & 1) * kLzStagePlane + (lane & 15) * kLzHalf + (kg >> 1) * 16;
+#pragma unroll
+              for (int ks = 0; ks < 4; ++ks) bfr[u][ks] = *reinterpret_cast<const bf16x8*>(fp + ks * 32);
+              part[sub] = 0.f;                       // the floor of Eq. 2
             }
-            part[sub] = pm;
+#pragma unroll 1
+            for (int tl = 0; tl < tiles; ++tl) {
+              const char* ap = pk + (kg & 1) * kLzPickPlane + (tl * 16 + (lane & 15)) * kLzHalf + (kg >> 1) * 16;
+              bf16x8 av[4];
+#pragma unroll
+              for (int ks = 0; ks < 4; ++ks) av[ks] = *reinterpret_cast<const bf16x8*>(ap + ks * 32);
+              const float4 p0 = *reinterpret_cast<const float4*>(pick_r + tl * 16 + 4 * kg);
+              f32x4 acc[SB];
+#pragma unroll
+              for (int u = 0; u < SB; ++u) acc[u] = f32x4{0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+              for (int ks = 0; ks < 4; ++ks)
+#pragma unroll
+                for (int u = 0; u < SB; ++u) acc[u] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(av[ks], bfr[u][ks], acc[u], 0, 0, 0);
+#pragma unroll
+              for (int u = 0; u < SB; ++u)
+                part[s0 + u] = hw_max(part[s0 + u], hw_max(hw_max(acc[u][0] * p0.x, acc[u][1] * p0.y), hw_max(acc[u][2] * p0.z, acc[u][3] * p0.w)));
+            }
           }
           // lane (col, kg) holds partial maxima of row col of sub-block 0..3; list entry 16*sub + col of the
           // group is finished by lane (col, kg = sub).  Exchange through the wave's scratch: [sub][kg][col].
