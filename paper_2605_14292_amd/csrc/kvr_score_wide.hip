@@ -199,9 +199,11 @@ __global__ __launch_bounds__(kWideThreads, 2) void score_wide_kernel(const char*
   __syncthreads();
   for (int g = tid; g < GP; g += kWideThreads) {
     float mm = fmaxf(fmaxf(pm[g], pm[GP + g]), fmaxf(pm[2 * GP + g], pm[3 * GP + g]));
+    // a split without a finite logit counts for nothing in the merge; a head without one is NaN
+    const float ms = MODE == kWideStats && mm == -INFINITY ? 0.f : mm;
     float ll = 0.f;
 #pragma unroll
-    for (int w = 0; w < 4; ++w) ll += pl[w * GP + g] * __builtin_amdgcn_exp2f(pm[w * GP + g] - mm);
+    for (int w = 0; w < 4; ++w) ll += pl[w * GP + g] * __builtin_amdgcn_exp2f(pm[w * GP + g] - ms);
     if constexpr (MODE == kWideStats) {
       if (g < G) { so[2 * blockIdx.y * G + g] = mm; so[(2 * blockIdx.y + 1) * G + g] = ll; }
     } else {

@@ -23,3 +23,19 @@ def test_wide_scores_match_the_oracle_on_either_side_of_the_split(heads, n, G):
         want = O.score_softmax_mean(K[h].double().numpy(), Q[h].double().numpy())
         # exact products, fp32 sums of 128 terms of order one: logits good to 1e-6, so scores to a few 1e-6 relative
         np.testing.assert_allclose(s_out[h].cpu().numpy(), want, rtol=2e-5)
+
+
+def test_a_split_without_a_finite_logit_counts_for_nothing():
+    from paper_2605_14292_amd import binding as B
+    heads, n, G = 2, 4000, 64
+    g = torch.Generator().manual_seed(5)
+    K = torch.randn((heads, n, 128), generator=g).to(torch.bfloat16)
+    Q = torch.randn((heads, G, 128), generator=g).to(torch.bfloat16)
+    Q[:, :, 0] = 1.0
+    K[:, :2500, 0] = -float("inf")                       # logits of -inf: these tokens score zero
+    s_out = B.kvr_score(K.cuda(), Q.cuda())
+    torch.cuda.synchronize()
+    for h in range(heads):
+        want = O.score_softmax_mean(K[h].double().numpy(), Q[h].double().numpy())
+        assert np.all(want[:2500] == 0) and abs(want.sum() - 1) < 1e-12
+        np.testing.assert_allclose(s_out[h].cpu().numpy(), want, rtol=2e-5)
