@@ -919,6 +919,13 @@ hipError_t launch_select_lazy_f32(const void* V, const float* s, const Layout& l
     hipLaunchKernelGGL(kern, dim3(lay.heads), dim3(512), smem, st, a);
     return hipGetLastError();
   };
+  // Every wave owns 64 S consecutive tokens and fills an eighth of the pool with them, so a wave past the head's end leaves
+  // its share of the pool empty and its part of the passes to the others: the fewest slots that hold the head.  Measured
+  // with four slots / these (the whole flat event): 64 sequences of 1024 tokens 807 / 775 us, of 300 407 / 323; 32 of 700
+  // 422 / 387; 16 of 1400 460 / 439.
+  if (lay.n <= 512) return go(&select_lazy_kernel<8, 1, 128, false, true>, LazyCfg<8, 1, 128, true>::smem_bytes());
+  if (lay.n <= 1024) return go(&select_lazy_kernel<8, 2, 128, false, true>, LazyCfg<8, 2, 128, true>::smem_bytes());
+  if (lay.n <= 1536) return go(&select_lazy_kernel<8, 3, 128, false, true>, LazyCfg<8, 3, 128, true>::smem_bytes());
   if (lay.n <= 2048) return go(&select_lazy_kernel<8, 4, 128, false, true>, LazyCfg<8, 4, 128, true>::smem_bytes());
   return go(&select_lazy_kernel<8, 8, 128, false, true>, LazyCfg<8, 8, 128, true>::smem_bytes());
 }

@@ -29,3 +29,21 @@ def test_exact_gains_and_ties_give_the_oracles_order(heads, n, b, levels):
         np.testing.assert_array_equal(order[h].cpu().numpy(), want["order"])
         np.testing.assert_array_equal(gain[h].cpu().numpy().astype(np.float64), want["gain"])
         np.testing.assert_array_equal(idx[h].cpu().numpy(), np.sort(want["order"]))
+
+
+# long fp32 heads, either side of every step in the number of token slots a wave holds
+@pytest.mark.parametrize("n", [257, 512, 513, 1024, 1025, 1536, 1537])
+@pytest.mark.parametrize("b", [65, 128])
+def test_long_fp32_heads_at_the_edges_of_the_slots(n, b):
+    from paper_2605_14292_amd import binding as B
+    g = torch.Generator().manual_seed(n + b)
+    s = torch.randint(0, 12, (3, n), generator=g).float() / 64
+    V = torch.zeros((3, n, 128))
+    V.scatter_(2, torch.randint(0, 100, (3, n, 1), generator=g), 1.0)
+    idx, order, gain = B.kvr_select_greedy(V.cuda(), s.cuda(), b, 0.25, 0.0)
+    torch.cuda.synchronize()
+    for h in range(3):
+        want = O.alpha_select(s[h].double().numpy(), V[h].double().numpy(), b, 0.25, 0.0)
+        np.testing.assert_array_equal(order[h].cpu().numpy(), want["order"])
+        np.testing.assert_array_equal(gain[h].cpu().numpy().astype(np.float64), want["gain"])
+        np.testing.assert_array_equal(idx[h].cpu().numpy(), np.sort(want["order"]))
