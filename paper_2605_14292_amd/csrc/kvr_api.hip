@@ -86,6 +86,9 @@ hipError_t select_only(const void* V, const float* s, const kvr::Layout& l, int 
   }
   if (kvr::lazy_f32_supported(l, b, lambda))
     return kvr::launch_select_lazy_f32(V, s, l, b, lambda, eps, idx_sorted, pick_order, pick_gain, st);
+  if (kvr::large_supported(l, b))
+    return kvr::launch_select_large(nullptr, V, s, l, b, lambda, eps, idx_sorted, pick_order, pick_gain,
+                                    nullptr, nullptr, st);
   if (kvr::pool_supported(l, b))
     return kvr::launch_select_pool(nullptr, V, s, l, b, lambda, eps, idx_sorted, pick_order, pick_gain,
                                    nullptr, nullptr, st, nullptr, true);
@@ -148,9 +151,12 @@ int kvr_debug_bounds_selftest(int32_t* out, void* stream) {
 
 int kvr_debug_bounds_violation(uint32_t* worst_id) {
   if (!worst_id) return KVR_ERR_ARG;
-  const unsigned int a = kvr::bounds_bad_lazy(), b = kvr::bounds_bad_pool(), c = kvr::bounds_bad_sparse();
-  if (a == 0xffffffffu || b == 0xffffffffu || c == 0xffffffffu) return KVR_ERR_HIP;
-  *worst_id = a > b ? (a > c ? a : c) : (b > c ? b : c);
+  const unsigned int bad[] = {kvr::bounds_bad_lazy(), kvr::bounds_bad_pool(), kvr::bounds_bad_sparse(), kvr::bounds_bad_large()};
+  *worst_id = 0;
+  for (const unsigned int id : bad) {
+    if (id == 0xffffffffu) return KVR_ERR_HIP;
+    if (id > *worst_id) *worst_id = id;
+  }
   return KVR_OK;
 }
 
@@ -279,6 +285,11 @@ int kvr_retain(const void* K, const void* V, const void* Q, int G, const float* 
                                   nullptr, sparse);
     return e == hipSuccess ? KVR_OK : KVR_ERR_HIP;
   }
+  if (kvr::large_supported(l, b)) {
+    const hipError_t e = kvr::launch_select_large(K, V, s, l, b, lambda, eps, idx_sorted, pick_order,
+                                                  pick_gain, K_out, V_out, st);
+    return e == hipSuccess ? KVR_OK : KVR_ERR_HIP;
+  }
   if (kvr::pool_supported(l, b)) {
     const hipError_t e = kvr::launch_select_pool(K, V, s, l, b, lambda, eps, idx_sorted, pick_order,
                                                  pick_gain, K_out, V_out, st, nullptr, Q == nullptr);
@@ -348,7 +359,7 @@ int retain_budgeted(const void* K, const void* V, const void* Q, int G, const fl
   // bf16 heads of up to 4096 tokens: the fused kernels take the per-head budgets themselves (the chain of a head
   // stops at its own budget; lists, padding and kept rows are written by the kernel that selected
   // them); what is left is elementwise: the gains of protected tokens, per-head lambdas, position ids.
-  const bool long_heads = lambda > 0.0f && kvr::pool_supported(l, b_max);
+  const bool long_heads = lambda > 0.0f && (kvr::pool_supported(l, b_max) || kvr::large_supported(l, b_max));
   const bool long_topb = kvr::topb_supported(l, b_max, lambda) && l.dtype == KVR_BF16;
   const bool fused = (K_out == nullptr) == (V_out == nullptr) && (!K_out || K) &&
                      (kvr::pruned_supported(l, b_max, lambda, false) || kvr::dense_supported(l, b_max, 0, false) ||
@@ -369,6 +380,9 @@ int retain_budgeted(const void* K, const void* V, const void* Q, int G, const fl
       if (e == hipSuccess)
         e = kvr::launch_select_lazy(K, V, s_work, l, b_max, lambda, eps, idx_sorted, pick_order, pick_gain, K_out,
                                     V_out, st, b_h, sparse);
+    } else if (long_heads && kvr::large_supported(l, b_max)) {
+      e = kvr::launch_select_large(K, V, s_work, l, b_max, lambda, eps, idx_sorted, pick_order, pick_gain, K_out,
+                                   V_out, st, b_h);
     } else if (long_heads) {
       e = kvr::launch_select_pool(K, V, s_work, l, b_max, lambda, eps, idx_sorted, pick_order, pick_gain, K_out,
                                   V_out, st, b_h, Q == nullptr);

@@ -71,6 +71,12 @@ __device__ __forceinline__ float hw_max(float a, float b) {
   asm("v_max_f32 %0, %1, %2" : "=v"(r) : "v"(a), "v"(b));
   return r;
 }
+// max(a, b, c), likewise
+__device__ __forceinline__ float max3(float a, float b, float c) {
+  float r;
+  asm("v_max3_f32 %0, %1, %2, %3" : "=v"(r) : "v"(a), "v"(b), "v"(c));
+  return r;
+}
 // ra[lane ln] = va, rb[lane ln] = vb for wave-uniform va, vb, ln; the other lanes keep their
 // values.  The lane select goes through m0 because a VALU instruction reads one SGPR only.
 __device__ __forceinline__ void write_lane2(int& ra, int& rb, int va, int vb, int ln) {

@@ -114,7 +114,7 @@ hipError_t launch_budget_finalize(const void* K, const void* V, const Layout& la
                                   float* pick_gain, void* K_out, void* V_out, int32_t* pos_out,
                                   hipStream_t st);
 
-// Pool-based exact greedy for bf16 heads with 256 < n <= 8192 and b <= 1024 (selection plus
+// Pool-based exact greedy for bf16 heads with 256 < n <= 4096 and b <= 1024 (selection plus
 // optional compaction; scores come in through s).
 bool pool_supported(const Layout& lay, int b);
 hipError_t launch_select_pool(const void* K, const void* V, const float* s, const Layout& lay, int b,
@@ -125,6 +125,13 @@ hipError_t launch_select_pool(const void* K, const void* V, const float* s, cons
 // and skips their rows.  Worth it for scores the caller supplies; mean-of-softmax scores over hundreds
 // of tokens lie far below any lambda in use, nothing can be dropped, and the variant only costs.
 
+// The same selection for bf16 heads with 4096 < n <= 8192 and b <= 1024, with lazily refreshed penalties: the rows of the
+// picks are streamed past the rows to refresh.  Always applies the score bound first.
+bool large_supported(const Layout& lay, int b);
+hipError_t launch_select_large(const void* K, const void* V, const float* s, const Layout& lay, int b,
+                               float lambda, float eps, int32_t* idx_sorted, int32_t* pick_order,
+                               float* pick_gain, void* K_out, void* V_out, hipStream_t st,
+                               const int32_t* b_h = nullptr);
 
 // The same selection with lazily refreshed penalties for bf16 heads with 256 < n <= 4096, b <= 128 and
 // lambda > 0: after the first epoch only the tokens whose gain bounds can matter soon are brought up to
@@ -162,6 +169,7 @@ hipError_t validate_finite(const void* K, const void* V, const void* Q, int G, c
 unsigned int bounds_bad_lazy();
 unsigned int bounds_bad_pool();
 unsigned int bounds_bad_sparse();
+unsigned int bounds_bad_large();
 // One thread range-checks the index 5 against the limit 3 (id 199) and stores what the check returned (2 in the
 // debug build, 5 in the product build) in out[0]; no memory is accessed through the index.
 hipError_t launch_bounds_selftest(int32_t* out, hipStream_t st);

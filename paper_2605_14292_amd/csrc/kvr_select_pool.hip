@@ -1,5 +1,5 @@
-// Greedy selection (paper Sec. 4.1, Algorithm 1) for heads with 256 < n <= 8192
-// bf16 tokens and b <= 1024, followed by the compaction of the kept rows.
+// Greedy selection (paper Sec. 4.1, Algorithm 1) for heads with 256 < n <= 4096
+// bf16 tokens and b <= 1024 (longer ones: select_large_kernel), followed by the compaction of the kept rows.
 //
 // Exact greedy on a pool.  Streaming all of V for every pick (one cosine row per
 // pick) is what Algorithm 1 asks for literally; it is also what makes large n
@@ -23,8 +23,7 @@
 //
 // Layout: one workgroup per head, W wave64s, token j = 64*S*w + 64*k + lane in
 // wave w, lane `lane`, slot k; score, m and inverse norm of a token stay in its
-// lane's registers for the whole event (slots 0-7; with sixteen slots per lane,
-// n > 4096, the state of slots 8-15 lives in LDS, one column per thread).
+// lane's registers for the whole event.
 #define KVR_BOUNDS_FILE 2   // ids 2xx of the debug build's bounds checks (kvr_bounds.hpp)
 #include "kvr_dense_common.hpp"
 #include "kvr_kernels.hpp"
@@ -57,14 +56,11 @@ template <int W, int S> struct PoolCfg {
   static constexpr int kUnion = (W * kWaveStage > kTriBytes ? W * kWaveStage : kTriBytes);
   // floats: slots 64 | shared 16 | wcount 16 | pool_tok,r,s,m,picked 5*128 | pend 128 x 16 bit |
   //         order,gain,idxs 3*bcap (b rounded up to 64) ; then pool rows ; then the union area (triangle, stages, and at
-  //         the end the pick flags of the read-out) ; then score, m, inverse norm and pool slot of the
-  //         token slots that do not live in registers
+  //         the end the pick flags of the read-out)
   static constexpr int kFixedFloats = 64 + 16 + 16 + 5 * kPool + 64;          // without the pick lists
-  static constexpr int kRegSlots = S > 8 ? 8 : S;
-  static constexpr int kLdsState = (S - kRegSlots) * 64 * W * 16;
   static_assert(64 * S * W * 4 <= kUnion, "the pick flags of the read-out fit the union area");
   static constexpr int smem_bytes(int b) {
-    return (kFixedFloats + 3 * ((b + 63) & ~63)) * 4 + kPool * kPoolPitch + kUnion + kLdsState;
+    return (kFixedFloats + 3 * ((b + 63) & ~63)) * 4 + kPool * kPoolPitch + kUnion;
   }
 };
 
@@ -101,12 +97,6 @@ __global__ __launch_bounds__(64 * W, (W <= 4 ? 2 : 1)) void select_pool_kernel(P
   float* tri = reinterpret_cast<float*>(uni);                    // packed P x P cosine triangle (race) ...
   // ... or the per-wave row stages of the pass over V ...
   int32_t* flag = reinterpret_cast<int32_t*>(uni);               // ... or, at the end, [n padded] pick flags for the ascending read-out
-  constexpr int SR = Cfg::kRegSlots;                             // token slots whose state lives in registers
-  constexpr int SL = S - SR;                                     // ... and in LDS, [slot - SR][thread]
-  float* sX = reinterpret_cast<float*>(uni + Cfg::kUnion);
-  float* mX = sX + SL * NT;
-  float* rX = mX + SL * NT;
-  int32_t* pX = reinterpret_cast<int32_t*>(rX + SL * NT);
 
   const int h = blockIdx.x;
   const int tid = threadIdx.x, lane = tid & 63;
@@ -122,26 +112,15 @@ __global__ __launch_bounds__(64 * W, (W <= 4 ? 2 : 1)) void select_pool_kernel(P
   float* scratch = reinterpret_cast<float*>(stage + CH * kPoolPitch);
   float* norm_x = scratch + 256;                                 // [64] squared norms of the wave's current 64 tokens
 
-  float s[SR], m[SR], r[SR];
-  int pslot[SR];                 // pool slot of this token in the current epoch, or -1
-  // slot k of this lane: a register for k < SR, this thread's LDS column otherwise (k is a constant
-  // wherever these are used: the loops over the slots are unrolled)
-  const int tidx = threadIdx.x;
-  auto get_s = [&](int k) -> float { return k < SR ? s[k < SR ? k : 0] : sX[(k - SR) * NT + tidx]; };
-  auto get_m = [&](int k) -> float { return k < SR ? m[k < SR ? k : 0] : mX[(k - SR) * NT + tidx]; };
-  auto get_r = [&](int k) -> float { return k < SR ? r[k < SR ? k : 0] : rX[(k - SR) * NT + tidx]; };
-  auto get_p = [&](int k) -> int { return k < SR ? pslot[k < SR ? k : 0] : pX[(k - SR) * NT + tidx]; };
-  auto set_s = [&](int k, float v) { if (k < SR) s[k < SR ? k : 0] = v; else sX[(k - SR) * NT + tidx] = v; };
-  auto set_m = [&](int k, float v) { if (k < SR) m[k < SR ? k : 0] = v; else mX[(k - SR) * NT + tidx] = v; };
-  auto set_r = [&](int k, float v) { if (k < SR) r[k < SR ? k : 0] = v; else rX[(k - SR) * NT + tidx] = v; };
-  auto set_p = [&](int k, int v) { if (k < SR) pslot[k < SR ? k : 0] = v; else pX[(k - SR) * NT + tidx] = v; };
+  float s[S], m[S], r[S];
+  int pslot[S];                  // pool slot of this token in the current epoch, or -1
   auto tok_of = [&](int k) -> int { return base + 64 * k + lane; };
 #pragma unroll
   for (int k = 0; k < S; ++k) {
-    set_s(k, tok_of(k) < n ? a.s_in[static_cast<long long>(h) * n + tok_of(k)] : -INFINITY);
-    set_m(k, 0.f);
-    set_r(k, 0.f);
-    set_p(k, -1);
+    s[k] = tok_of(k) < n ? a.s_in[static_cast<long long>(h) * n + tok_of(k)] : -INFINITY;
+    m[k] = 0.f;
+    r[k] = 0.f;
+    pslot[k] = -1;
   }
   const float nlam = -a.lambda;
   int par = 0;
@@ -172,10 +151,7 @@ __global__ __launch_bounds__(64 * W, (W <= 4 ? 2 : 1)) void select_pool_kernel(P
 
   if (b == 1) {
     float gmax; int i;
-    float sa[S];
-#pragma unroll
-    for (int k = 0; k < S; ++k) sa[k] = get_s(k);
-    wg_argmax(sa, gmax, i);
+    wg_argmax(s, gmax, i);
     if (!(gmax > -INFINITY)) starved = true;
     else { if (tid == 0) { order_l[0] = i; gain_l[0] = gmax; } t = 1; }
   } else {
@@ -199,7 +175,7 @@ __global__ __launch_bounds__(64 * W, (W <= 4 ? 2 : 1)) void select_pool_kernel(P
       float hi = -INFINITY, lo = INFINITY;
 #pragma unroll
       for (int k = 0; k < S; ++k) {
-        const float sk = get_s(k);
+        const float sk = s[k];
         if (sk > -INFINITY && sk < INFINITY) { hi = hw_max(hi, sk); lo = fminf(lo, sk); }
       }
       hi = wave_max_uniform(hi);
@@ -215,11 +191,11 @@ __global__ __launch_bounds__(64 * W, (W <= 4 ? 2 : 1)) void select_pool_kernel(P
     }
     if (!wide) {
 #pragma unroll
-      for (int k = 0; k < S; ++k) alive[k] = __ballot(!(get_s(k) == -INFINITY));
+      for (int k = 0; k < S; ++k) alive[k] = __ballot(!(s[k] == -INFINITY));
     } else {
       uint32_t key[S];
 #pragma unroll
-      for (int k = 0; k < S; ++k) key[k] = tok_of(k) < n ? ordered_key(get_s(k) + 0.0f) : 0u;
+      for (int k = 0; k < S; ++k) key[k] = tok_of(k) < n ? ordered_key(s[k] + 0.0f) : 0u;
       uint32_t T = 0;                                // s_(b) from the leading 16 bits: at most s_(b), the bound only loosens
       for (int bit = 31; bit >= 16; --bit) {
         const uint32_t cand = T | (1u << bit);
@@ -238,8 +214,8 @@ __global__ __launch_bounds__(64 * W, (W <= 4 ? 2 : 1)) void select_pool_kernel(P
       const float thr = sb - a.lambda * 1.00001f - 1e-5f * fabsf(sb);   // fp32 cosines may exceed 1 by a few ulp
 #pragma unroll
       for (int k = 0; k < S; ++k) {
-        const float sk = get_s(k);
-        if (sk < thr) set_s(k, -INFINITY);           // (a NaN threshold or score leaves the token in)
+        const float sk = s[k];
+        if (sk < thr) s[k] = -INFINITY;           // (a NaN threshold or score leaves the token in)
         alive[k] = __ballot(!(sk < thr) && !(sk == -INFINITY));
       }
     }
@@ -263,7 +239,7 @@ __global__ __launch_bounds__(64 * W, (W <= 4 ? 2 : 1)) void select_pool_kernel(P
       // When the cut keys cannot tell a wave's best tokens apart the best one may be left outside
       // and the epoch ends without a pick; it is then repeated on the full keys, where the best
       // token of every wave is a member (equal values join in token order).
-      for (int k = 0; k < S; ++k) { g[k] = fmaf(nlam, get_m(k), get_s(k)); key[k] = ordered_key(g[k]) >> (32 - kbits); }
+      for (int k = 0; k < S; ++k) { g[k] = fmaf(nlam, m[k], s[k]); key[k] = ordered_key(g[k]) >> (32 - kbits); }
       uint32_t tau = 0;                              // largest key value with at least Q keys >= it
       for (int bit = kbits - 1; bit >= 0; --bit) {
         const uint32_t cand = tau | (1u << bit);
@@ -286,12 +262,12 @@ __global__ __launch_bounds__(64 * W, (W <= 4 ? 2 : 1)) void select_pool_kernel(P
         const bool in = above || (equal && eq_before < need_eq);
         const unsigned long long inm = __ballot(in);
         const int slot = w * Q + kvr_ix_if(in, rank_base + __popcll(inm & ((1ull << lane) - 1ull)), Q, 201);   // 201: a member's place in the wave's share
-        set_p(k, in ? slot : -1);
+        pslot[k] = in ? slot : -1;
         if (in) {
           pool_tok[slot] = tok_of(k) < n ? tok_of(k) : -1;
-          pool_r[slot] = get_r(k);
-          pool_s[slot] = get_s(k);
-          pool_m[slot] = get_m(k);
+          pool_r[slot] = r[k];
+          pool_s[slot] = s[k];
+          pool_m[slot] = m[k];
           pool_picked[slot] = 0;
         }
         go[k] = in ? -INFINITY : g[k];
@@ -403,11 +379,11 @@ __global__ __launch_bounds__(64 * W, (W <= 4 ? 2 : 1)) void select_pool_kernel(P
       // pool members: m from the race, picked members leave
 #pragma unroll
       for (int k = 0; k < S; ++k) {
-        const int ps = get_p(k);
+        const int ps = pslot[k];
         if (ps >= 0) {
-          set_m(k, pool_m[ps]);
-          if (!have_r) set_r(k, pool_r[ps]);
-          if (pool_picked[ps]) set_s(k, -INFINITY);
+          m[k] = pool_m[ps];
+          if (!have_r) r[k] = pool_r[ps];
+          if (pool_picked[ps]) s[k] = -INFINITY;
         }
       }
       if (t >= b) break;
@@ -415,7 +391,7 @@ __global__ __launch_bounds__(64 * W, (W <= 4 ? 2 : 1)) void select_pool_kernel(P
       if (np == 0 && t + 1 == b) {                   // the outside token wins the last pick: no row needed
         if (tid == 0) { order_l[t] = jout; gain_l[t] = gout; }
 #pragma unroll
-        for (int k = 0; k < S; ++k) { if (tok_of(k) == jout) set_s(k, -INFINITY); }
+        for (int k = 0; k < S; ++k) { if (tok_of(k) == jout) s[k] = -INFINITY; }
         ++t;
         break;
       }
@@ -423,7 +399,7 @@ __global__ __launch_bounds__(64 * W, (W <= 4 ? 2 : 1)) void select_pool_kernel(P
         if (kbits == 32) { starved = true; break; }  // cannot happen on finite input: the best token was in the pool
         kbits = 32;                                  // the outside bound won on cut keys: full keys from here on
 #pragma unroll
-        for (int k = 0; k < S; ++k) set_p(k, -1);
+        for (int k = 0; k < S; ++k) pslot[k] = -1;
         lds_barrier();                               // the pool tables are rewritten next
         continue;
       }
@@ -540,15 +516,15 @@ __global__ __launch_bounds__(64 * W, (W <= 4 ? 2 : 1)) void select_pool_kernel(P
           wave_lds_sync();
           const float* sp = scratch + kg * 64 + (lane & 15);
           const float mx = hw_max(hw_max(sp[0], sp[16]), hw_max(sp[32], sp[48]));
-          const int ps = get_p(k);
-          float rk = get_r(k);
-          if (!have_r && ps < 0) { rk = tok_of(k) < n ? 1.0f / (sqrtf(norm_x[lane]) + a.eps) : 0.f; set_r(k, rk); }
-          if (ps < 0) set_m(k, hw_max(get_m(k), mx * rk));
+          const int ps = pslot[k];
+          float rk = r[k];
+          if (!have_r && ps < 0) { rk = tok_of(k) < n ? 1.0f / (sqrtf(norm_x[lane]) + a.eps) : 0.f; r[k] = rk; }
+          if (ps < 0) m[k] = hw_max(m[k], mx * rk);
         }
       }
       have_r = true;
 #pragma unroll
-      for (int k = 0; k < S; ++k) set_p(k, -1);
+      for (int k = 0; k < S; ++k) pslot[k] = -1;
       lds_barrier();                               // stages are dead: the next epoch reuses the area
     }
   }
@@ -613,7 +589,7 @@ __global__ __launch_bounds__(64 * W, (W <= 4 ? 2 : 1)) void select_pool_kernel(P
 KVR_BOUNDS_TU(pool)
 
 bool pool_supported(const Layout& lay, int b) {
-  return lay.dtype == DT_BF16 && lay.n > 256 && lay.n <= 8192 && b <= kPoolMaxB;
+  return lay.dtype == DT_BF16 && lay.n > 256 && lay.n <= 4096 && b <= kPoolMaxB;
 }
 
 hipError_t launch_select_pool(const void* K, const void* V, const float* s, const Layout& lay, int b,
@@ -640,8 +616,7 @@ hipError_t launch_select_pool(const void* K, const void* V, const float* s, cons
     if (lay.n <= 512) return go(&select_pool_kernel<2, 4, BUD, PR>, 128, PoolCfg<2, 4>::smem_bytes(b));
     if (lay.n <= 1024) return go(&select_pool_kernel<4, 4, BUD, PR>, 256, PoolCfg<4, 4>::smem_bytes(b));
     if (lay.n <= 2048) return go(&select_pool_kernel<8, 4, BUD, PR>, 512, PoolCfg<8, 4>::smem_bytes(b));
-    if (lay.n <= 4096) return go(&select_pool_kernel<8, 8, BUD, PR>, 512, PoolCfg<8, 8>::smem_bytes(b));
-    return go(&select_pool_kernel<8, 16, BUD, PR>, 512, PoolCfg<8, 16>::smem_bytes(b));
+    return go(&select_pool_kernel<8, 8, BUD, PR>, 512, PoolCfg<8, 8>::smem_bytes(b));
   };
   if (b_h) return prune ? by_shape(std::true_type{}, std::true_type{}) : by_shape(std::true_type{}, std::false_type{});
   return prune ? by_shape(std::false_type{}, std::true_type{}) : by_shape(std::false_type{}, std::false_type{});
