@@ -126,6 +126,55 @@ __device__ __forceinline__ int first_of_slots(const unsigned long long (&e)[NQ])
     return static_cast<int>(best);
   }
 }
+// Which lanes' values satisfy a comparison, for the S token slots of a wave: m[k] = lanes with x <= v[k] (unsigned or float; a
+// NaN never does) or v[k] == x.  The comparisons write S different scalar registers back to back; the compiler's own
+// ballots go through vcc one after the other, and each waits some twenty cycles for the scalar unit to have read the one
+// before (a count over eight slots: 500 -> 200 cycles).  x may come from a v_readfirstlane right before: two wait states.
+#define KVR_MASKS8(op)                                                                                               \
+  asm("s_nop 1\n\t" op " %0, %8, %9\n\t" op " %1, %8, %10\n\t" op " %2, %8, %11\n\t" op " %3, %8, %12\n\t"             \
+      op " %4, %8, %13\n\t" op " %5, %8, %14\n\t" op " %6, %8, %15\n\t" op " %7, %8, %16"                            \
+      : "=&s"(m[0]), "=&s"(m[1]), "=&s"(m[2]), "=&s"(m[3]), "=&s"(m[4]), "=&s"(m[5]), "=&s"(m[6]), "=&s"(m[7])        \
+      : "s"(x), "v"(v[0]), "v"(v[1]), "v"(v[2]), "v"(v[3]), "v"(v[4]), "v"(v[5]), "v"(v[6]), "v"(v[7]))
+#define KVR_MASKS4(op)                                                                                               \
+  asm("s_nop 1\n\t" op " %0, %4, %5\n\t" op " %1, %4, %6\n\t" op " %2, %4, %7\n\t" op " %3, %4, %8"                   \
+      : "=&s"(m[0]), "=&s"(m[1]), "=&s"(m[2]), "=&s"(m[3]) : "s"(x), "v"(v[0]), "v"(v[1]), "v"(v[2]), "v"(v[3]))
+template <int S>
+__device__ __forceinline__ void masks_ge(const uint32_t (&v)[S], uint32_t x, unsigned long long (&m)[S]) {
+  x = static_cast<uint32_t>(__builtin_amdgcn_readfirstlane(static_cast<int>(x)));   // (no-ops when the compiler knows x uniform)
+  if constexpr (S == 8) KVR_MASKS8("v_cmp_le_u32");
+  else if constexpr (S == 4) KVR_MASKS4("v_cmp_le_u32");
+  else
+#pragma unroll
+    for (int k = 0; k < S; ++k) m[k] = __ballot(v[k] >= x);
+}
+template <int S>
+__device__ __forceinline__ void masks_ge(const float (&v)[S], float x, unsigned long long (&m)[S]) {
+  x = __int_as_float(__builtin_amdgcn_readfirstlane(__float_as_int(x)));
+  if constexpr (S == 8) KVR_MASKS8("v_cmp_le_f32");
+  else if constexpr (S == 4) KVR_MASKS4("v_cmp_le_f32");
+  else
+#pragma unroll
+    for (int k = 0; k < S; ++k) m[k] = __ballot(v[k] >= x);
+}
+template <int S>
+__device__ __forceinline__ void masks_eq(const float (&v)[S], float x, unsigned long long (&m)[S]) {
+  x = __int_as_float(__builtin_amdgcn_readfirstlane(__float_as_int(x)));
+  if constexpr (S == 8) KVR_MASKS8("v_cmp_eq_f32");
+  else if constexpr (S == 4) KVR_MASKS4("v_cmp_eq_f32");
+  else
+#pragma unroll
+    for (int k = 0; k < S; ++k) m[k] = __ballot(v[k] == x);
+}
+template <int S, class T>
+__device__ __forceinline__ int count_slots_ge(const T (&v)[S], T x) {
+  unsigned long long m[S];
+  masks_ge<S>(v, x, m);
+  int c = 0;
+#pragma unroll
+  for (int k = 0; k < S; ++k) c += __popcll(m[k]);
+  return c;
+}
+
 // max / sum over each half of the wave (lanes 0-31 and 32-63); valid in lanes 31 and 63
 __device__ __forceinline__ float half_max_at_31(float v) {
   KVR_DPP_MAX(v, 0x111, 0xf) KVR_DPP_MAX(v, 0x112, 0xf) KVR_DPP_MAX(v, 0x114, 0xf)

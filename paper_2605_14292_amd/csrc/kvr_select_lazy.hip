@@ -204,13 +204,16 @@ __global__ __launch_bounds__(64 * W, (W <= 4 ? 2 : 1)) void select_lazy_kernel(L
     for (int k = 1; k < S; ++k) best = hw_max(best, av[k]);
     amax_w = wave_max_uniform(best);
     int i_w = -1;
+    {
+      unsigned long long eq[S], e = 0;               // the lowest slot that holds the maximum, its lowest lane
+      masks_eq<S>(av, amax_w, eq);
+      int k0 = 0;
 #pragma unroll
-    for (int k = S - 1; k >= 0; --k) {
-      const unsigned long long eq = __ballot(av[k] == amax_w);
-      if (eq) {
-        const int l0 = __ffsll(static_cast<long long>(eq)) - 1;
-        const int fr = (__builtin_amdgcn_readlane(static_cast<int>(fresh), l0) >> k) & 1;
-        i_w = (base + 64 * k + l0) | (fr ? 0 : (1 << 30));
+      for (int k = S - 1; k >= 0; --k) { k0 = eq[k] ? k : k0; e = eq[k] ? eq[k] : e; }
+      if (e) {
+        const int l0 = __ffsll(static_cast<long long>(e)) - 1;
+        const int fr = (__builtin_amdgcn_readlane(static_cast<int>(fresh), l0) >> k0) & 1;
+        i_w = (base + 64 * k0 + l0) | (fr ? 0 : (1 << 30));
       }
     }
     if (lane == 0) { slot_gain[par * 16 + w] = amax_w; slot_idx[par * 16 + w] = i_w; }
@@ -313,12 +316,7 @@ __global__ __launch_bounds__(64 * W, (W <= 4 ? 2 : 1)) void select_lazy_kernel(L
         ekey[k] = ((fresh >> k) & 1u) ? k1 : 0u;
       }
       uint32_t tau = 0;                              // largest value with at least Q fresh keys >= it
-      auto at_least_q = [&](uint32_t x) -> bool {
-        int c = 0;
-#pragma unroll
-        for (int k = 0; k < S; ++k) c += __popcll(__ballot(ekey[k] >= x));
-        return c >= Q;
-      };
+      auto at_least_q = [&](uint32_t x) -> bool { return count_slots_ge<S>(ekey, x) >= Q; };
       if (kbits == kLzSelBits && tau_prev != 0) {
         // the value moves little from one epoch to the next: bracket it from the last one with doubling
         // steps, then bisect (a third of the counts of the bit-wise search on the benchmark inputs)
@@ -408,11 +406,8 @@ __global__ __launch_bounds__(64 * W, (W <= 4 ? 2 : 1)) void select_lazy_kernel(L
       // KR tokens qualify: a few bisection steps around the previous epoch's value.
       int cnt_r = 0;
       {
-        auto count_ge = [&](float thr) -> int {
-          int c = 0;
-#pragma unroll
-          for (int k = 0; k < S; ++k) c += __popcll(__ballot(go[k] >= thr && go[k] > -INFINITY));
-          return c;
+        auto count_ge = [&](float thr) -> int {      // (pool members and dead tokens, at -inf, never count)
+          return count_slots_ge<S>(go, thr < -3.402823466e38f ? -3.402823466e38f : thr);
         };
         float thr_r = -INFINITY;                     // first pass: every outside token that can still be picked
         if (have_r && gmax_w > -INFINITY) {
