@@ -7,7 +7,7 @@
 // registers.  The logits of the head are kept in LDS when G*n floats fit, so K
 // is read from HBM exactly once; otherwise the logits are recomputed in a
 // second pass.
-#include "kvr_device.hpp"
+#include "kvr_dense_common.hpp"
 #include "kvr_kernels.hpp"
 
 namespace kvr {
@@ -174,8 +174,18 @@ __global__ __launch_bounds__(kScoreThreads) void score_kernel(const void* __rest
 // bf16, G <= 32 (GQ = 8 or 32 query rows of the MFMA's 32-row operand in use): the logits are a thin dense contraction ([G x d] x [d x n]), so
 // they go through the matrix cores.  K is streamed from HBM once, straight into MFMA
 // operand registers.  The logits of the head wait in LDS for the softmax.
-typedef __attribute__((ext_vector_type(8))) __bf16 bf16x8;
-typedef __attribute__((ext_vector_type(16))) float f32x16;
+
+// The sum over the wave that a butterfly of lane exchanges (32, 16, 8, 4, 2, 1) gives, bit for bit, without its trips through
+// LDS: the halves and the rows are swapped in registers, and from there on every value repeats, so a rotation of the row by 8, 4,
+// 2 and 1 lanes meets the butterfly's partner.  Valid in every lane.
+__device__ __forceinline__ float butterfly_sum(float v) {
+  const auto a = __builtin_amdgcn_permlane32_swap(__float_as_uint(v), __float_as_uint(v), false, false);
+  v = __uint_as_float(a[0]) + __uint_as_float(a[1]);
+  const auto b = __builtin_amdgcn_permlane16_swap(__float_as_uint(v), __float_as_uint(v), false, false);
+  v = __uint_as_float(b[0]) + __uint_as_float(b[1]);
+  KVR_DPP_ADD(v, 0x128, 0xf) KVR_DPP_ADD(v, 0x124, 0xf) KVR_DPP_ADD(v, 0x122, 0xf) KVR_DPP_ADD(v, 0x121, 0xf)
+  return v;
+}
 
 template <int GQ, int NW>
 __global__ __launch_bounds__(64 * NW) void score_mfma_kernel(const char* __restrict__ K,
@@ -217,6 +227,9 @@ __global__ __launch_bounds__(64 * NW) void score_mfma_kernel(const char* __restr
     }
   };
   const float scale = 0.08838834764831845f;
+  float zm[GQ / 2];                                   // maxima of this lane's logits (a tile past the head's end repeats its last token)
+#pragma unroll
+  for (int r = 0; r < GQ / 2; ++r) zm[r] = -INFINITY;
   if (wave < ntiles) fetch(wave, kf);
   for (int t = wave; t < ntiles; t += NW) {
     if (t + NW < ntiles) fetch(t + NW, kn);
@@ -225,35 +238,28 @@ __global__ __launch_bounds__(64 * NW) void score_mfma_kernel(const char* __restr
     for (int ks = 0; ks < 8; ++ks)
       acc = __builtin_amdgcn_mfma_f32_32x32x16_bf16(qf[ks], kf[ks], acc, 0, 0, 0);
     const int j = t * 32 + (lane & 31);
-    if (j < n) {
-      // lane (token, hf) holds query rows (r/4)*8 + hf*4 + r%4 of the 32x32 tile
+    // lane (token, hf) holds query rows (r/4)*8 + hf*4 + r%4 of the 32x32 tile
 #pragma unroll
-      for (int r = 0; r < GQ / 2; ++r) {
-        const int g = (r >> 2) * 8 + hf * 4 + (r & 3);
-        if (g < G) zbuf[g * n + j] = acc[r] * scale;
-      }
+    for (int r = 0; r < GQ / 2; ++r) {
+      const float z = acc[r] * scale;
+      zm[r] = hw_max(zm[r], z);
+      const int g = (r >> 2) * 8 + hf * 4 + (r & 3);
+      if (g < G && j < n) zbuf[g * n + j] = z;
     }
     if (t + NW < ntiles) {
 #pragma unroll
       for (int ks = 0; ks < 8; ++ks) kf[ks] = kn[ks];
     }
   }
-  __syncthreads();
   // softmax over the tokens for each query, then the mean over queries
+#pragma unroll
+  for (int r = 0; r < GQ / 2; ++r) {
+    const float v = half_max_at_31(zm[r]);
+    if ((lane & 31) == 31) red[wave * GQ + (r >> 2) * 8 + hf * 4 + (r & 3)] = v;
+  }
   float zmax[GQ], zsum[GQ];
 #pragma unroll
-  for (int g = 0; g < GQ; ++g) { zmax[g] = -INFINITY; zsum[g] = 0.f; }
-  for (int j = tid; j < n; j += 64 * NW)
-#pragma unroll
-    for (int g = 0; g < GQ; ++g)
-      if (g < G) zmax[g] = fmaxf(zmax[g], zbuf[g * n + j]);
-#pragma unroll
-  for (int g = 0; g < GQ; ++g) {
-    float v = zmax[g];
-#pragma unroll
-    for (int off = 32; off >= 1; off >>= 1) v = fmaxf(v, __shfl_xor(v, off, kWave));
-    if (lane == 0) red[wave * GQ + g] = v;
-  }
+  for (int g = 0; g < GQ; ++g) zsum[g] = 0.f;
   __syncthreads();
 #pragma unroll
   for (int g = 0; g < GQ; ++g) {
@@ -272,9 +278,7 @@ __global__ __launch_bounds__(64 * NW) void score_mfma_kernel(const char* __restr
       }
 #pragma unroll
   for (int g = 0; g < GQ; ++g) {
-    float v = zsum[g];
-#pragma unroll
-    for (int off = 32; off >= 1; off >>= 1) v += __shfl_xor(v, off, kWave);
+    const float v = butterfly_sum(zsum[g]);
     if (lane == 0) red[(NW + wave) * GQ + g] = v;
   }
   __syncthreads();
