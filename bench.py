@@ -210,6 +210,8 @@ def kernel_names(w, b, lam, has_q, mode):
         lazy = w.n <= 4096 and b <= 128             # the library's dispatch
         tail = ["kvr::select_topb_kernel" if lam == 0.0 else "kvr::select_lazy_kernel" if lazy else
                 "kvr::select_pool_kernel" if w.n <= 4096 else "kvr::select_large_kernel"]
+        if lam == 0.0 and has_q and w.G <= 8 and w.n <= 4096 and 12 * (w.G * w.n + 64) <= 160 * 1024:
+            return ["kvr::score_topb_kernel"]
         if lazy and lam > 0.0 and not has_q and b >= 2:   # scores handed in: the heads the score bound shrinks to a short head first
             tail = ["kvr::retain_sparse_kernel", "kvr::select_lazy_kernel (the heads it hands on)"]
     else:

@@ -249,6 +249,10 @@ int kvr_retain(const void* K, const void* V, const void* Q, int G, const float* 
                                                       pick_order, pick_gain, K_out, V_out, st);
     return e == hipSuccess ? KVR_OK : KVR_ERR_HIP;
   }
+  if (Q && kvr::score_topb_supported(l, b, lambda, G)) {   // lambda = 0 on longer heads: likewise
+    const hipError_t e = kvr::launch_score_topb(K, V, Q, G, l, b, s_out, idx_sorted, pick_order, pick_gain, K_out, V_out, st);
+    return e == hipSuccess ? KVR_OK : KVR_ERR_HIP;
+  }
   if (Q) {
     if (kvr::launch_score(K, Q, G, l, s_out, st) != hipSuccess) return KVR_ERR_HIP;
     s = s_out;

@@ -7,8 +7,8 @@
 // registers.  The logits of the head are kept in LDS when G*n floats fit, so K
 // is read from HBM exactly once; otherwise the logits are recomputed in a
 // second pass.
-#include "kvr_dense_common.hpp"
 #include "kvr_kernels.hpp"
+#include "kvr_topb.hpp"
 
 namespace kvr {
 
@@ -187,12 +187,10 @@ __device__ __forceinline__ float butterfly_sum(float v) {
   return v;
 }
 
-template <int GQ, int NW>
-__global__ __launch_bounds__(64 * NW) void score_mfma_kernel(const char* __restrict__ K,
-                                                                   const char* __restrict__ Q, int G,
-                                                                   Layout lay,
-                                                                   float* __restrict__ s_out) {
-  extern __shared__ __align__(16) char smem_raw[];
+// One head's scores on a workgroup of NW waves; finish(score_at) is called when they are there: score_at(j) is token j's.
+template <int GQ, int NW, class Finish>
+__device__ __forceinline__ void score_head(const char* __restrict__ K, const char* __restrict__ Q, int G, const Layout& lay,
+                                           char* smem_raw, Finish finish) {
   float* zbuf = reinterpret_cast<float*>(smem_raw);                         // [G][n]
   const int n = lay.n;
   float* red = zbuf + G * n;                                                // [2][NW][GQ]
@@ -291,14 +289,85 @@ __global__ __launch_bounds__(64 * NW) void score_mfma_kernel(const char* __restr
     for (int u = 1; u < NW; ++u) v += red[(NW + u) * GQ + g];
     wgt[g] = invG / v;
   }
-  float* so = s_out + static_cast<long long>(h) * n;
-  for (int j = tid; j < n; j += 64 * NW) {
+  finish([&](int j) -> float {
     float p = 0.f;
 #pragma unroll
     for (int g = 0; g < GQ; ++g)
       if (g < G) p = fmaf(zbuf[g * n + j], wgt[g], p);
-    so[j] = p;
-  }
+    return p;
+  });
+}
+
+template <int GQ, int NW>
+__global__ __launch_bounds__(64 * NW, GQ == 8 ? 4 : 3) void score_mfma_kernel(const char* __restrict__ K,
+                                                                   const char* __restrict__ Q, int G,
+                                                                   Layout lay,
+                                                                   float* __restrict__ s_out) {
+  extern __shared__ __align__(16) char smem_raw[];
+  float* so = s_out + static_cast<long long>(blockIdx.x) * lay.n;
+  score_head<GQ, NW>(K, Q, G, lay, smem_raw, [&](auto score_at) {
+    for (int j = threadIdx.x; j < lay.n; j += 64 * NW) so[j] = score_at(j);
+  });
+}
+
+// The whole lambda = 0 event: scores, top-b, kept rows.  The search and the copies of one workgroup run beside the streams of K of
+// the others on its CU; as a kernel of its own (select_topb_kernel) the 7168 heads of a call search and copy at the same
+// time, at 4 TB/s: 7168 heads of 1024 tokens, b = 64, 476 us in two launches, 443 in one; of 300, b = 17, 178 and 147.  (Four
+// workgroups per CU instead of three are better up to 512 tokens only: 156 -> 147 us at 300, 443 -> 450 at 1024.)
+template <int S>
+__global__ __launch_bounds__(kTopbThreads, S <= 2 ? 4 : 1) void score_topb_kernel(const char* __restrict__ K, const char* __restrict__ Q, int G,
+                                                                  Layout lay, float* __restrict__ s_out, TopbArgs a) {
+  extern __shared__ __align__(16) char smem_raw[];
+  const int h = blockIdx.x, tid = threadIdx.x, lane = tid & 63;
+  const int w = __builtin_amdgcn_readfirstlane(tid >> 6);
+  float* so = s_out + static_cast<long long>(h) * lay.n;
+  uint32_t key[S];
+  score_head<8, kTopbThreads / 64>(K, Q, G, lay, smem_raw, [&](auto score_at) {
+#pragma unroll
+    for (int k = 0; k < S; ++k) {
+      const int j = k * kTopbThreads + tid;
+      key[k] = 0u;
+      if (j < lay.n) {
+        const float p = score_at(j);
+        so[j] = p;
+        key[k] = ordered_key(p + 0.0f);
+      }
+    }
+  });
+  lds_barrier();                                      // the logits are dead: the tables of the selection take their place
+  topb_finish<S>(a, reinterpret_cast<int32_t*>(smem_raw), key, h, tid, lane, w);
+}
+
+// LDS of a four-wave scorer with its logits; where it leaves room for three workgroups per CU or more, four waves score a head
+static int score_smem_four(const Layout& lay, int G) { return (G * lay.n + 2 * 4 * 8) * 4; }
+
+bool score_topb_supported(const Layout& lay, int b, float lambda, int G) {
+  return topb_supported(lay, b, lambda) && lay.dtype == DT_BF16 && G <= 8 && lay.n <= 16 * kTopbThreads &&
+         3 * score_smem_four(lay, G) <= 160 * 1024;
+}
+
+hipError_t launch_score_topb(const void* K, const void* V, const void* Q, int G, const Layout& lay, int b, float* s_out,
+                             int32_t* idx_sorted, int32_t* pick_order, float* pick_gain, void* K_out, void* V_out,
+                             hipStream_t st) {
+  TopbArgs a;
+  a.b_h = nullptr;
+  a.K = static_cast<const char*>(K); a.V = static_cast<const char*>(V); a.s_in = nullptr;
+  a.idx_sorted = idx_sorted; a.pick_order = pick_order; a.pick_gain = pick_gain;
+  a.K_out = static_cast<char*>(K_out); a.V_out = static_cast<char*>(V_out);
+  a.stride_head = lay.stride_head; a.stride_tok = lay.stride_tok;
+  a.n = lay.n; a.b = b;
+  auto go = [&](auto kern, int slots) -> hipError_t {
+    const int s1 = score_smem_four(lay, G), s2 = topb_smem_bytes(slots, b), smem = s1 > s2 ? s1 : s2;
+    const hipError_t e = hipFuncSetAttribute(reinterpret_cast<const void*>(kern), hipFuncAttributeMaxDynamicSharedMemorySize, smem);
+    if (e != hipSuccess) return e;
+    hipLaunchKernelGGL(kern, dim3(lay.heads), dim3(kTopbThreads), smem, st, static_cast<const char*>(K),
+                       static_cast<const char*>(Q), G, lay, s_out, a);
+    return hipGetLastError();
+  };
+  if (lay.n <= 2 * kTopbThreads) return go(&score_topb_kernel<2>, 2);
+  if (lay.n <= 4 * kTopbThreads) return go(&score_topb_kernel<4>, 4);
+  if (lay.n <= 8 * kTopbThreads) return go(&score_topb_kernel<8>, 8);
+  return go(&score_topb_kernel<16>, 16);
 }
 
 hipError_t launch_score(const void* K, const void* Q, int G, const Layout& lay, float* s_out,
