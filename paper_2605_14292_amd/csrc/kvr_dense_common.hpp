@@ -129,42 +129,44 @@ __device__ __forceinline__ int first_of_slots(const unsigned long long (&e)[NQ])
 // Which lanes' values satisfy a comparison, for the S token slots of a wave: m[k] = lanes with x <= v[k] (unsigned or float; a
 // NaN never does) or v[k] == x.  The comparisons write S different scalar registers back to back; the compiler's own
 // ballots go through vcc one after the other, and each waits some twenty cycles for the scalar unit to have read the one
-// before (a count over eight slots: 500 -> 200 cycles).  x may come from a v_readfirstlane right before: two wait states.
+// before (a count over eight slots: 500 -> 200 cycles).  x may come from a v_readfirstlane right before, and a
+// mask may go to a vector instruction right after: two wait states at either end.
 #define KVR_MASKS8(op)                                                                                               \
   asm("s_nop 1\n\t" op " %0, %8, %9\n\t" op " %1, %8, %10\n\t" op " %2, %8, %11\n\t" op " %3, %8, %12\n\t"             \
-      op " %4, %8, %13\n\t" op " %5, %8, %14\n\t" op " %6, %8, %15\n\t" op " %7, %8, %16"                            \
+      op " %4, %8, %13\n\t" op " %5, %8, %14\n\t" op " %6, %8, %15\n\t" op " %7, %8, %16\n\ts_nop 1"                            \
       : "=&s"(m[0]), "=&s"(m[1]), "=&s"(m[2]), "=&s"(m[3]), "=&s"(m[4]), "=&s"(m[5]), "=&s"(m[6]), "=&s"(m[7])        \
       : "s"(x), "v"(v[0]), "v"(v[1]), "v"(v[2]), "v"(v[3]), "v"(v[4]), "v"(v[5]), "v"(v[6]), "v"(v[7]))
 #define KVR_MASKS4(op)                                                                                               \
-  asm("s_nop 1\n\t" op " %0, %4, %5\n\t" op " %1, %4, %6\n\t" op " %2, %4, %7\n\t" op " %3, %4, %8"                   \
+  asm("s_nop 1\n\t" op " %0, %4, %5\n\t" op " %1, %4, %6\n\t" op " %2, %4, %7\n\t" op " %3, %4, %8\n\ts_nop 1"                   \
       : "=&s"(m[0]), "=&s"(m[1]), "=&s"(m[2]), "=&s"(m[3]) : "s"(x), "v"(v[0]), "v"(v[1]), "v"(v[2]), "v"(v[3]))
-template <int S>
-__device__ __forceinline__ void masks_ge(const uint32_t (&v)[S], uint32_t x, unsigned long long (&m)[S]) {
-  x = static_cast<uint32_t>(__builtin_amdgcn_readfirstlane(static_cast<int>(x)));   // (no-ops when the compiler knows x uniform)
-  if constexpr (S == 8) KVR_MASKS8("v_cmp_le_u32");
-  else if constexpr (S == 4) KVR_MASKS4("v_cmp_le_u32");
-  else
-#pragma unroll
-    for (int k = 0; k < S; ++k) m[k] = __ballot(v[k] >= x);
-}
-template <int S>
-__device__ __forceinline__ void masks_ge(const float (&v)[S], float x, unsigned long long (&m)[S]) {
-  x = __int_as_float(__builtin_amdgcn_readfirstlane(__float_as_int(x)));
-  if constexpr (S == 8) KVR_MASKS8("v_cmp_le_f32");
-  else if constexpr (S == 4) KVR_MASKS4("v_cmp_le_f32");
-  else
-#pragma unroll
-    for (int k = 0; k < S; ++k) m[k] = __ballot(v[k] >= x);
-}
-template <int S>
-__device__ __forceinline__ void masks_eq(const float (&v)[S], float x, unsigned long long (&m)[S]) {
-  x = __int_as_float(__builtin_amdgcn_readfirstlane(__float_as_int(x)));
-  if constexpr (S == 8) KVR_MASKS8("v_cmp_eq_f32");
-  else if constexpr (S == 4) KVR_MASKS4("v_cmp_eq_f32");
-  else
-#pragma unroll
-    for (int k = 0; k < S; ++k) m[k] = __ballot(v[k] == x);
-}
+#define KVR_MASKS3(op)                                                                                               \
+  asm("s_nop 1\n\t" op " %0, %3, %4\n\t" op " %1, %3, %5\n\t" op " %2, %3, %6\n\ts_nop 1"                                          \
+      : "=&s"(m[0]), "=&s"(m[1]), "=&s"(m[2]) : "s"(x), "v"(v[0]), "v"(v[1]), "v"(v[2]))
+#define KVR_MASKS2(op)                                                                                               \
+  asm("s_nop 1\n\t" op " %0, %2, %3\n\t" op " %1, %2, %4\n\ts_nop 1" : "=&s"(m[0]), "=&s"(m[1]) : "s"(x), "v"(v[0]), "v"(v[1]))
+#define KVR_MASKS(name, T, op, cmp, uniform)                                                                         \
+  template <int S>                                                                                                   \
+  __device__ __forceinline__ void name(const T (&v)[S], T x, unsigned long long (&m)[S]) {                           \
+    x = uniform;                                       /* (no-op when the compiler knows x uniform) */               \
+    if constexpr (S == 8) KVR_MASKS8(op);                                                                            \
+    else if constexpr (S == 4) KVR_MASKS4(op);                                                                       \
+    else if constexpr (S == 3) KVR_MASKS3(op);                                                                       \
+    else if constexpr (S == 2) KVR_MASKS2(op);                                                                       \
+    else if constexpr (S > 8 && S % 8 == 0) {                                                                        \
+      _Pragma("unroll") for (int c = 0; c < S; c += 8) {                                                             \
+        T v8[8];                                                                                                     \
+        unsigned long long m8[8];                                                                                    \
+        _Pragma("unroll") for (int k = 0; k < 8; ++k) v8[k] = v[c + k];                                              \
+        name<8>(v8, x, m8);                                                                                          \
+        _Pragma("unroll") for (int k = 0; k < 8; ++k) m[c + k] = m8[k];                                              \
+      }                                                                                                              \
+    } else {                                                                                                         \
+      _Pragma("unroll") for (int k = 0; k < S; ++k) m[k] = __ballot(v[k] cmp x);                                     \
+    }                                                                                                                \
+  }
+KVR_MASKS(masks_ge, uint32_t, "v_cmp_le_u32", >=, static_cast<uint32_t>(__builtin_amdgcn_readfirstlane(static_cast<int>(x))))
+KVR_MASKS(masks_ge, float, "v_cmp_le_f32", >=, __int_as_float(__builtin_amdgcn_readfirstlane(__float_as_int(x))))
+KVR_MASKS(masks_eq, float, "v_cmp_eq_f32", ==, __int_as_float(__builtin_amdgcn_readfirstlane(__float_as_int(x))))
 template <int S, class T>
 __device__ __forceinline__ int count_slots_ge(const T (&v)[S], T x) {
   unsigned long long m[S];

@@ -97,9 +97,7 @@ __global__ __launch_bounds__(kDenseThreads, 4) void retain_pruned_kernel(PrunedA
       uint32_t T = 0;
       for (int bit = 31; bit >= 16; --bit) {
         const uint32_t cand = T | (1u << bit);
-        int cnt = 0;
-#pragma unroll
-        for (int q = 0; q < 4; ++q) cnt += __popcll(__ballot(key[q] >= cand));
+        const int cnt = count_slots_ge<4>(key, cand);
         if (cnt >= bq) T = cand;
       }
       const float sb = key_to_float(T);
@@ -118,14 +116,10 @@ __global__ __launch_bounds__(kDenseThreads, 4) void retain_pruned_kernel(PrunedA
       uint32_t T2 = 0;
       for (int bit = 31; bit >= 0; --bit) {
         const uint32_t cand = T2 | (1u << bit);
-        int cnt = 0;
-#pragma unroll
-        for (int q = 0; q < 4; ++q) cnt += __popcll(__ballot(key[q] >= cand));
+        const int cnt = count_slots_ge<4>(key, cand);
         if (cnt >= kPrN) T2 = cand;
       }
-      int cnt_ge = 0;
-#pragma unroll
-      for (int q = 0; q < 4; ++q) cnt_ge += __popcll(__ballot(key[q] >= T2));
+      const int cnt_ge = count_slots_ge<4>(key, T2);
       const uint32_t cut = cnt_ge == kPrN ? T2 : T2 + 1u;   // T2 < 0xffffffff here: kPrN < n tokens reach it
       ns = 0;
       float out_best = -INFINITY;

@@ -157,9 +157,7 @@ __global__ __launch_bounds__(kF32Threads, 1) void select_dense_f32_kernel(F32Arg
         uint32_t T = 0;
         for (int bit = 31; bit >= 16; --bit) {
           const uint32_t cand = T | (1u << bit);
-          int cnt = 0;
-#pragma unroll
-          for (int q = 0; q < NQ; ++q) cnt += __popcll(__ballot(key[q] >= cand));
+          const int cnt = count_slots_ge<NQ>(key, cand);
           if (cnt >= b) T = cand;
         }
         const float sb = key_to_float(T);
