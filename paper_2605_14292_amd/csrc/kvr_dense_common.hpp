@@ -189,6 +189,20 @@ __device__ __forceinline__ float half_sum_at_31(float v) {
   return v;
 }
 
+// The sum over the wave that a butterfly of lane exchanges (32, 16, 8, 4, 2, 1) gives, bit for bit, without its trips through
+// LDS: the halves and the rows are swapped in registers, and from there on every value repeats, so a rotation of the row by 8, 4,
+// 2 and 1 lanes meets the butterfly's partner.  Valid in every lane.
+__device__ __forceinline__ float half_butterfly_sum(float v) {   // (over lanes 0-31 and 32-63)
+  const auto b = __builtin_amdgcn_permlane16_swap(__float_as_uint(v), __float_as_uint(v), false, false);
+  v = __uint_as_float(b[0]) + __uint_as_float(b[1]);
+  KVR_DPP_ADD(v, 0x128, 0xf) KVR_DPP_ADD(v, 0x124, 0xf) KVR_DPP_ADD(v, 0x122, 0xf) KVR_DPP_ADD(v, 0x121, 0xf)
+  return v;
+}
+__device__ __forceinline__ float butterfly_sum(float v) {
+  const auto a = __builtin_amdgcn_permlane32_swap(__float_as_uint(v), __float_as_uint(v), false, false);
+  return half_butterfly_sum(__uint_as_float(a[0]) + __uint_as_float(a[1]));
+}
+
 // half_sum_at_31 of four values at once: one instruction a step, the four chains filling each other's wait states
 __device__ __forceinline__ void half_sums_at_31(float (&v)[4]) {
 #define KVR_SUM4(ctrl, rmask)                                                        \

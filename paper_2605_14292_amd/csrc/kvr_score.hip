@@ -175,18 +175,6 @@ __global__ __launch_bounds__(kScoreThreads) void score_kernel(const void* __rest
 // they go through the matrix cores.  K is streamed from HBM once, straight into MFMA
 // operand registers.  The logits of the head wait in LDS for the softmax.
 
-// The sum over the wave that a butterfly of lane exchanges (32, 16, 8, 4, 2, 1) gives, bit for bit, without its trips through
-// LDS: the halves and the rows are swapped in registers, and from there on every value repeats, so a rotation of the row by 8, 4,
-// 2 and 1 lanes meets the butterfly's partner.  Valid in every lane.
-__device__ __forceinline__ float butterfly_sum(float v) {
-  const auto a = __builtin_amdgcn_permlane32_swap(__float_as_uint(v), __float_as_uint(v), false, false);
-  v = __uint_as_float(a[0]) + __uint_as_float(a[1]);
-  const auto b = __builtin_amdgcn_permlane16_swap(__float_as_uint(v), __float_as_uint(v), false, false);
-  v = __uint_as_float(b[0]) + __uint_as_float(b[1]);
-  KVR_DPP_ADD(v, 0x128, 0xf) KVR_DPP_ADD(v, 0x124, 0xf) KVR_DPP_ADD(v, 0x122, 0xf) KVR_DPP_ADD(v, 0x121, 0xf)
-  return v;
-}
-
 // One head's scores on a workgroup of NW waves; finish(score_at) is called when they are there: score_at(j) is token j's.
 template <int GQ, int NW, class Finish>
 __device__ __forceinline__ void score_head(const char* __restrict__ K, const char* __restrict__ Q, int G, const Layout& lay,

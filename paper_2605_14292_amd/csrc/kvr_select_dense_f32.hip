@@ -70,26 +70,41 @@ __global__ __launch_bounds__(kF32Threads, 1) void select_dense_f32_kernel(F32Arg
   const int n = a.n, b = a.b;
   const bool diverse = a.lambda != 0.0f && b > 1;
 
+  // The rows start their trip from memory before anything else, those of V behind those of K and the first query: 32 threads per
+  // row (float4 each), rows past n read as zero.  (One head, n = 192, b = 64: 29.0 us with V requested after the scores and
+  // their sums exchanged through LDS, 27.8 now.)
+  float4 kr[NT], xr[NT], q0 = make_float4(0.f, 0.f, 0.f, 0.f);
+  const float* Qh = a.Q + static_cast<long long>(h) * a.G * kD + (tid & 31) * 4;
   if (a.Q) {
-    // Base scores (the stand-in for the paper's external scorer): s_i = (1/G) sum_g softmax_i(q_g . k_i / sqrt(d)).
-    // 32 threads per row (float4 each) take the dot products in fp32, one wave per query takes its softmax.
+    q0 = *reinterpret_cast<const float4*>(Qh);
     const float* Kh = a.K + h * a.stride_head;
-    float4 kr[NT];
 #pragma unroll
     for (int k = 0; k < NT; ++k) {
       const int r = (tid >> 5) + 32 * k;
       kr[k] = make_float4(0.f, 0.f, 0.f, 0.f);
       if (r < n) kr[k] = *reinterpret_cast<const float4*>(Kh + r * a.stride_tok + (tid & 31) * 4);
     }
+  }
+  if (diverse) {
+    const float* Vh = a.V + h * a.stride_head;
+#pragma unroll
+    for (int k = 0; k < NT; ++k) {
+      const int r = (tid >> 5) + 32 * k;
+      xr[k] = make_float4(0.f, 0.f, 0.f, 0.f);
+      if (r < n) xr[k] = *reinterpret_cast<const float4*>(Vh + r * a.stride_tok + (tid & 31) * 4);
+    }
+  }
+  if (a.Q) {
+    // Base scores (the stand-in for the paper's external scorer): s_i = (1/G) sum_g softmax_i(q_g . k_i / sqrt(d)).
+    // 32 threads per row (float4 each) take the dot products in fp32, one wave per query takes its softmax.
     float* zl = stage;                                 // [G][N32] logits, then probabilities (the stage is free until the rows arrive)
     const float scale = 0.08838834764831845f;          // 1/sqrt(128)
     for (int g = 0; g < a.G; ++g) {
-      const float4 qv = *reinterpret_cast<const float4*>(a.Q + (static_cast<long long>(h) * a.G + g) * kD + (tid & 31) * 4);
+      const float4 qv = q0;
+      if (g + 1 < a.G) q0 = *reinterpret_cast<const float4*>(Qh + (g + 1) * kD);
 #pragma unroll
       for (int k = 0; k < NT; ++k) {
-        float p = fmaf(kr[k].x, qv.x, fmaf(kr[k].y, qv.y, fmaf(kr[k].z, qv.z, kr[k].w * qv.w)));
-#pragma unroll
-        for (int off = 16; off >= 1; off >>= 1) p += __shfl_xor(p, off, kWave);
+        const float p = half_butterfly_sum(fmaf(kr[k].x, qv.x, fmaf(kr[k].y, qv.y, fmaf(kr[k].z, qv.z, kr[k].w * qv.w))));
         const int r = (tid >> 5) + 32 * k;
         if ((tid & 31) == 0) zl[g * N32 + r] = r < n ? p * scale : -INFINITY;
       }
@@ -100,13 +115,11 @@ __global__ __launch_bounds__(kF32Threads, 1) void select_dense_f32_kernel(F32Arg
       float mx = -INFINITY;
 #pragma unroll
       for (int q = 0; q < NQ; ++q) { v[q] = zl[wave * N32 + lane + 64 * q]; mx = fmaxf(mx, v[q]); }
-#pragma unroll
-      for (int off = 32; off >= 1; off >>= 1) mx = fmaxf(mx, __shfl_xor(mx, off, kWave));
+      mx = wave_max_uniform(mx);
       float sum = 0.f;
 #pragma unroll
       for (int q = 0; q < NQ; ++q) { v[q] = __expf(v[q] - mx); sum += v[q]; }   // exp(-inf) = 0 for padding
-#pragma unroll
-      for (int off = 32; off >= 1; off >>= 1) sum += __shfl_xor(sum, off, kWave);
+      sum = butterfly_sum(sum);
       const float inv = 1.0f / sum;
 #pragma unroll
       for (int q = 0; q < NQ; ++q) zl[wave * N32 + lane + 64 * q] = v[q] * inv;
@@ -128,16 +141,6 @@ __global__ __launch_bounds__(kF32Threads, 1) void select_dense_f32_kernel(F32Arg
   f32x16_t acc[MAXT];
   int ns = 0;                                       // size of the reduced problem, 0 = all n tokens
   if (diverse) {
-    // the rows start their trip from memory before anything else: 32 threads per row (float4
-    // each), rows past n read as zero
-    const float* Vh = a.V + h * a.stride_head;
-    float4 xr[NT];
-#pragma unroll
-    for (int k = 0; k < NT; ++k) {
-      const int r = (tid >> 5) + 32 * k;
-      xr[k] = make_float4(0.f, 0.f, 0.f, 0.f);
-      if (r < n) xr[k] = *reinterpret_cast<const float4*>(Vh + r * a.stride_tok + (tid & 31) * 4);
-    }
     // Exact candidate reduction for heads of more than 128 tokens: a token with s_j < s_(b) - lambda
     // never wins Eq. 3 (while fewer than b tokens are selected one of the b best-scored is free and
     // gains at least s_(b) - lambda; the token itself gains at most s_j).  When at most 128 tokens
