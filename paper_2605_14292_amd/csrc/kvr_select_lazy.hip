@@ -743,9 +743,14 @@ __global__ __launch_bounds__(64 * W, (W <= 4 ? 2 : 1)) void select_lazy_kernel(L
               for (int q = 0; q < LPC; ++q) {
                 const uint4 x = pre[sub][q];
                 *reinterpret_cast<uint4*>(stage + ((lane & 15) >> 3) * kLzStagePlane + ((lane >> 4) + 4 * q) * kLzHalf + (lane & 7) * 16) = x;
-                if (!have_r) {                       // row (lane >> 4) + 4q of the sub-block is list entry 16*sub + row of the group
-                  const float ss = sum_sq(x);
-                  if ((lane & 15) == 15) norm_x[sub * 16 + (lane >> 4) + 4 * q] = ss;
+              }
+              if (!have_r) {                         // row (lane >> 4) + 4q of the sub-block is list entry 16*sub + row of the group
+                float ss[LPC];                       // (four sums at once fill each other's wait states)
+#pragma unroll
+                for (int q = 0; q < LPC; ++q) ss[q] = sum_sq(pre[sub][q]);
+                if ((lane & 15) == 15) {
+#pragma unroll
+                  for (int q = 0; q < LPC; ++q) norm_x[sub * 16 + (lane >> 4) + 4 * q] = ss[q];
                 }
               }
               fetch(gi + 1, sub);
