@@ -472,9 +472,12 @@ __global__ __launch_bounds__(64 * W, (W <= 4 ? 2 : 1)) void select_lazy_kernel(L
 #pragma unroll
           for (int q = 0; q < LPC; ++q) pre[sub][q] = *reinterpret_cast<const uint4*>(Vh + (o + q * 64u));
         } else {
+          // (rows 4 (lane >> 4) + q of the sub-block: their list entries are one LDS read)
+          const int4 e4 = *reinterpret_cast<const int4*>(lrw_i + gi * GR + sub * CH + 4 * (lane >> 4));
+          const int e[4] = {e4.x, e4.y, e4.z, e4.w};
 #pragma unroll
-          for (int q = 0; q < LPC; ++q) {
-            const int row = kvr_ix(lrw_i[gi * GR + sub * CH + (lane >> 4) + 4 * q], n, 104);
+          for (int q = 0; q < 4; ++q) {
+            const int row = kvr_ix(e[q], n, 104);
             pre[sub][q] = *reinterpret_cast<const uint4*>(Vh + (static_cast<uint32_t>(row) * pitch_b + (lane & 15) * 16u));
           }
         }
@@ -742,16 +745,13 @@ __global__ __launch_bounds__(64 * W, (W <= 4 ? 2 : 1)) void select_lazy_kernel(L
 #pragma unroll
               for (int q = 0; q < LPC; ++q) {
                 const uint4 x = pre[sub][q];
-                *reinterpret_cast<uint4*>(stage + ((lane & 15) >> 3) * kLzStagePlane + ((lane >> 4) + 4 * q) * kLzHalf + (lane & 7) * 16) = x;
+                *reinterpret_cast<uint4*>(stage + ((lane & 15) >> 3) * kLzStagePlane + (4 * (lane >> 4) + q) * kLzHalf + (lane & 7) * 16) = x;
               }
-              if (!have_r) {                         // row (lane >> 4) + 4q of the sub-block is list entry 16*sub + row of the group
-                float ss[LPC];                       // (four sums at once fill each other's wait states)
+              if (!have_r) {                         // row 4 (lane >> 4) + q of the sub-block is list entry 16*sub + row of the group
+                float ss[4];                         // (four sums at once fill each other's wait states)
 #pragma unroll
-                for (int q = 0; q < LPC; ++q) ss[q] = sum_sq(pre[sub][q]);
-                if ((lane & 15) == 15) {
-#pragma unroll
-                  for (int q = 0; q < LPC; ++q) norm_x[sub * 16 + (lane >> 4) + 4 * q] = ss[q];
-                }
+                for (int q = 0; q < 4; ++q) ss[q] = sum_sq(pre[sub][q]);
+                if ((lane & 15) == 15) *reinterpret_cast<float4*>(norm_x + sub * 16 + 4 * (lane >> 4)) = make_float4(ss[0], ss[1], ss[2], ss[3]);
               }
               fetch(gi + 1, sub);
               wave_lds_sync();
