@@ -442,6 +442,9 @@ __global__ __launch_bounds__(64 * W, (W <= 4 ? 2 : 1)) void select_lazy_kernel(L
             if (above && idle > 0) thr_r = gmax_w - hi_d;
             delta = -1.f;
           }
+          // A token with a score of +inf is outside, and distances from an infinite bound say nothing (inf - inf is a NaN, which
+          // would list no token: none of them fresh again, none ever picked).  The list takes exactly these tokens.
+          if (gmax_w == INFINITY) { thr_r = 3.402823466e38f; delta = -1.f; }
         }
         int off = 0;
 #pragma unroll
@@ -622,7 +625,7 @@ __global__ __launch_bounds__(64 * W, (W <= 4 ? 2 : 1)) void select_lazy_kernel(L
           if (kbits == 32) { starved = true; break; }
           kbits = 32;
         }
-        if (++idle > n + 8) { starved = true; break; }   // (never reached on finite input, by the count above)
+        if (++idle > n + 8) { starved = true; break; }   // (never reached without a NaN, by the count above)
       } else {
         idle = 0;
       }

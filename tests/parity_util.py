@@ -95,6 +95,24 @@ def check_head(s64, V64, b, lam, eps, order, gain, idx_sorted) -> HeadReport:
     return HeadReport(identical, near, o_ties, max_err)
 
 
+def check_infinite_first(s64, V64, b, lam, eps, order, gain):
+    """A head with scores of +inf: these tokens are picked first, in token order, and Eq. 2 goes on from there."""
+    first = np.flatnonzero(np.isposinf(s64))[:b]
+    np.testing.assert_array_equal(order[:len(first)], first)
+    assert np.all(np.isposinf(gain[:len(first)]))
+    sc = s64.copy()
+    sc[first] = -np.inf
+    Vh = O.signatures(V64, eps)
+    m = np.maximum((Vh @ Vh[first].T).max(1), 0.0)
+    for t in range(len(first), b):
+        g = sc - lam * m
+        scale = max(abs(sc[order[t]]) + lam * m[order[t]], 1e-30)
+        assert g.max() - g[order[t]] <= NEAR_TIE * scale, f"pick {t}"
+        assert abs(gain[t] - g[order[t]]) <= GAIN_RTOL * scale, f"pick {t}"
+        sc[order[t]] = -np.inf
+        np.maximum(m, Vh @ Vh[order[t]], out=m)
+
+
 def check_scores(s_hip, s64):
     s_hip = np.asarray(s_hip, dtype=np.float64)
     err = np.abs(s_hip - s64) / np.maximum(np.abs(s64), 1e-30)

@@ -71,19 +71,7 @@ def test_many_infinite_scores(n, b, every):
     s[0, ::every] = float("inf")
     out = B.kvr_retain(K, V, b, .5, 1e-6, s=s)
     torch.cuda.synchronize()
-    first = np.arange(0, n, every)[:b]
-    order, gain = out.pick_order[0].cpu().numpy(), out.pick_gain[0].cpu().numpy()
-    np.testing.assert_array_equal(order[:len(first)], first)
-    assert np.all(np.isposinf(gain[:len(first)]))
-    rows, sc = W.to_f64(V[0]), W.to_f64(s[0])
-    rows = rows / (np.linalg.norm(rows, axis=1, keepdims=True) + 1e-6)
-    m = np.maximum((rows @ rows[first].T).max(1), 0.)
-    sc[first] = -np.inf
-    for t in range(len(first), b):                     # a sum of 128 products of bf16 rows in fp32 is right to about 1e-6
-        g = sc - .5 * m
-        assert g[order[t]] >= g.max() - 2e-6 and abs(gain[t] - g[order[t]]) <= 2e-6
-        sc[order[t]] = -np.inf
-        m = np.maximum(m, rows @ rows[order[t]])
+    P.check_infinite_first(W.to_f64(s[0]), W.to_f64(V[0]), b, .5, 1e-6, out.pick_order[0].cpu().numpy(), out.pick_gain[0].cpu().numpy())
     P.check_head(W.to_f64(s[1]), W.to_f64(V[1]), b, .5, 1e-6, out.pick_order[1].cpu().numpy(), out.pick_gain[1].cpu().numpy(),
                  out.idx_sorted[1].cpu().numpy())
 

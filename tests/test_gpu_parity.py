@@ -576,6 +576,24 @@ def test_non_finite_scores_on_long_heads_still_give_distinct_indices_in_range(n,
     assert order[2][0] == 5 and order[2][1] == 7          # +inf scores go first, lowest index first
 
 
+@pytest.mark.parametrize("n,b,every,dtype", [
+    (500, 128, 3, torch.bfloat16), (1000, 100, 2, torch.bfloat16), (1024, 128, 1, torch.bfloat16), (700, 100, 8, torch.bfloat16),
+    (2048, 128, 3, torch.bfloat16), (3000, 100, 29, torch.bfloat16), (4096, 128, 2, torch.bfloat16), (1024, 200, 4, torch.bfloat16),
+    (900, 100, 4, torch.float32), (2500, 128, 3, torch.float32), (4096, 128, 40, torch.float32)])
+def test_more_infinite_scores_than_a_pool_holds(n, b, every, dtype):
+    # (a recent window that a caller marks with +inf: more such tokens than a wave has places in the pool)
+    K, V, s = _mk(3, n, 4444 + n, dtype)
+    s = s.clone()
+    s[0, ::every] = float("inf")
+    s[1, n - n // every:] = float("inf")
+    out = B().kvr_retain(K, V, b, 0.5, 1e-6, s=s)
+    torch.cuda.synchronize()
+    for hh in (0, 1):
+        P.check_infinite_first(W.to_f64(s[hh]), W.to_f64(V[hh]), b, 0.5, 1e-6, out.pick_order[hh].cpu().numpy(),
+                               out.pick_gain[hh].cpu().numpy())
+    _check_heads(W.WORKLOADS["c3"], {"K": K, "V": V, "s": s}, out, b, 0.5, 1e-6, [2])
+
+
 @pytest.mark.parametrize("dtype", [torch.bfloat16, torch.float32])
 def test_debug_validator_finds_non_finite_inputs(dtype):
     h, n, G = 5, 300, 3
