@@ -67,12 +67,14 @@ template <int S> struct LargeCfg {
   static_assert(kLgW * kStage <= kPass, "the stages fit the chunks' area");
   static constexpr int kTriBytes = padded_tri_floats(kLgPool) * 4;
   static constexpr int kRowBytes = kLgPool * kLgPitch;
+  static constexpr int kCounts = 16 * 64;         // per wave, while its list is built: stale entries by class and lane
   static constexpr int kMax2 = kTriBytes > kRowBytes ? kTriBytes : kRowBytes;
   static constexpr int kUnion = ((kPass > kMax2 ? kPass : kMax2) + 15) & ~15;
-  // floats: slots 64 | shared 16 | wcount 16 | first 64 picks needed by every 64 list entries 8*8 | stale entries by those W*16 |
+  static_assert(kRowBytes + kLgW * kCounts * 4 <= kUnion && kRowBytes % 16 == 0, "the counters of the lists fit above the pool's rows");
+  // floats: slots 64 | shared 16 | wcount 16 | first 64 picks needed by every 64 list entries 8*8 |
   //         pool_tok,r,s,m,picked 5*P | inverse norms 64*S*W | lists W*CAP (at the end the sorted indices) |
   //         order, gain, pick_r 3*bcap ; then the waves' scratch and the union area (pool rows -> triangle -> stages -> chunks -> pick flags)
-  static constexpr int kTables = 160 + 16 * kLgW;
+  static constexpr int kTables = 160;
   static constexpr int kFixedFloats = kTables + 5 * kLgPool + TPW * kLgW;
   static constexpr int kListFloats = kLgW * CAP;
   static_assert(kListFloats >= kLgMaxB, "the sorted indices fit the lists");
@@ -99,7 +101,6 @@ __global__ __launch_bounds__(kLgThreads, 1) void select_large_kernel(LargeArgs a
   int32_t* shared_i = reinterpret_cast<int32_t*>(smem + 64);     // [16] np, t, stop reason
   int32_t* wcount = reinterpret_cast<int32_t*>(smem + 80);       // [16]
   int32_t* gstart = reinterpret_cast<int32_t*>(smem + 96);       // [W][8] first 64 picks (by number / 64) that 64 entries of the wave's list need, kLgNone past the last
-  int32_t* hist = reinterpret_cast<int32_t*>(smem + 160);        // [W][16] stale entries of a wave's list by that number, then their first positions
   int32_t* pool_tok = reinterpret_cast<int32_t*>(smem + Cfg::kTables);    // [P] token of the member, -1 = none
   float* pool_r = smem + Cfg::kTables + P;
   float* pool_s = smem + Cfg::kTables + 2 * P;
@@ -380,31 +381,56 @@ __global__ __launch_bounds__(kLgThreads, 1) void select_large_kernel(LargeArgs a
       int cnt_r = 0;                                 // entries of the list
       bool split = false;                            // the list takes two turns: the wave's lower slots, then the others
       float thr_r = -INFINITY;
-      // Stale entries come first, ordered by the 64 picks from which they have yet to meet the picks (an LDS atomic gives an
-      // entry its place among those with the same ones; their order changes nothing), then the fresh ones in token order.
+      // Stale entries come first, ordered by the 64 picks from which they have yet to meet the picks (their class), those of a
+      // class by lane and slot, then the fresh ones in token order.  The order decides which entries share a start, so it must not
+      // depend on the order in which the hardware serves lanes: every lane counts its entries of a class in a counter of its own, and
+      // a prefix sum over (class, lane) gives each counter its first position.
       auto build_list = [&](auto member) {
-        int32_t* hw = hist + w * 16;
-        if (lane < 16) hw[lane] = 0;
+        fresh_lane();
+        int wu = w;
+        asm volatile("" : "+s"(wu));                 // (likewise: no addresses kept over the epochs)
+        int32_t* const counts = reinterpret_cast<int32_t*>(uni + Cfg::kRowBytes) + wu * Cfg::kCounts;   // [16][64], above the pool's rows, which other waves may be storing
+        int32_t* const mine = counts + lane;
+        auto class_of = [&](int k) -> int { return static_cast<int>((cov[k >> 2] >> (8 * (k & 3) + 2)) & 0xfu); };
+        int4* const share = reinterpret_cast<int4*>(counts + lane * 16);   // sixteen counters of a class, four lanes a class
+#pragma unroll
+        for (int u = 0; u < 4; ++u) share[u] = make_int4(0, 0, 0, 0);
         wave_lds_sync();
         int place_in[S];
 #pragma unroll
         for (int k = 0; k < S; ++k) {
           place_in[k] = 0;
-          if (member(k) && !((fresh >> k) & 1u)) place_in[k] = atomicAdd(&hw[(cov[k >> 2] >> (8 * (k & 3) + 2)) & 0xfu], 1);
+          if (member(k) && !((fresh >> k) & 1u)) place_in[k] = atomicAdd(&mine[64 * class_of(k)], 1);
         }
         wave_lds_sync();
-        const int own = lane < 16 ? hw[lane] : 0;
-        int incl = own;                              // inclusive prefix sums over the sixteen (one DPP row)
-        incl += __builtin_amdgcn_update_dpp(0, incl, 0x111, 0xf, 0xf, false);
-        incl += __builtin_amdgcn_update_dpp(0, incl, 0x112, 0xf, 0xf, false);
-        incl += __builtin_amdgcn_update_dpp(0, incl, 0x114, 0xf, 0xf, false);
-        incl += __builtin_amdgcn_update_dpp(0, incl, 0x118, 0xf, 0xf, false);
-        if (lane < 16) hw[lane] = incl - own;
-        int off = __builtin_amdgcn_readlane(incl, 15);
+        int incl;
+        {
+          int4 c[4];
+#pragma unroll
+          for (int u = 0; u < 4; ++u) c[u] = share[u];
+          int own = 0;
+#pragma unroll
+          for (int u = 0; u < 4; ++u) {
+            const int x = c[u].x, y = c[u].y, z = c[u].z, q = c[u].w;
+            c[u] = make_int4(own, own + x, own + x + y, own + x + y + z);
+            own += x + y + z + q;
+          }
+          incl = own;                                // inclusive prefix sums over the lanes' shares
+          incl += __builtin_amdgcn_update_dpp(0, incl, 0x111, 0xf, 0xf, false);
+          incl += __builtin_amdgcn_update_dpp(0, incl, 0x112, 0xf, 0xf, false);
+          incl += __builtin_amdgcn_update_dpp(0, incl, 0x114, 0xf, 0xf, false);
+          incl += __builtin_amdgcn_update_dpp(0, incl, 0x118, 0xf, 0xf, false);
+          incl += __builtin_amdgcn_update_dpp(0, incl, 0x142, 0xa, 0xf, false);
+          incl += __builtin_amdgcn_update_dpp(0, incl, 0x143, 0xc, 0xf, false);
+          const int at = incl - own;
+#pragma unroll
+          for (int u = 0; u < 4; ++u) share[u] = make_int4(c[u].x + at, c[u].y + at, c[u].z + at, c[u].w + at);
+        }
+        int off = __builtin_amdgcn_readlane(incl, 63);
         wave_lds_sync();
 #pragma unroll
         for (int k = 0; k < S; ++k)                  // (all the reads before the first write)
-          place_in[k] += hw[(cov[k >> 2] >> (8 * (k & 3) + 2)) & 0xfu];
+          place_in[k] += mine[64 * class_of(k)];
 #pragma unroll
         for (int k = 0; k < S; ++k) {
           const bool mem = member(k), fr = (fresh >> k) & 1u;
@@ -420,7 +446,7 @@ __global__ __launch_bounds__(kLgThreads, 1) void select_large_kernel(LargeArgs a
         int first = kLgNone;                         // lane g: of entry 64 g
 #pragma unroll
         for (int g = 0; g < CAP / 64; ++g) {
-          const int c = __popcll(__ballot(lane < 16 && incl <= 64 * g));
+          const int c = __popcll(__ballot((lane & 3) == 3 && incl <= 64 * g));
           const int f = g * 64 < cnt_r ? (c < 16 ? min(c, t0 >> 6) : t0 >> 6) : kLgNone;
           first = lane == g ? f : first;
         }

@@ -76,6 +76,23 @@ def test_many_infinite_scores(n, b, every):
                  out.idx_sorted[1].cpu().numpy())
 
 
+@pytest.mark.parametrize("n,b,kind", [(8192, 1024, "tight"), (5000, 400, "tied")])
+def test_runs_repeat_bit_for_bit(n, b, kind):
+    """The order of a refresh list decides which products a token meets, and with them its last bits: the same heads again, on
+    another stream, and each head at another place of the call."""
+    heads = 8
+    K, V, s = (x.repeat((heads // 2,) + (1,) * (x.dim() - 1)) for x in _inputs(2, n, kind, n - b))
+    a = B.kvr_retain(K, V, b, .5, 1e-6, s=s)
+    torch.cuda.synchronize()
+    st = torch.cuda.Stream()
+    with torch.cuda.stream(st):
+        c = B.kvr_retain(K, V, b, .5, 1e-6, s=s, stream=st)
+    st.synchronize()
+    for f in ("idx_sorted", "pick_order", "pick_gain", "K_out", "V_out"):
+        x, y = getattr(a, f), getattr(c, f)
+        assert torch.equal(x, y) and torch.equal(x, x[:2].repeat((heads // 2,) + (1,) * (x.dim() - 1))), f
+
+
 def test_rows_apart_in_memory():
     """Token strides: a little more than a row, and so much that a head spans 2 GiB (offsets of 64 bits)."""
     n, b = 4100, 130
