@@ -78,12 +78,13 @@ __device__ __forceinline__ float max3(float a, float b, float c) {
   return r;
 }
 // ra[lane ln] = va, rb[lane ln] = vb for wave-uniform va, vb, ln; the other lanes keep their
-// values.  The lane select goes through m0 because a VALU instruction reads one SGPR only.
+// values.  The lane select goes through m0 because a VALU instruction reads one SGPR only.  (va may come from a v_readfirstlane
+// right before the block, which the compiler does not look into: two wait states before it is read, s_nop and s_mov.)
 __device__ __forceinline__ void write_lane2(int& ra, int& rb, int va, int vb, int ln) {
   va = __builtin_amdgcn_readfirstlane(va);             // no-ops when the compiler knows them uniform
   vb = __builtin_amdgcn_readfirstlane(vb);
   ln = __builtin_amdgcn_readfirstlane(ln);
-  asm("s_mov_b32 m0, %4\n\tv_writelane_b32 %0, %2, m0\n\tv_writelane_b32 %1, %3, m0"
+  asm("s_nop 0\n\ts_mov_b32 m0, %4\n\tv_writelane_b32 %0, %2, m0\n\tv_writelane_b32 %1, %3, m0"
       : "+v"(ra), "+v"(rb)
       : "s"(va), "s"(vb), "s"(ln)
       : "m0");
