@@ -11,7 +11,7 @@ from paper_2605_14292_amd import build
 
 def _blocks(source, tmp_path):
     out = tmp_path / "out.s"
-    subprocess.run([os.environ.get("HIPCC", "/opt/rocm/bin/hipcc"), *build.FLAGS, "-S", "--cuda-device-only",
+    subprocess.run([os.environ.get("HIPCC", "/opt/rocm/bin/hipcc"), *build.FLAGS, "-I", build.CSRC, "-S", "--cuda-device-only",
                     os.path.join(build.CSRC, source), "-o", str(out)], check=True, stderr=subprocess.DEVNULL)
     return re.findall(r"#ASMSTART\n(.*?)#ASMEND", out.read_text(), re.S)
 
@@ -33,3 +33,25 @@ def test_the_race_waits_before_its_first_scalar_operand(source, tmp_path):
             lanes += 1
             assert _states(block[: block.index("v_writelane_b32")]) >= 2
     assert races > 0 and lanes > 0
+
+
+def test_the_mask_blocks_wait_at_either_end(tmp_path):
+    """x of masks_ge / masks_eq may come from a v_readfirstlane right before the block, a mask may go to a vector instruction
+    right after it."""
+    src = tmp_path / "masks.hip"
+    src.write_text("""#include "kvr_dense_common.hpp"
+template <int S> __global__ void masks(const uint32_t* u, const float* f, unsigned long long* out, uint32_t x, float y) {
+  uint32_t v[S]; float g[S]; unsigned long long m[3][S];
+  for (int k = 0; k < S; ++k) { v[k] = u[64 * k + threadIdx.x]; g[k] = f[64 * k + threadIdx.x]; }
+  kvr::masks_ge<S>(v, x, m[0]); kvr::masks_ge<S>(g, y, m[1]); kvr::masks_eq<S>(g, y, m[2]);
+  for (int q = 0; q < 3; ++q) for (int k = 0; k < S; ++k) out[q * S + k] = m[q][k];
+}
+""" + "".join("template __global__ void masks<%d>(const uint32_t*, const float*, unsigned long long*, uint32_t, float);\n" % n
+              for n in (2, 3, 4, 8, 16)))
+    blocks = [re.findall(r"^\s+([a-z]\S+)\s*(.*)$", b, re.M) for b in _blocks(str(src), tmp_path) if "v_cmp" in b]
+    assert len(blocks) == 3 * (4 + 2)                           # sixteen slots are two blocks
+    for b in blocks:
+        assert b[0] == ("s_nop", "1") and b[-1] == ("s_nop", "1")
+        assert all(op in ("v_cmp_le_u32", "v_cmp_le_f32", "v_cmp_eq_f32") for op, _ in b[1:-1]) and len(b) > 3
+        written = [args.split(",")[0] for _, args in b[1:-1]]
+        assert len(set(written)) == len(written)
