@@ -442,14 +442,13 @@ __global__ __launch_bounds__(64 * W, (W <= 4 ? 2 : 1)) void select_lazy_kernel(L
             if (above && idle > 0) thr_r = gmax_w - hi_d;
             delta = -1.f;
           }
-          // A token with a score of +inf is outside, and distances from an infinite bound say nothing (inf - inf is a NaN, which
-          // would list no token: none of them fresh again, none ever picked).  The list takes exactly these tokens.
-          if (gmax_w == INFINITY) { thr_r = 3.402823466e38f; delta = -1.f; }
         }
         int off = 0;
 #pragma unroll
         for (int k = 0; k < S; ++k) {
-          const bool mem = go[k] >= thr_r && go[k] > -INFINITY;     // (go is -inf for pool members and dead tokens)
+          // (go is -inf for pool members and dead tokens.  With a token at +inf outside, a distance from the best one is inf - inf and
+          // thr_r a NaN: every token is listed then, or those at +inf would stay stale and could never be picked)
+          const bool mem = !(go[k] < thr_r) && go[k] > -INFINITY;
           const unsigned long long mm = __ballot(mem);
           if (mem) {
             const int pos = kvr_ix(off + __popcll(mm & below), TPW, 102);   // 102: position in the refresh list
