@@ -354,13 +354,13 @@ int retain_budgeted(const void* K, const void* V, const void* Q, int G, const fl
   hipStream_t st = static_cast<hipStream_t>(stream);
   const kvr::Layout l = to_dev(lay);
   const float* src = s_in;
-  if (Q) {
+  if (Q) {                               // (also at lambda = 0: the scores are adjusted before the selection, which score_topb_kernel cannot)
     if (kvr::launch_score(K, Q, G, l, s_work, st) != hipSuccess) return KVR_ERR_HIP;
     src = s_work;
   }
   if (kvr::launch_budget_prepare(src, l, n_h, keep, lambda_h, lambda, s_work, st) != hipSuccess)
     return KVR_ERR_HIP;
-  // bf16 heads of up to 4096 tokens: the fused kernels take the per-head budgets themselves (the chain of a head
+  // bf16 heads of up to 8192 tokens: the fused kernels take the per-head budgets themselves (the chain of a head
   // stops at its own budget; lists, padding and kept rows are written by the kernel that selected
   // them); what is left is elementwise: the gains of protected tokens, per-head lambdas, position ids.
   const bool long_heads = lambda > 0.0f && (kvr::pool_supported(l, b_max) || kvr::large_supported(l, b_max));

@@ -286,6 +286,9 @@ __device__ __forceinline__ void score_head(const char* __restrict__ K, const cha
   });
 }
 
+// Waves per SIMD asked for: what the registers allow anyway (124 and 149), told to the compiler, which then spends all of them on the
+// tile in flight; against no bound: 7168 heads of 300 tokens, 7 queries, 104.0 -> 101.1 us, of 1024 332.7 -> 331.0, 1024 of 900
+// with 32 queries 101.7 -> 100.8; 2048 of 4096 and 112 of 1024 or 4000 tokens do not change.
 template <int GQ, int NW>
 __global__ __launch_bounds__(64 * NW, GQ == 8 ? 4 : 3) void score_mfma_kernel(const char* __restrict__ K,
                                                                    const char* __restrict__ Q, int G,

@@ -9,14 +9,18 @@
 //   3. one wave runs Algorithm 1 inside the pool for as long as the pool's best (gain, lower index) beats the bound;
 //   4. every wave brings the quarter of its tokens with the highest bounds up to date (the first epoch: every token).
 // What differs is where the rows of the picks are: a thousand of them do not fit LDS, so step 4 streams them, 128 at a
-// time and shared by all waves, past the 128 rows that every wave holds as operands, and a token meets only the picks that
-// its m does not cover yet.  Every token carries the 16-pick tile up to which it is covered; a wave's list holds its
-// stale tokens first, the least covered ones in front, and its fresh ones, which need the last epoch's picks only, after them.
+// time and shared by all waves, past the 128 rows that every wave holds as operands.  Every token carries the 16-pick tile up to
+// which its m covers the picks; a wave's list holds its stale tokens first, the least covered ones in front, and its fresh ones,
+// which need the last epoch's picks only, after them, and every 64 entries start at the first block of 64 picks that one of them
+// has yet to meet.  (So an entry meets up to 63 picks again, more beside less covered neighbours.  Their cosines are the ones that
+// m has seen but for the last bit: the triangle multiplies a sum by the norms of its two tokens in their order, the pass by
+// the pick's first.)
 //
-// Why lazily here too: with all of V read after every epoch 256 heads of 8192 tokens with b = 1024 read their rows 23
-// times (13 GB) and took 2770 us at 4.7 TB/s, here 6 times in 1610 us.  A pool of 192 and an eighth of the tokens per pass
-// are faster (1300 us), but then the epochs are others than those of a full refresh, other cosines come out of the pool's
-// triangle, where the two inverse norms are multiplied in another order, and among 7840 heads two kept another token; with
+// Why lazily here too: with all of V read after every epoch 256 heads of 8192 tokens with b = 1024 fetched 13.2 GB and took
+// 2770 us, here 4.6 GB in 1620-1700 us (by the memory counters, 24.6 and 8.6 times V's 0.54 GB: the listed rows, the rows of
+// the pools and of the picks, which every round streams again, and spilled registers).  A pool of 192 and an eighth of the
+// tokens per pass are faster (1300 us), but then the epochs are others than those of a full refresh, other cosines come out of
+// the pool's triangle, and among 7840 heads two kept another token; with
 // a quarter of the tokens fresh the pools are nearly always those of a full refresh (none did).  Asking for that in
 // every epoch, with passes until no stale bound reaches a wave's best seventeen, costs more than it saves (2250 us).
 //
@@ -140,7 +144,8 @@ __global__ __launch_bounds__(kLgThreads, 1) void select_large_kernel(LargeArgs a
   int32_t* lrw_i = reinterpret_cast<int32_t*>(lrw);
 
   // Kept in registers: m, two packed tables and bit masks.  The scores are read from memory again in every epoch (they are
-  // needed for the choice of the pool and the list only), which is what leaves the pass its 150 registers.
+  // needed for the choice of the pool and the list only).  All 256 registers are in use all the same, and 22 to 24 of them spill: 176
+  // bytes of scratch per lane, some 0.86 of the 1.0 GB that 256 heads of 8192 tokens write.
   float s[S], m[S];
   uint32_t dead = 0;             // bit k: token past the head, below the score bound or picked (its score counts as -inf)
   uint32_t place[S / 2];         // 16 bits each: 0 = none, 1 + pool slot of this token in the current epoch, or 0x8000 + position in the wave's refresh list
@@ -718,9 +723,6 @@ __global__ __launch_bounds__(kLgThreads, 1) void select_large_kernel(LargeArgs a
 #pragma unroll
                 for (int ks = 0; ks < 4; ++ks) av[ks] = *reinterpret_cast<const bf16x8*>(ap + ks * 16);
                 const float4 p0 = *reinterpret_cast<const float4*>(pr);
-#ifdef VB
-                __builtin_amdgcn_sched_barrier(0);
-#endif
                 f32x4 acc[4 * quads];
 #pragma unroll
                 for (int v = 0; v < quads; ++v) {
