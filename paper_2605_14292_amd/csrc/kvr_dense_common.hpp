@@ -166,8 +166,13 @@ __device__ __forceinline__ int first_of_slots(const unsigned long long (&e)[NQ])
     }                                                                                                                \
   }
 KVR_MASKS(masks_ge, uint32_t, "v_cmp_le_u32", >=, static_cast<uint32_t>(__builtin_amdgcn_readfirstlane(static_cast<int>(x))))
+KVR_MASKS(masks_gt, uint32_t, "v_cmp_lt_u32", >, static_cast<uint32_t>(__builtin_amdgcn_readfirstlane(static_cast<int>(x))))
 KVR_MASKS(masks_ge, float, "v_cmp_le_f32", >=, __int_as_float(__builtin_amdgcn_readfirstlane(__float_as_int(x))))
 KVR_MASKS(masks_eq, float, "v_cmp_eq_f32", ==, __int_as_float(__builtin_amdgcn_readfirstlane(__float_as_int(x))))
+// how many lanes below this one are in the mask
+__device__ __forceinline__ int lane_rank(unsigned long long m) {
+  return static_cast<int>(__builtin_amdgcn_mbcnt_hi(static_cast<uint32_t>(m >> 32), __builtin_amdgcn_mbcnt_lo(static_cast<uint32_t>(m), 0u)));
+}
 template <int S, class T>
 __device__ __forceinline__ int count_slots_ge(const T (&v)[S], T x) {
   unsigned long long m[S];
