@@ -364,13 +364,19 @@ hipError_t launch_score_topb(const void* K, const void* V, const void* Q, int G,
 hipError_t launch_score(const void* K, const void* Q, int G, const Layout& lay, float* s_out,
                         hipStream_t st) {
   // the logits of a head (G x n floats) wait in LDS
-  if (lay.dtype == DT_BF16 && G <= 32 && static_cast<long long>(G) * lay.n <= (G <= 8 ? 24576 : 31488)) {
+  const bool fits = static_cast<long long>(G) * lay.n <= (G <= 8 ? 24576 : 31488);
+  // Logits that fill a CU's LDS: one workgroup of sixteen waves per CU still reads K once where score_wide_kernel reads it twice.
+  // Few heads leave CUs idle here, while the other kernel splits a head over several.  Two passes / one, us, 4 queries: 256 heads of 8192
+  // tokens 196 / 101, 448 354 / 180, 128 86 / 68, 112 75 / 67, 96 65 / 67, 32 32 / 67; 256 of 5500 with 7 queries 136 / 72.  (Scores' error against 64
+  // bits, 2-norm, 256 heads of 8192: 3.6e-7 / 1.3e-7.)
+  const bool whole_cu = !fits && lay.n > 4096 && G <= 8 && (G * lay.n + 2 * 16 * 8) * 4 <= 160 * 1024 && 5 * lay.heads > 2 * cu_count();
+  if (lay.dtype == DT_BF16 && G <= 32 && (fits || whole_cu)) {
     const int gq = G <= 8 ? 8 : 32;
     // The logit buffer sets how many workgroups share a CU; when it leaves room for two or fewer, eight waves per
     // workgroup keep as many rows in flight as four waves do with a small buffer.
     const int smem_one = (G * lay.n + 8 * gq) * 4;
     const bool big = 3 * smem_one > 160 * 1024;
-    const int nw = big ? 8 : 4;
+    const int nw = whole_cu ? 16 : (big ? 8 : 4);
     const int smem_m = (G * lay.n + 2 * nw * gq) * 4;
     auto go_m = [&](auto kern) -> hipError_t {
       const hipError_t em = hipFuncSetAttribute(reinterpret_cast<const void*>(kern),
@@ -380,6 +386,7 @@ hipError_t launch_score(const void* K, const void* Q, int G, const Layout& lay, 
                          static_cast<const char*>(K), static_cast<const char*>(Q), G, lay, s_out);
       return hipGetLastError();
     };
+    if (whole_cu) return go_m(&score_mfma_kernel<8, 16>);
     if (big) return gq == 8 ? go_m(&score_mfma_kernel<8, 8>) : go_m(&score_mfma_kernel<32, 8>);
     return gq == 8 ? go_m(&score_mfma_kernel<8, 4>) : go_m(&score_mfma_kernel<32, 4>);
   }

@@ -42,3 +42,19 @@ def test_a_split_without_a_finite_logit_counts_for_nothing(heads, G):
         want = O.score_softmax_mean(K[h].double().numpy(), Q[h].double().numpy())
         assert np.all(want[:2500] == 0) and abs(want.sum() - 1) < 1e-12
         np.testing.assert_allclose(s_out[h].cpu().numpy(), want, rtol=2e-5)
+
+
+# heads above 4096 tokens whose logits fill a CU's LDS: the fewest heads that take one workgroup of sixteen waves, the most
+# logits it holds, and one head and one token more or less (which score_wide_kernel takes)
+@pytest.mark.parametrize("heads,n,G", [(103, 8192, 4), (102, 8192, 4), (103, 5814, 7), (103, 5815, 7), (104, 6145, 4), (104, 5057, 8)])
+def test_scores_of_one_pass_match_the_oracle(heads, n, G):
+    from paper_2605_14292_amd import binding as B
+    g = torch.Generator().manual_seed(n + G)
+    K = torch.randn((heads, n, 128), generator=g).to(torch.bfloat16)
+    Q = torch.randn((heads, G, 128), generator=g).to(torch.bfloat16)
+    s_out = torch.full((heads, n), float("nan"), device="cuda")
+    B.kvr_score(K.cuda(), Q.cuda(), s_out=s_out)
+    torch.cuda.synchronize()
+    for h in {0, heads - 1}:
+        want = O.score_softmax_mean(K[h].double().numpy(), Q[h].double().numpy())
+        np.testing.assert_allclose(s_out[h].cpu().numpy(), want, rtol=2e-5)   # (the bound above)
