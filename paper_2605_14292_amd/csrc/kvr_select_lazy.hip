@@ -134,8 +134,7 @@ __global__ __launch_bounds__(64 * W, (W <= 4 ? 2 : 1)) void select_lazy_kernel(L
   int32_t* wcount = reinterpret_cast<int32_t*>(smem + 80);       // [16]
   int32_t* pool_tok = reinterpret_cast<int32_t*>(smem + 96);     // [P] token of the member, -1 = none
   float* pool_r = smem + 96 + P;
-  float* pool_s = smem + 96 + 2 * P;
-  float* pool_m = smem + 96 + 3 * P;
+  float2* pool_sm = reinterpret_cast<float2*>(smem + 96 + 2 * P);   // score and m of the member
   int32_t* pool_picked = reinterpret_cast<int32_t*>(smem + 96 + 4 * P);
   int32_t* pend_l = reinterpret_cast<int32_t*>(smem + 96 + 5 * P);        // [64] pool slots picked this epoch
   int32_t* order_l = reinterpret_cast<int32_t*>(smem + 96 + 5 * P + 64);
@@ -152,8 +151,12 @@ __global__ __launch_bounds__(64 * W, (W <= 4 ? 2 : 1)) void select_lazy_kernel(L
 
   const int h = blockIdx.x;
   if (a.only_marked && a.idx_sorted[static_cast<long long>(h) * a.b] != -1) return;   // (uniform: a scalar load)
-  const int tid = threadIdx.x, lane = tid & 63;
+  int tid = threadIdx.x, lane = tid & 63;
   const int w = __builtin_amdgcn_readfirstlane(tid >> 6);
+  // What an epoch computes from the lane number is computed where it is used: hoisted out of the epochs, as the compiler would, it takes 20
+  // registers (255 of 256 with eight slots, and then the tables below read without branches spill 32: 1740 -> 1930 us on 2048 heads
+  // of 4096).  With four slots there is room, and the hoisted addresses are worth 1 %.
+  auto fresh_lane = [&]() { asm volatile("" : "+v"(lane), "+v"(tid)); };
   const int n = a.n;
   // the head's own budget: its picks are the first b picks of a run for a.b (the rows of the
   // outputs per head), so the epochs stop there
@@ -168,7 +171,6 @@ __global__ __launch_bounds__(64 * W, (W <= 4 ? 2 : 1)) void select_lazy_kernel(L
   float* lr2 = F32 ? reinterpret_cast<float*>(stage) : norm_x + 64;   // [TPW] inverse norms found in the first pass
   float* lrw = lr_all + w * (TPW + 64);                                 // [TPW] list of tokens to refresh, then their raw maxima
   int32_t* lrw_i = reinterpret_cast<int32_t*>(lrw);
-  const unsigned long long below = (1ull << lane) - 1ull;
 
   // where 16-byte piece p of a pick's row goes in the rows of the picks (without the row's offset)
   auto pick_piece = [](int p) -> int {
@@ -299,9 +301,9 @@ __global__ __launch_bounds__(64 * W, (W <= 4 ? 2 : 1)) void select_lazy_kernel(L
 
     int idle = 0;                                    // epochs in a row without a pick
     while (t < b) {
+      if constexpr (S >= 8) fresh_lane();
       // ================= 1. pool = the best Q fresh unselected tokens of every wave =================
       float g[S];
-      uint32_t key[S];
       // Keys are cut to their leading kbits bits: the pool only has to be a good guess (the
       // race against the outside bound keeps the picks exact), and the search is shorter.
       // When the cut keys cannot tell a wave's best tokens apart the best one may be left outside
@@ -311,20 +313,23 @@ __global__ __launch_bounds__(64 * W, (W <= 4 ? 2 : 1)) void select_lazy_kernel(L
 #pragma unroll
       for (int k = 0; k < S; ++k) {
         g[k] = fmaf(nlam, m[k], s[k]);
-        key[k] = ordered_key(g[k]) >> (32 - kbits);
-        const uint32_t k1 = key[k] + 1u;             // (wraps to 0 for an all-ones key, which only a NaN with full keys has)
+        const uint32_t k1 = (ordered_key(g[k]) >> (32 - kbits)) + 1u;             // (wraps to 0 for an all-ones key, which only a NaN with full keys has)
         ekey[k] = ((fresh >> k) & 1u) ? k1 : 0u;
       }
-      uint32_t tau = 0;                              // largest value with at least Q fresh keys >= it
-      auto at_least_q = [&](uint32_t x) -> bool { return count_slots_ge<S>(ekey, x) >= Q; };
+      uint32_t tau = 0;                              // a value with at least Q fresh keys >= it: one with exactly Q, or the largest one
+      int n_ge = 0;                                  // how many keys the last count found
+      auto at_least_q = [&](uint32_t x) -> bool { n_ge = count_slots_ge<S>(ekey, x); return n_ge >= Q; };
       if (kbits == kLzSelBits && tau_prev != 0) {
-        // the value moves little from one epoch to the next: bracket it from the last one with doubling
-        // steps, then bisect (a third of the counts of the bit-wise search on the benchmark inputs)
+        // the value moves little from one epoch to the next (by 15 to 60 after the third): bracket it from the last one with
+        // doubling steps, then bisect, until a count is exactly Q.  With steps from 1 on, a search to the last bit and the second epoch
+        // bracketed too (30 counts: see below) an epoch took 14 counts; 2048 heads of 4096 tokens 1737 -> 1697 us with what follows, 7168 of 1024
+        // 1796 -> 1758.  (A lower bound from the lanes' maxima and regula falsi: five counts, but 7168 heads of 1024 slower by 2 %.)
         constexpr uint32_t kTop = (1u << kLzSelBits) + 1u;   // no key + 1 reaches this
         uint32_t lo, hi;                             // at_least_q(lo), !at_least_q(hi)
         if (at_least_q(tau_prev)) {
           lo = tau_prev;
-          for (uint32_t d = 1;; d <<= 1) {
+          hi = lo + 1u;
+          for (uint32_t d = 16; n_ge != Q; d <<= 1) {
             hi = lo + d;
             if (hi >= kTop) { hi = kTop; break; }
             if (!at_least_q(hi)) break;
@@ -332,56 +337,54 @@ __global__ __launch_bounds__(64 * W, (W <= 4 ? 2 : 1)) void select_lazy_kernel(L
           }
         } else {
           hi = tau_prev;
-          for (uint32_t d = 1;; d <<= 1) {
+          for (uint32_t d = 16;; d <<= 1) {
             lo = hi > d ? hi - d : 0u;               // (every key is >= 0)
             if (lo == 0u || at_least_q(lo)) break;
             hi = lo;
           }
         }
-        while (hi - lo > 1u) {
+        while (hi - lo > 1u && n_ge != Q) {
           const uint32_t mid = (lo + hi) >> 1;
           if (at_least_q(mid)) lo = mid; else hi = mid;
         }
         tau = lo;
       } else {
-        for (int bit = kbits; bit >= 0; --bit) {
+        for (int bit = kbits; bit >= 0 && n_ge != Q; --bit) {
           if (bit == 32) continue;                   // keys + 1 of full-width keys are searched over 32 bits
           const uint32_t cand = tau | (1u << bit);
           if (at_least_q(cand)) tau = cand;
         }
       }
-      tau_prev = tau;
+      // (the gains change their sign with the first picks: the next epoch's value is nowhere near the first one's)
+      tau_prev = have_r ? tau : 0u;
       if (tau == 0) tau = 1;                         // fewer than Q fresh tokens: all of them join
-      int taken = 0;                                 // members with key > tau come first, ties in token order
-#pragma unroll
-      for (int k = 0; k < S; ++k) taken += __popcll(__ballot(ekey[k] > tau));
-      int need_eq = Q - taken;                       // how many of the key == tau tokens join
-      int rank_base = 0;
       float go[S];                                   // gains (bounds) of the tokens left outside
+      {
+        // members with key > tau, then so many with key == tau, in token order
+        int need_eq = Q - (tau == 0xffffffffu ? 0 : count_slots_ge<S>(ekey, tau + 1u));
+        int rank_base = 0;
 #pragma unroll
-      for (int k = 0; k < S; ++k) {
-        const bool above = ekey[k] > tau, equal = ekey[k] == tau;
-        const unsigned long long eqm = __ballot(equal);
-        const int eq_before = __popcll(eqm & below);
-        const bool in = above || (equal && eq_before < need_eq);
-        const unsigned long long inm = __ballot(in);
-        const int slot = w * Q + kvr_ix_if(in, rank_base + __popcll(inm & below), Q, 101);   // 101: a member's place in the wave's share
-        pslot[k] = in ? slot : -1;
-        if (in) {
-          pool_tok[slot] = tok_of(k) < n ? tok_of(k) : -1;
-          pool_r[slot] = r[k];
-          pool_s[slot] = s[k];
-          pool_m[slot] = m[k];
-          pool_picked[slot] = 0;
+        for (int k = 0; k < S; ++k) {
+          unsigned long long inm = __ballot(ekey[k] >= tau);
+          const unsigned long long eqm = __ballot(ekey[k] == tau);
+          const int eq_in = __popcll(eqm);
+          if (eq_in > need_eq) inm ^= __ballot(__builtin_amdgcn_inverse_ballot_w64(eqm) && lane_rank(eqm) >= need_eq);
+          need_eq -= eq_in < need_eq ? eq_in : need_eq;
+          const bool in = __builtin_amdgcn_inverse_ballot_w64(inm);
+          const int slot = w * Q + kvr_ix_if(in, rank_base + lane_rank(inm), Q, 101);   // 101: a member's place in the wave's share
+          pslot[k] = in ? slot : -1;
+          if (in) {
+            pool_tok[slot] = tok_of(k) < n ? tok_of(k) : -1;
+            pool_r[slot] = r[k];
+            pool_sm[slot] = make_float2(s[k], m[k]);
+          }
+          go[k] = in ? -INFINITY : g[k];
+          rank_base += __popcll(inm);
         }
-        go[k] = in ? -INFINITY : g[k];
-        rank_base += __popcll(inm);
-        const int eq_in = __popcll(eqm);
-        need_eq -= eq_in < need_eq ? eq_in : need_eq;
-      }
-      if (lane >= rank_base && lane < Q) {           // fewer fresh tokens than the wave's share: empty slots
-        const int slot = w * Q + lane;
-        pool_tok[slot] = -1; pool_r[slot] = 0.f; pool_s[slot] = -INFINITY; pool_m[slot] = 0.f; pool_picked[slot] = 0;
+        if (lane >= rank_base && lane < Q) {         // fewer fresh tokens than the wave's share: empty slots
+          const int slot = w * Q + lane;
+          pool_tok[slot] = -1; pool_r[slot] = 0.f; pool_sm[slot] = make_float2(-INFINITY, 0.f);
+        }
       }
       float gout, gmax_w; int jout_f;
       wg_argmax(go, gout, jout_f, gmax_w);           // barrier inside: the pool tables are complete
@@ -394,6 +397,7 @@ __global__ __launch_bounds__(64 * W, (W <= 4 ? 2 : 1)) void select_lazy_kernel(L
       constexpr int kGat = P * LPR / NT;         // rows per thread
       constexpr int kGatRows = NT / LPR;         // rows per round
       const int gat_row = tid / LPR, gat_piece = tid % LPR;
+      for (int u = tid; u < P; u += NT) pool_picked[u] = 0;
       uint4 x[kGat];
 #pragma unroll
       for (int k = 0; k < kGat; ++k) {
@@ -443,19 +447,18 @@ __global__ __launch_bounds__(64 * W, (W <= 4 ? 2 : 1)) void select_lazy_kernel(L
             delta = -1.f;
           }
         }
+        // (go is -inf for pool members and dead tokens.  With a token at +inf outside, a distance from the best one is inf - inf and
+        // thr_r a NaN: every token is listed then, or those at +inf would stay stale and could never be picked)
+        unsigned long long mem[S];
+        masks_ge<S>(go, thr_r >= -3.402823466e38f ? thr_r : -3.402823466e38f, mem);
         int off = 0;
 #pragma unroll
         for (int k = 0; k < S; ++k) {
-          // (go is -inf for pool members and dead tokens.  With a token at +inf outside, a distance from the best one is inf - inf and
-          // thr_r a NaN: every token is listed then, or those at +inf would stay stale and could never be picked)
-          const bool mem = !(go[k] < thr_r) && go[k] > -INFINITY;
-          const unsigned long long mm = __ballot(mem);
-          if (mem) {
-            const int pos = kvr_ix(off + __popcll(mm & below), TPW, 102);   // 102: position in the refresh list
-            lrw_i[pos] = tok_of(k);
-            pslot[k] = -2 - pos;
-          }
-          off += __popcll(mm);
+          const bool in = __builtin_amdgcn_inverse_ballot_w64(mem[k]);
+          const int pos = kvr_ix_if(in, off + lane_rank(mem[k]), TPW, 102);   // 102: position in the refresh list
+          if (in) lrw_i[pos] = tok_of(k);
+          pslot[k] = in ? -2 - pos : pslot[k];
+          off += __popcll(mem[k]);
         }
         cnt_r = off;
         // pad to a multiple of 64 with a valid row (its results are never read)
@@ -564,8 +567,9 @@ __global__ __launch_bounds__(64 * W, (W <= 4 ? 2 : 1)) void select_lazy_kernel(L
 #pragma unroll
         for (int q = 0; q < NQ; ++q) {
           const int p = lane + 64 * q;
-          sq[q] = pool_s[p];
-          mq[q] = pool_m[p];
+          const float2 sm = pool_sm[p];
+          sq[q] = sm.x;
+          mq[q] = sm.y;
           tja[q] = padded_row_start(p) * 4 + tri0;         // start of the slot's row
         }
         const int jb = __builtin_amdgcn_readfirstlane(jout < 0 ? 0x7fffffff : jout);
@@ -588,7 +592,7 @@ __global__ __launch_bounds__(64 * W, (W <= 4 ? 2 : 1)) void select_lazy_kernel(L
         }
         rec_i >>= 2;
 #pragma unroll
-        for (int q = 0; q < NQ; ++q) pool_m[lane + 64 * q] = mq[q];   // the pool's m is authoritative
+        for (int q = 0; q < NQ; ++q) pool_sm[lane + 64 * q].y = mq[q];   // the pool's m is authoritative
         if (lane < np) {
           const int ri = kvr_ix(rec_i, P, 106);          // 106: pool slot of a pick
           const int tp = kvr_ix(t + lane, kLzMaxB, 107); // 107: number of a pick
@@ -605,11 +609,18 @@ __global__ __launch_bounds__(64 * W, (W <= 4 ? 2 : 1)) void select_lazy_kernel(L
       // pool members: m from the race (it covers every pick so far), picked members leave
 #pragma unroll
       for (int k = 0; k < S; ++k) {
-        const int ps = pslot[k];
-        if (ps >= 0) {
-          m[k] = pool_m[ps];
-          if (!have_r) r[k] = pool_r[ps];
-          if (pool_picked[ps]) s[k] = -INFINITY;
+        const bool in = pslot[k] >= 0;
+        const int ps = in ? pslot[k] : 0;            // (read in any case: no branch between the reads)
+        const float mp = pool_sm[ps].y;
+        const bool gone = in && pool_picked[ps] != 0;
+        m[k] = in ? mp : m[k];
+        s[k] = gone ? -INFINITY : s[k];
+      }
+      if (!have_r) {
+#pragma unroll
+        for (int k = 0; k < S; ++k) {
+          const float rp = pool_r[pslot[k] >= 0 ? pslot[k] : 0];
+          r[k] = pslot[k] >= 0 ? rp : r[k];
         }
       }
       if (t >= b) break;
@@ -804,13 +815,12 @@ __global__ __launch_bounds__(64 * W, (W <= 4 ? 2 : 1)) void select_lazy_kernel(L
         uint32_t now = 0;
 #pragma unroll
         for (int k = 0; k < S; ++k) {
-          const int ps = pslot[k];
-          if (ps <= -2) {
-            const int pos = kvr_ix(-2 - ps, TPW, 111);   // 111: list position of a refreshed token
-            if (!have_r) r[k] = lr2[pos];
-            m[k] = hw_max(m[k], lrw[pos] * r[k]);
-          }
-          if (ps != -1) now |= 1u << k;              // pool members left the race up to date
+          const bool listed = pslot[k] <= -2;
+          const int pos = kvr_ix_if(listed, listed ? -2 - pslot[k] : 0, TPW, 111);   // 111: list position of a refreshed token (others read what is there: no branch between the reads)
+          const float mx = lrw[pos];
+          if (!have_r) { const float rx = lr2[pos]; r[k] = listed ? rx : r[k]; }
+          m[k] = listed ? hw_max(m[k], mx * r[k]) : m[k];
+          now |= pslot[k] != -1 ? 1u << k : 0u;      // pool members left the race up to date
           pslot[k] = -1;
         }
         fresh = np > 0 ? now : (fresh | now);
@@ -852,7 +862,7 @@ __global__ __launch_bounds__(64 * W, (W <= 4 ? 2 : 1)) void select_lazy_kernel(L
 #pragma unroll
     for (int k = 0; k < S; ++k) {
       if ((sel[k] >> lane) & 1ull) {
-        const int rank = off + __popcll(sel[k] & below);
+        const int rank = off + lane_rank(sel[k]);
         if (rank < b) idxs_l[rank] = tok_of(k);
       }
       off += __popcll(sel[k]);
