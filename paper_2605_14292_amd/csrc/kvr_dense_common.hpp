@@ -222,6 +222,19 @@ __device__ __forceinline__ void half_sums_at_31(float (&v)[4]) {
 #undef KVR_SUM4
 }
 
+// likewise half_max_at_31
+__device__ __forceinline__ void half_maxes_at_31(float (&v)[4]) {
+#define KVR_MAX4(ctrl, rmask)                                                        \
+  "v_max_f32_dpp %0, %0, %0 " ctrl " row_mask:" rmask " bank_mask:0xf\n\t"           \
+  "v_max_f32_dpp %1, %1, %1 " ctrl " row_mask:" rmask " bank_mask:0xf\n\t"           \
+  "v_max_f32_dpp %2, %2, %2 " ctrl " row_mask:" rmask " bank_mask:0xf\n\t"           \
+  "v_max_f32_dpp %3, %3, %3 " ctrl " row_mask:" rmask " bank_mask:0xf\n\t"
+  asm("s_nop 1\n\t" KVR_MAX4("row_shr:1", "0xf") KVR_MAX4("row_shr:2", "0xf") KVR_MAX4("row_shr:4", "0xf")
+      KVR_MAX4("row_shr:8", "0xf") KVR_MAX4("row_bcast:15", "0xa") "s_nop 1"
+      : "+v"(v[0]), "+v"(v[1]), "+v"(v[2]), "+v"(v[3]));
+#undef KVR_MAX4
+}
+
 typedef __attribute__((ext_vector_type(4))) float f32x4;
 
 // A cosine triangle whose row i (columns 0..i) takes (i + 4) & ~3 floats, so that four neighbouring columns of a row are
@@ -303,6 +316,38 @@ __device__ __forceinline__ void write_cos_tile(float* tri, const float* rinv, co
       }
       off += 8 * i + 36;
       i += 8;
+    }
+  }
+}
+
+// The same into the packed triangle from the other orientation (column block J as operand A, row block I as operand B: lane (row = lane &
+// 31, hf) holds columns 8R + 4hf .. + 3 of its row).  A lane's addresses are then one base and constants, two neighbouring columns a
+// store; with one store and one address per element a tile costs the LDS pipe and the vector unit half as much again.
+__device__ __forceinline__ void write_cos_tile_rows(float* tri, const float* rinv, const f32x16& acc, int I, int J, int lane) {
+  const int hf = lane >> 5;
+  const int row = I * 32 + (lane & 31);
+  const float rrow = rinv[row];
+  float4 rc[4];                                       // the columns' inverse norms, all requested before the first use
+#pragma unroll
+  for (int R = 0; R < 4; ++R) rc[R] = *reinterpret_cast<const float4*>(rinv + J * 32 + 8 * R + 4 * hf);
+  float* dst = tri + row * (row + 1) / 2 + J * 32 + 4 * hf;
+  if (I != J) {
+#pragma unroll
+    for (int R = 0; R < 4; ++R) {
+      dst[8 * R] = acc[4 * R] * rrow * rc[R].x;
+      dst[8 * R + 1] = acc[4 * R + 1] * rrow * rc[R].y;
+      dst[8 * R + 2] = acc[4 * R + 2] * rrow * rc[R].z;
+      dst[8 * R + 3] = acc[4 * R + 3] * rrow * rc[R].w;
+    }
+  } else {
+    const int last = (lane & 31) - 4 * hf;            // the row's diagonal element, counted from dst
+#pragma unroll
+    for (int R = 0; R < 4; ++R) {
+      const float v[4] = {acc[4 * R] * rrow * rc[R].x, acc[4 * R + 1] * rrow * rc[R].y,
+                          acc[4 * R + 2] * rrow * rc[R].z, acc[4 * R + 3] * rrow * rc[R].w};
+#pragma unroll
+      for (int q = 0; q < 4; ++q)
+        if (8 * R + q <= last) dst[8 * R + q] = 8 * R + q == last ? INFINITY : v[q];
     }
   }
 }

@@ -3,8 +3,17 @@
 // workgroup gets a CU to itself (a decode-time event of one sequence: layers x KV heads <= CUs).
 // Throughput is then the latency of one head, so the parallel phases -- rows, logits, Gram,
 // cosine triangle, outputs -- are spread over sixteen wave64s instead of four; the b dependent
-// picks stay on one wave.  Same arithmetic, same LDS layout and same helpers as
+// picks stay on one wave.  Same arithmetic and same helpers as
 // retain_dense_kernel, which remains the kernel for batched calls (several heads per CU).
+//
+// What is not the chain is a row of latencies, so it is cut where it can be.  Both tensors and the queries are requested at once and staged
+// side by side (the triangle takes their place).  Waves 0-3 work out the scores while waves 4-15 run the Gram, two row blocks
+// by two column blocks each, so that an operand read from LDS meets two others (one tile at a time the Gram was bound by its LDS
+// reads); the second half of the softmax runs beside the writing of the triangle.  The triangle is the packed one: in padded rows
+// (16-byte stores) it is written as fast, but a pick reads its columns with bank conflicts (24 cycles of 302).
+// 112 heads, n = 256, b = 128, cycles of a head: rows in LDS 4 500, Gram until 8 400, triangle until 12 900, picks until 51 600,
+// outputs until 57 500.  Before, with K staged first, then the scores, V and the Gram: chain from 20 200 on, 65 300 in all; the call 29.4 -> 26.5 us,
+// n = 192, b = 64 17.8 -> 15.7.
 #include "kvr_dense_common.hpp"
 #include "kvr_kernels.hpp"
 
@@ -14,9 +23,16 @@ constexpr int kD16Threads = 1024;
 constexpr int kD16Waves = kD16Threads / 64;
 constexpr int kD16MaxB = 256;
 
+constexpr int kD16MaxG = 8;
+
+// staged rows of V, then of K; the triangle takes their place | s_l[N32] | rinv[N32] | max [8 queries][4], sum [8][8] |
+// queries [8][272 B] | met [4] | idx_l | order_l | gain_l
+__host__ __device__ constexpr int dense16_area(int NT) {
+  const int rows = 2 * NT * 32 * kRowPitch, tri = dense_tri_floats(NT) * 4;
+  return rows > tri ? rows : tri;
+}
 __host__ __device__ constexpr int dense16_smem_bytes(int NT) {
-  // region A | s_l[N32] | rinv[N32] | red[2][16][8] | idx_l | order_l | gain_l
-  return dense_region_a(NT) + NT * 32 * 4 * 2 + 2 * kD16Waves * 8 * 4 + kD16MaxB * 4 * 3;
+  return dense16_area(NT) + NT * 32 * 4 * 2 + 2 * kD16MaxG * 8 * 4 + kD16MaxG * kRowPitch + 16 + kD16MaxB * 4 * 3;
 }
 
 struct Dense16Args {
@@ -33,20 +49,23 @@ template <int NT>
 __global__ __launch_bounds__(kD16Threads, 1) void retain_dense16_kernel(Dense16Args a) {
   constexpr int N32 = NT * 32;
   constexpr int NQ = NT / 2;
-  constexpr int NTILES = NT * (NT + 1) / 2;
-  constexpr int MAXT = (NTILES + kD16Waves - 1) / kD16Waves;
+  constexpr int UNITS = NT / 2 * (NT / 2 + 1) / 2;    // pairs of row blocks by pairs of column blocks in the lower triangle
   constexpr int kIters = N32 * 16 / kD16Threads;      // 16-byte pieces of the head's rows per thread
+  static_assert(NT % 2 == 0 && NT >= 4 && UNITS <= kD16Waves - 4, "a wave per unit");
   extern __shared__ __align__(16) char smem[];
-  char* stage = smem;                                // staged rows ...
-  float* tri = reinterpret_cast<float*>(smem);       // ... later the packed cosine triangle
-  float* s_l = reinterpret_cast<float*>(smem + dense_region_a(NT));
+  char* stage = smem;                                // staged rows of V ...
+  char* stage_k = smem + N32 * kRowPitch;            // ... and of K
+  float* tri = reinterpret_cast<float*>(smem);       // ... later the cosine triangle
+  float* s_l = reinterpret_cast<float*>(smem + dense16_area(NT));
   float* rinv = s_l + N32;
-  float* red = rinv + N32;                           // [2][16 waves][8 queries]
-  int32_t* idx_l = reinterpret_cast<int32_t*>(red + 2 * kD16Waves * 8);
+  float* red = rinv + N32;                           // maxima [8 queries][4 waves], sums [8 queries][8 blocks]
+  char* stage_q = reinterpret_cast<char*>(red + 2 * kD16MaxG * 8);
+  int32_t* met = reinterpret_cast<int32_t*>(stage_q + kD16MaxG * kRowPitch);   // [4] waves that have their maxima
+  int32_t* idx_l = met + 4;
   int32_t* order_l = idx_l + kD16MaxB;
   float* gain_l = reinterpret_cast<float*>(order_l + kD16MaxB);
 
-  const int tid = threadIdx.x, lane = tid & 63, hf = lane >> 5;
+  const int tid = threadIdx.x, lane = tid & 63, hf = lane >> 5, l32 = lane & 31;
   const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
   const int h = blockIdx.x;
   const int n = a.n, b = a.b;
@@ -56,137 +75,164 @@ __global__ __launch_bounds__(kD16Threads, 1) void retain_dense16_kernel(Dense16A
   const long long head_off = h * a.stride_head * 2;   // bytes
   const int chunk = tid & 15, r0 = tid >> 4;          // 64 rows per step of the row loops
 
-  // both tensors start their trip from memory at once; rows past n read as zero
-  uint4 vreg[kIters], kreg[kIters];
+  // everything starts its trip from memory at once; rows past n are the last one again (never picked).  (Vector types, not the
+  // struct uint4: the arrays of those ended up in scratch memory)
+  {
+    typedef __attribute__((ext_vector_type(4))) uint32_t u32x4;
+    const long long tok_bytes = a.stride_tok * 2, off = head_off + chunk * 16;
+    u32x4 kreg[kIters], vreg[kIters], q = {0u, 0u, 0u, 0u};
+    if (tid < 4) met[tid] = 0;
+    if (a.Q) {
 #pragma unroll
-  for (int k = 0; k < kIters; ++k) {
-    const int row = r0 + 64 * k;
-    vreg[k] = kreg[k] = make_uint4(0u, 0u, 0u, 0u);
-    if (row < n) {
-      const long long off = head_off + (row * a.stride_tok + chunk * 8) * 2;
-      if (a.Q) kreg[k] = *reinterpret_cast<const uint4*>(a.K + off);
-      if (need_v) vreg[k] = *reinterpret_cast<const uint4*>(a.V + off);
+      for (int k = 0; k < kIters; ++k) kreg[k] = *reinterpret_cast<const u32x4*>(a.K + off + min(r0 + 64 * k, n - 1) * tok_bytes);
+      // (rows past G are the last query again; their results are not used)
+      if (wave < 2) q = *reinterpret_cast<const u32x4*>(a.Q + (static_cast<long long>(h) * a.G + min(r0, a.G - 1)) * kD * 2 + chunk * 16);
+    }
+    if (need_v) {
+#pragma unroll
+      for (int k = 0; k < kIters; ++k) vreg[k] = *reinterpret_cast<const u32x4*>(a.V + off + min(r0 + 64 * k, n - 1) * tok_bytes);
+    }
+    if (a.Q) {
+#pragma unroll
+      for (int k = 0; k < kIters; ++k) *reinterpret_cast<u32x4*>(stage_k + (r0 + 64 * k) * kRowPitch + chunk * 16) = kreg[k];
+      if (wave < 2) *reinterpret_cast<u32x4*>(stage_q + r0 * kRowPitch + chunk * 16) = q;
+    } else if (tid < N32) {
+      s_l[tid] = tid < n ? a.s_in[static_cast<long long>(h) * n + tid] : -INFINITY;
+    }
+    if (need_v) {
+#pragma unroll
+      for (int k = 0; k < kIters; ++k) *reinterpret_cast<u32x4*>(stage + (r0 + 64 * k) * kRowPitch + chunk * 16) = vreg[k];
     }
   }
+  lds_barrier();
 
-  // ---------------------------------------------------------------- scores
-  if (a.Q) {
-#pragma unroll
-    for (int k = 0; k < kIters; ++k)
-      *reinterpret_cast<uint4*>(stage + (r0 + 64 * k) * kRowPitch + chunk * 16) = kreg[k];
-    bf16x8 qf[8];
-    {
-      const int g = lane & 31;
-      const char* qp = a.Q + (static_cast<long long>(h) * a.G + g) * kD * 2 + hf * 16;
-#pragma unroll
-      for (int ks = 0; ks < 8; ++ks) {
-        uint4 w = make_uint4(0u, 0u, 0u, 0u);
-        if (g < a.G && wave < NT) w = *reinterpret_cast<const uint4*>(qp + ks * 32);
-        qf[ks] = *reinterpret_cast<bf16x8*>(&w);
+  if (wave >= 4) {
+    // ------------------------------------------------ Gram -> packed cosines: waves 4-15, a pair of row blocks by a pair of column blocks each
+    if (need_v && wave - 4 < UNITS) {
+      int P = wave - 4, Q = P;                        // the pairs on the diagonal first (two diagonal tiles and the one between them)
+      if (P >= NT / 2) {
+        const int o = P - NT / 2;
+        P = 1;
+        while (P * (P + 1) / 2 <= o) ++P;
+        Q = o - P * (P - 1) / 2;
       }
-    }
-    lds_barrier();
-    // wave I < NT takes token block I: lane (token, hf) ends up with the logits of queries hf*4 .. hf*4+3
-    const bool has_block = wave < NT;
-    const bool live = has_block && (wave * 32 + (lane & 31)) < n;
-    const float scale = 0.08838834764831845f;      // 1/sqrt(128)
-    float z[4];
-    {
-      f32x16 acc = {0};
-      if (has_block) {
+      // Four operands from LDS make four tiles.  (One tile at a time the Gram was bound by the LDS: 16 reads a tile.)
+      f32x16 t00 = {0}, t01 = {0}, t10 = {0}, t11 = {0};   // tile (2P + first, 2Q + second)
+      if (P == Q) {
 #pragma unroll
-        for (int ks = 0; ks < 8; ++ks)
-          acc = __builtin_amdgcn_mfma_f32_32x32x16_bf16(qf[ks], frag_at(stage, wave, ks, lane), acc, 0, 0, 0);
-      }
+        for (int ks = 0; ks < 8; ++ks) {
+          const bf16x8 i0 = frag_at(stage, 2 * P, ks, lane), i1 = frag_at(stage, 2 * P + 1, ks, lane);
+          t00 = __builtin_amdgcn_mfma_f32_32x32x16_bf16(i0, i0, t00, 0, 0, 0);
+          t11 = __builtin_amdgcn_mfma_f32_32x32x16_bf16(i1, i1, t11, 0, 0, 0);
+          t10 = __builtin_amdgcn_mfma_f32_32x32x16_bf16(i0, i1, t10, 0, 0, 0);
+        }
+        // squared norms: element r of lane (l32, hf) is column 8 (r / 4) + 4 hf + r % 4 of the tile, so row l32's own sits in one of its two lanes
+        auto norms = [&](const f32x16& t, int block) {
+          auto pick = [](int bit, float one, float zero) { return bit ? one : zero; };
+          float v8[8], v4[4];
 #pragma unroll
-      for (int r = 0; r < 4; ++r) z[r] = live ? acc[r] * scale : -INFINITY;
-    }
+          for (int k = 0; k < 8; ++k) v8[k] = pick(l32 & 1, t[2 * k + 1], t[2 * k]);
 #pragma unroll
-    for (int r = 0; r < 4; ++r) {
-      const float v = half_max_at_31(z[r]);
-      if ((lane & 31) == 31) red[wave * 8 + hf * 4 + r] = v;
-    }
-    lds_barrier();
-    float zmax[4], zsum[4];
+          for (int k = 0; k < 4; ++k) v4[k] = pick(l32 & 2, v8[2 * k + 1], v8[2 * k]);
+          const float ss = pick(l32 & 16, pick(l32 & 8, v4[3], v4[2]), pick(l32 & 8, v4[1], v4[0]));
+          if (((l32 >> 2) & 1) == hf) rinv[block * 32 + l32] = 1.0f / (sqrtf(ss) + a.eps);
+        };
+        norms(t00, 2 * P);
+        norms(t11, 2 * P + 1);
+      } else {
 #pragma unroll
-    for (int r = 0; r < 4; ++r) {
-      const int g = hf * 4 + r;
-      float m = red[g];
-#pragma unroll
-      for (int u = 1; u < NT; ++u) m = fmaxf(m, red[u * 8 + g]);
-      zmax[r] = m;
-      z[r] = __expf(z[r] - zmax[r]);                 // exp(-inf) = 0 for padded tokens
-      zsum[r] = z[r];
-    }
-#pragma unroll
-    for (int r = 0; r < 4; ++r) {
-      const float v = half_sum_at_31(zsum[r]);
-      if ((lane & 31) == 31) red[kD16Waves * 8 + wave * 8 + hf * 4 + r] = v;
-    }
-    lds_barrier();
-    const float invG = 1.0f / static_cast<float>(a.G);
-    float p = 0.f;
-#pragma unroll
-    for (int r = 0; r < 4; ++r) {
-      const int g = hf * 4 + r;
-      float tot = 0.f;
-#pragma unroll
-      for (int u = 0; u < NT; ++u) tot += red[kD16Waves * 8 + u * 8 + g];
-      p = fmaf(z[r], g < a.G ? invG / tot : 0.f, p);
-    }
-    p += __shfl_xor(p, 32, kWave);                 // queries 0-3 live in lanes 0-31, 4-7 in 32-63
-    if (has_block && hf == 0) {
-      const int j = wave * 32 + (lane & 31);
-      s_l[j] = j < n ? p : -INFINITY;               // padding never competes
-      if (j < n && a.s_out) a.s_out[static_cast<long long>(h) * n + j] = p;
-    }
-    lds_barrier();                                // K fragments are dead; s_l is complete
-  } else {
-    if (tid < N32) s_l[tid] = tid < n ? a.s_in[static_cast<long long>(h) * n + tid] : -INFINITY;
-  }
-
-  // ------------------------------------------------ Gram -> packed cosines
-  if (need_v) {
-#pragma unroll
-    for (int k = 0; k < kIters; ++k)
-      *reinterpret_cast<uint4*>(stage + (r0 + 64 * k) * kRowPitch + chunk * 16) = vreg[k];
-    lds_barrier();
-    // tile t of the lower triangle: row block I, column block J <= I; wave w takes tiles w, w + 16, ...
-    f32x16 acc[MAXT];
-#pragma unroll
-    for (int sl = 0; sl < MAXT; ++sl) {
-      const int tile = wave + kD16Waves * sl;
-      acc[sl] = f32x16{0};
-      if (tile < NTILES) {
-        int I = 0;
-        while ((I + 1) * (I + 2) / 2 <= tile) ++I;
-        const int J = tile - I * (I + 1) / 2;
-#pragma unroll
-        for (int ks = 0; ks < 8; ++ks)
-          acc[sl] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(frag_at(stage, I, ks, lane), frag_at(stage, J, ks, lane),
-                                                            acc[sl], 0, 0, 0);
-        if (I == J) {                               // squared norms sit on the diagonal
-#pragma unroll
-          for (int r = 0; r < 16; ++r) {
-            const int il = (r >> 2) * 8 + hf * 4 + (r & 3);
-            if (il == (lane & 31)) rinv[I * 32 + il] = acc[sl][r];
-          }
+        for (int ks = 0; ks < 8; ++ks) {
+          const bf16x8 i0 = frag_at(stage, 2 * P, ks, lane), i1 = frag_at(stage, 2 * P + 1, ks, lane);
+          const bf16x8 j0 = frag_at(stage, 2 * Q, ks, lane), j1 = frag_at(stage, 2 * Q + 1, ks, lane);
+          t00 = __builtin_amdgcn_mfma_f32_32x32x16_bf16(j0, i0, t00, 0, 0, 0);
+          t01 = __builtin_amdgcn_mfma_f32_32x32x16_bf16(j1, i0, t01, 0, 0, 0);
+          t10 = __builtin_amdgcn_mfma_f32_32x32x16_bf16(j0, i1, t10, 0, 0, 0);
+          t11 = __builtin_amdgcn_mfma_f32_32x32x16_bf16(j1, i1, t11, 0, 0, 0);
         }
       }
+      lds_barrier();                                  // staged rows are dead from here on, the norms complete
+      write_cos_tile_rows(tri, rinv, t00, 2 * P, 2 * Q, lane);
+      write_cos_tile_rows(tri, rinv, t10, 2 * P + 1, 2 * Q, lane);
+      write_cos_tile_rows(tri, rinv, t11, 2 * P + 1, 2 * Q + 1, lane);
+      if (P != Q) write_cos_tile_rows(tri, rinv, t01, 2 * P, 2 * Q + 1, lane);
+    } else {
+      lds_barrier();
     }
-    lds_barrier();                                // staged rows are dead from here on
-    if (tid < N32) rinv[tid] = 1.0f / (sqrtf(rinv[tid]) + a.eps);
-    lds_barrier();
+  } else {
+    // ---------------------------------------------------------------- scores: wave w takes the token blocks w and w + 4
+    if (a.Q) {
+      __builtin_amdgcn_s_setprio(2);                  // (ahead of the tiles of the waves on the same SIMD)
+      const float scale = 0.08838834764831845f;      // 1/sqrt(128)
+      float z[2][4];                                  // lane (token, hf): the logits of queries hf*4 .. hf*4+3
+      {
+        f32x16 d0 = {0}, d1 = {0};
+        const int second = wave + 4 < NT ? wave + 4 : wave;   // (no second block: the first again, its logits are -inf)
 #pragma unroll
-    for (int sl = 0; sl < MAXT; ++sl) {
-      const int tile = wave + kD16Waves * sl;
-      if (tile < NTILES) {
-        int I = 0;
-        while ((I + 1) * (I + 2) / 2 <= tile) ++I;
-        const int J = tile - I * (I + 1) / 2;
-        write_cos_tile(tri, rinv, acc[sl], I, J, lane);
+        for (int ks = 0; ks < 8; ++ks) {
+          const bf16x8 q = *reinterpret_cast<const bf16x8*>(stage_q + min(l32, kD16MaxG - 1) * kRowPitch + ks * 32 + hf * 16);
+          d0 = __builtin_amdgcn_mfma_f32_32x32x16_bf16(q, frag_at(stage_k, wave, ks, lane), d0, 0, 0, 0);
+          d1 = __builtin_amdgcn_mfma_f32_32x32x16_bf16(q, frag_at(stage_k, second, ks, lane), d1, 0, 0, 0);
+        }
+        const bool live0 = wave * 32 + l32 < n, live1 = wave + 4 < NT && wave * 32 + 128 + l32 < n;
+#pragma unroll
+        for (int r = 0; r < 4; ++r) { z[0][r] = live0 ? d0[r] * scale : -INFINITY; z[1][r] = live1 ? d1[r] * scale : -INFINITY; }
+      }
+      {
+        float v[4];
+#pragma unroll
+        for (int r = 0; r < 4; ++r) v[r] = hw_max(z[0][r], z[1][r]);
+        half_maxes_at_31(v);
+#pragma unroll
+        for (int r = 0; r < 4; ++r)
+          if (l32 == 31) red[(hf * 4 + r) * 4 + wave] = v[r];
+      }
+      // This exchange is among the four waves only (a barrier would wait for the tiles of the others): each adds itself to a counter and
+      // waits until all four have.  (None of them waits for anything in between.)
+      asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");
+      if (lane == 0) __hip_atomic_fetch_add(met, 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
+      while (__hip_atomic_load(met, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP) < 4) {}
+      asm volatile("" ::: "memory");
+#pragma unroll
+      for (int r = 0; r < 4; ++r) {
+        const float4 x = *reinterpret_cast<const float4*>(red + (hf * 4 + r) * 4);
+        const float zmax = fmaxf(fmaxf(x.x, x.y), fmaxf(x.z, x.w));
+        z[0][r] = __expf(z[0][r] - zmax);             // exp(-inf) = 0 for padded tokens
+        z[1][r] = __expf(z[1][r] - zmax);
+      }
+#pragma unroll
+      for (int u = 0; u < 2; ++u) {
+        float v[4] = {z[u][0], z[u][1], z[u][2], z[u][3]};
+        half_sums_at_31(v);
+#pragma unroll
+        for (int r = 0; r < 4; ++r)
+          if (l32 == 31) red[kD16MaxG * 4 + (hf * 4 + r) * 8 + wave + 4 * u] = v[r];
+      }
+      __builtin_amdgcn_s_setprio(0);
+      lds_barrier();                                  // the sums are there; staged rows are dead
+      const float invG = 1.0f / static_cast<float>(a.G);
+      float p[2] = {0.f, 0.f};
+#pragma unroll
+      for (int r = 0; r < 4; ++r) {
+        const float* rs = red + kD16MaxG * 4 + (hf * 4 + r) * 8;
+        const float4 x = *reinterpret_cast<const float4*>(rs), y = *reinterpret_cast<const float4*>(rs + 4);
+        const float v[8] = {x.x, x.y, x.z, x.w, y.x, y.y, y.z, y.w};
+        float tot = 0.f;                              // (the blocks' sums in their order)
+#pragma unroll
+        for (int u = 0; u < NT; ++u) tot += v[u];
+        const float wt = hf * 4 + r < a.G ? invG / tot : 0.f;
+        p[0] = fmaf(z[0][r], wt, p[0]);
+        p[1] = fmaf(z[1][r], wt, p[1]);
+      }
+      p[0] += __shfl_xor(p[0], 32, kWave);           // queries 0-3 live in lanes 0-31, 4-7 in 32-63
+      p[1] += __shfl_xor(p[1], 32, kWave);
+      const int j = wave * 32 + l32 + 128 * hf;       // lane (token, hf) stores the token of block wave + 4 hf
+      const float pj = hf ? p[1] : p[0];
+      if (j < N32) {
+        s_l[j] = j < n ? pj : -INFINITY;              // padding never competes
+        if (j < n && a.s_out) a.s_out[static_cast<long long>(h) * n + j] = pj;
       }
     }
+    if (!a.Q) lds_barrier();
   }
   lds_barrier();
 
