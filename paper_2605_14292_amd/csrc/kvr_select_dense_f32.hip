@@ -3,12 +3,15 @@
 // bf16 numbers, and fp32 caches.  One workgroup of sixteen wave64s per head (such launches have
 // few heads, so the latency of one head is what counts):
 //
-//   rows     staged in LDS as fp32, 132-float pitch (16-byte aligned rows; eight consecutive rows
-//            cover the 32 banks with their 16-byte pieces)
-//   Gram     lower-triangular 32x32 tiles on the fp32 MFMA (32x32x2, fp32 products and sums).  Which
-//            two of the 128 k an MFMA multiplies is free as long as both operands agree: MFMA m
-//            takes k = m for the lower half-wave and k = 64 + m for the upper one, so a lane reads
-//            64 consecutive floats of its row, four per LDS request
+//   rows     staged in LDS as fp32, 132-float pitch (16-byte aligned rows; sixteen consecutive rows
+//            cover the banks with their 16-byte pieces)
+//   Gram     lower-triangular 16x16 tiles on the fp32 MFMA (16x16x4, fp32 products and sums, one after the other in the order of
+//            the lanes' four k-groups).  The sums run over k = 0, 64, 1, 65, ..: MFMA t takes k = 2t, 64 + 2t, 2t + 1, 65 + 2t,
+//            and the rows are staged in the order [k / 64][k % 2][k % 64 / 2], so that a lane reads 32 consecutive floats of
+//            its row.  (32x32x2 MFMAs give the same bits at the same rate, but their tiles hold more of the upper triangle
+//            and 21 of them do not divide by four SIMDs: n = 192, 24 600 cycles at best, 20 000 now.  One head, n = 192, b = 64
+//            27.9 -> 25.2 us with the triangle's stores from one base address and the score bound's search only where it can
+//            drop a token; 32 heads of 130, b = 40 25.1 -> 22.3; n = 256, b = 128 44.6 -> 43.7)
 //   norms    r_j = 1/(||V_j|| + eps) from the Gram diagonal              (Eq. 1)
 //   cosines  packed fp32 triangle in the space the rows were staged in   (Algorithm 1, Sims)
 //   greedy   the single-wave pick loop of the bf16 kernels                (Eq. 2-3)
@@ -50,7 +53,7 @@ template <int NT>
 __global__ __launch_bounds__(kF32Threads, 1) void select_dense_f32_kernel(F32Args a) {
   constexpr int N32 = NT * 32;
   constexpr int NQ = NT / 2;
-  constexpr int NTILES = NT * (NT + 1) / 2;
+  constexpr int NTILES = NT * (2 * NT + 1);           // 16x16 tiles of the lower triangle
   constexpr int MAXT = (NTILES + kF32Waves - 1) / kF32Waves;
   extern __shared__ __align__(16) char smem[];
   float* stage = reinterpret_cast<float*>(smem);
@@ -137,8 +140,7 @@ __global__ __launch_bounds__(kF32Threads, 1) void select_dense_f32_kernel(F32Arg
     if (tid < N32) s_l[tid] = tid < n ? a.s[static_cast<long long>(h) * n + tid] : -INFINITY;
   }
   if (tid == 0) meta[0] = 0;
-  typedef __attribute__((ext_vector_type(16))) float f32x16_t;
-  f32x16_t acc[MAXT];
+  f32x4 acc[MAXT];
   int ns = 0;                                       // size of the reduced problem, 0 = all n tokens
   if (diverse) {
     // Exact candidate reduction for heads of more than 128 tokens: a token with s_j < s_(b) - lambda
@@ -156,9 +158,17 @@ __global__ __launch_bounds__(kF32Threads, 1) void select_dense_f32_kernel(F32Arg
           sv[q] = s_l[lane + 64 * q];
           key[q] = lane + 64 * q < n ? ordered_key(sv[q] + 0.0f) : 0u;
         }
+        // (nothing can go when the finite scores spread by no more than lambda: softmax means always do)
+        float hi = -INFINITY, lo = INFINITY;
+#pragma unroll
+        for (int q = 0; q < NQ; ++q)
+          if (sv[q] > -INFINITY && sv[q] < INFINITY) { hi = hw_max(hi, sv[q]); lo = fminf(lo, sv[q]); }
+        hi = wave_max_uniform(hi);
+        lo = -wave_max_uniform(-lo);
+        const bool wide = __builtin_amdgcn_readfirstlane(hi - lo > a.lambda ? 1 : 0) != 0;   // false also when no score is finite
         // s_(b) from the leading 16 bits of the ordered keys: at most s_(b), so the bound only loosens
         uint32_t T = 0;
-        for (int bit = 31; bit >= 16; --bit) {
+        for (int bit = 31; wide && bit >= 16; --bit) {
           const uint32_t cand = T | (1u << bit);
           const int cnt = count_slots_ge<NQ>(key, cand);
           if (cnt >= b) T = cand;
@@ -172,7 +182,7 @@ __global__ __launch_bounds__(kF32Threads, 1) void select_dense_f32_kernel(F32Arg
           keep[q] = __ballot(lane + 64 * q < n && !(sv[q] < thr));
           cnt += __popcll(keep[q]);
         }
-        if (cnt >= b && cnt <= 128) {
+        if (wide && cnt >= b && cnt <= 128) {
           wave_lds_sync();                            // every lane holds its scores before s_l is rewritten
           int base = 0;
 #pragma unroll
@@ -194,58 +204,80 @@ __global__ __launch_bounds__(kF32Threads, 1) void select_dense_f32_kernel(F32Arg
       ns = meta[0];
     }
     // rows -> LDS: at their own position, or at their position in the reduced problem
+    const int perm = (tid & 31) * 4, at = (perm & 64) + (perm & 63) / 2;   // k = perm .. + 3 go to at, at + 32, at + 1, at + 33
 #pragma unroll
     for (int k = 0; k < NT; ++k) {
       const int r = (tid >> 5) + 32 * k;
       const int dst = ns ? idx_l[r] : r;
-      if (dst >= 0) *reinterpret_cast<float4*>(stage + dst * kF32Pitch + (tid & 31) * 4) = xr[k];
+      if (dst >= 0) {
+        *reinterpret_cast<float2*>(stage + dst * kF32Pitch + at) = make_float2(xr[k].x, xr[k].z);
+        *reinterpret_cast<float2*>(stage + dst * kF32Pitch + at + 32) = make_float2(xr[k].y, xr[k].w);
+      }
     }
     if (ns)                                           // rows between the survivors and the end of their last block
-      for (int r = ns + (tid >> 5); r < ((ns + 31) & ~31); r += kF32Threads / 32)
+      for (int r = ns + (tid >> 5); r < ((ns + 15) & ~15); r += kF32Threads / 32)
         *reinterpret_cast<float4*>(stage + r * kF32Pitch + (tid & 31) * 4) = make_float4(0.f, 0.f, 0.f, 0.f);
     __syncthreads();
-    // tile t of the lower triangle: row block I, column block J <= I (only the blocks in use)
-    const int nblk = ns ? (ns + 31) >> 5 : NT;
+    // the tiles of the lower triangle (row block I, column block J <= I, only the blocks in use), row by row, in sixteen equal shares
+    const int nblk = ns ? (ns + 15) >> 4 : 2 * NT;
     const int ntiles = nblk * (nblk + 1) / 2;
+    const int c = lane & 15, kg = lane >> 4;
+    const int first = wave * ntiles / kF32Waves, count = (wave + 1) * ntiles / kF32Waves - first;
+    int I0 = 0;
+    while ((I0 + 1) * (I0 + 2) / 2 <= first) ++I0;
+    const float* const op = stage + c * kF32Pitch + (kg & 1) * 64 + (kg >> 1) * 32;   // lane (row c, k-group kg) of an operand
+    float4 xi[8];
+    {
+      int I = I0, J = first - I0 * (I0 + 1) / 2, held = -1;
 #pragma unroll
-    for (int sl = 0; sl < MAXT; ++sl) {
-      const int tile = wave + kF32Waves * sl;
-      acc[sl] = f32x16_t{0};
-      if (tile < ntiles) {
-        int I = 0;
-        while ((I + 1) * (I + 2) / 2 <= tile) ++I;
-        const int J = tile - I * (I + 1) / 2;
-        const float* pa = stage + (I * 32 + (lane & 31)) * kF32Pitch + hf * (kD / 2);
-        const float* pb = stage + (J * 32 + (lane & 31)) * kF32Pitch + hf * (kD / 2);
-#pragma unroll 4
-        for (int q = 0; q < kD / 8; ++q) {
-          const float4 xa = *reinterpret_cast<const float4*>(pa + 4 * q);
-          const float4 xb = *reinterpret_cast<const float4*>(pb + 4 * q);
-          acc[sl] = __builtin_amdgcn_mfma_f32_32x32x2f32(xa.x, xb.x, acc[sl], 0, 0, 0);
-          acc[sl] = __builtin_amdgcn_mfma_f32_32x32x2f32(xa.y, xb.y, acc[sl], 0, 0, 0);
-          acc[sl] = __builtin_amdgcn_mfma_f32_32x32x2f32(xa.z, xb.z, acc[sl], 0, 0, 0);
-          acc[sl] = __builtin_amdgcn_mfma_f32_32x32x2f32(xa.w, xb.w, acc[sl], 0, 0, 0);
-        }
-        if (I == J) {                                 // squared norms sit on the diagonal
+      for (int sl = 0; sl < MAXT; ++sl) {
+        acc[sl] = f32x4{0.f, 0.f, 0.f, 0.f};
+        if (sl < count) {
+          if (I != held) {                            // (the row block's operand stays for the tiles of its row)
 #pragma unroll
-          for (int r = 0; r < 16; ++r) {
-            const int il = (r >> 2) * 8 + hf * 4 + (r & 3);
-            if (il == (lane & 31)) rinv[I * 32 + il] = acc[sl][r];
+            for (int q = 0; q < 8; ++q) xi[q] = *reinterpret_cast<const float4*>(op + I * 16 * kF32Pitch + 4 * q);
+            held = I;
           }
+          const float* pj = op + J * 16 * kF32Pitch;
+#pragma unroll
+          for (int q = 0; q < 8; ++q) {
+            const float4 xj = *reinterpret_cast<const float4*>(pj + 4 * q);
+            acc[sl] = __builtin_amdgcn_mfma_f32_16x16x4f32(xj.x, xi[q].x, acc[sl], 0, 0, 0);
+            acc[sl] = __builtin_amdgcn_mfma_f32_16x16x4f32(xj.y, xi[q].y, acc[sl], 0, 0, 0);
+            acc[sl] = __builtin_amdgcn_mfma_f32_16x16x4f32(xj.z, xi[q].z, acc[sl], 0, 0, 0);
+            acc[sl] = __builtin_amdgcn_mfma_f32_16x16x4f32(xj.w, xi[q].w, acc[sl], 0, 0, 0);
+          }
+          // lane (row c of block I, kg) holds columns 4 kg .. + 3 of block J: the squared norm of row c sits in lane (c, c / 4)
+          if (I == J && (c >> 2) == kg) {
+            auto pick = [](int bit, float one, float zero) { return bit ? one : zero; };   // (by value: a choice between two elements would put the array in memory)
+            const float ss = pick(c & 2, pick(c & 1, acc[sl][3], acc[sl][2]), pick(c & 1, acc[sl][1], acc[sl][0]));
+            rinv[I * 16 + c] = 1.0f / (sqrtf(ss) + a.eps);
+          }
+          if (++J > I) { ++I; J = 0; }
         }
       }
     }
-    __syncthreads();                                  // staged rows are dead from here on
-    if (tid < nblk * 32) rinv[tid] = 1.0f / (sqrtf(rinv[tid]) + a.eps);
-    __syncthreads();
+    __syncthreads();                                  // staged rows are dead from here on, the norms complete
+    {
+      int I = I0, J = first - I0 * (I0 + 1) / 2;
 #pragma unroll
-    for (int sl = 0; sl < MAXT; ++sl) {
-      const int tile = wave + kF32Waves * sl;
-      if (tile < ntiles) {
-        int I = 0;
-        while ((I + 1) * (I + 2) / 2 <= tile) ++I;
-        const int J = tile - I * (I + 1) / 2;
-        write_cos_tile(tri, rinv, acc[sl], I, J, lane);
+      for (int sl = 0; sl < MAXT; ++sl) {
+        if (sl < count) {
+          const int row = I * 16 + c;
+          const float rrow = rinv[row];
+          const float4 rc = *reinterpret_cast<const float4*>(rinv + J * 16 + 4 * kg);
+          const float v[4] = {acc[sl][0] * rrow * rc.x, acc[sl][1] * rrow * rc.y, acc[sl][2] * rrow * rc.z, acc[sl][3] * rrow * rc.w};
+          float* dst = tri + row * (row + 1) / 2 + J * 16 + 4 * kg;
+          if (I != J) {
+#pragma unroll
+            for (int q = 0; q < 4; ++q) dst[q] = v[q];
+          } else {                                    // (reading the row of a pick retires it)
+#pragma unroll
+            for (int q = 0; q < 4; ++q)
+              if (4 * kg + q <= c) dst[q] = 4 * kg + q == c ? INFINITY : v[q];
+          }
+          if (++J > I) { ++I; J = 0; }
+        }
       }
     }
   }
