@@ -180,6 +180,7 @@ __global__ __launch_bounds__(64 * W, (W <= 4 ? 2 : 1)) void select_lazy_kernel(L
   float s[S], m[S], r[S];
   int pslot[S];                  // >= 0: pool slot of this token in the current epoch; <= -2: position -2 - p in the wave's refresh list; -1: neither
   uint32_t fresh = 0xffffffffu;  // bit k: m[k] covers every pick made so far
+  int cov[F32 ? S : 1];          // fp32 rows: the 16-pick operand from which on the passes have yet to bring the token its picks
   auto tok_of = [&](int k) -> int { return base + 64 * k + lane; };
 #pragma unroll
   for (int k = 0; k < S; ++k) {
@@ -187,6 +188,7 @@ __global__ __launch_bounds__(64 * W, (W <= 4 ? 2 : 1)) void select_lazy_kernel(L
     m[k] = 0.f;
     r[k] = 0.f;
     pslot[k] = -1;
+    if constexpr (F32) cov[k] = 0;
   }
   // rows of the picks: zero until written (a partly filled 16-row operand multiplies zeros)
   for (int u = tid; u < Cfg::kPickBytes / 16; u += NT) reinterpret_cast<uint4*>(pk)[u] = make_uint4(0u, 0u, 0u, 0u);
@@ -452,19 +454,35 @@ __global__ __launch_bounds__(64 * W, (W <= 4 ? 2 : 1)) void select_lazy_kernel(L
         unsigned long long mem[S];
         masks_ge<S>(go, thr_r >= -3.402823466e38f ? thr_r : -3.402823466e38f, mem);
         int off = 0;
+        if constexpr (F32) {
+          // The least covered tokens first, so that sixteen neighbours start at a common operand (every entry's maximum is its own: the
+          // order changes no bit).  A pass over all the picks again costs 32 MFMAs of 32 cycles an operand and sixteen rows.
+          for (int cl = 0; cl <= (t >> 4); ++cl) {
 #pragma unroll
-        for (int k = 0; k < S; ++k) {
-          const bool in = __builtin_amdgcn_inverse_ballot_w64(mem[k]);
-          const int pos = kvr_ix_if(in, off + lane_rank(mem[k]), TPW, 102);   // 102: position in the refresh list
-          if (in) lrw_i[pos] = tok_of(k);
-          pslot[k] = in ? -2 - pos : pslot[k];
-          off += __popcll(mem[k]);
+            for (int k = 0; k < S; ++k) {
+              const unsigned long long mm = mem[k] & __ballot(cov[k] == cl);
+              const bool in = __builtin_amdgcn_inverse_ballot_w64(mm);
+              const int pos = kvr_ix_if(in, off + lane_rank(mm), TPW, 102);   // 102: position in the refresh list
+              if (in) lrw_i[pos] = tok_of(k) | cl << 16;
+              pslot[k] = in ? -2 - pos : pslot[k];
+              off += __popcll(mm);
+            }
+          }
+        } else {
+#pragma unroll
+          for (int k = 0; k < S; ++k) {
+            const bool in = __builtin_amdgcn_inverse_ballot_w64(mem[k]);
+            const int pos = kvr_ix_if(in, off + lane_rank(mem[k]), TPW, 102);
+            if (in) lrw_i[pos] = tok_of(k);
+            pslot[k] = in ? -2 - pos : pslot[k];
+            off += __popcll(mem[k]);
+          }
         }
         cnt_r = off;
         // pad to a multiple of 64 with a valid row (its results are never read)
         // (at least one group: the first group's rows are requested whether or not the list has entries)
         const int padded = (cnt_r == 0 ? GR : (cnt_r + GR - 1) & ~(GR - 1)) + GR;     // ... and one group more: the pass requests a group ahead
-        for (int u = cnt_r + lane; u < padded; u += 64) lrw_i[u] = min(base, n - 1);
+        for (int u = cnt_r + lane; u < padded; u += 64) lrw_i[u] = min(base, n - 1) | (F32 ? 255 << 16 : 0);   // (fp32 rows: nothing to meet)
       }
       // The rows of the list's first 64 entries are requested here and travel while the pool's triangle is
       // computed and raced; further groups follow inside the pass, one group ahead.
@@ -472,7 +490,7 @@ __global__ __launch_bounds__(64 * W, (W <= 4 ? 2 : 1)) void select_lazy_kernel(L
       auto fetch = [&](int gi, int sub) {
         if constexpr (F32) {
           // straight into the operand layout of the 16x16x4 MFMA: lane (c, kg) holds pieces kg, kg + 4, .. of row c
-          const int row = kvr_ix(lrw_i[gi * GR + sub * CH + (lane & 15)], n, 104);   // 104: token of a list entry
+          const int row = kvr_ix(lrw_i[gi * GR + sub * CH + (lane & 15)] & 0xffff, n, 104);   // 104: token of a list entry
           const uint32_t o = static_cast<uint32_t>(row) * pitch_b + (lane >> 4) * 16u;
 #pragma unroll
           for (int q = 0; q < LPC; ++q) pre[sub][q] = *reinterpret_cast<const uint4*>(Vh + (o + q * 64u));
@@ -497,7 +515,13 @@ __global__ __launch_bounds__(64 * W, (W <= 4 ? 2 : 1)) void select_lazy_kernel(L
         for (int k = 0; k < kGat; ++k) {
           const int slot = k * kGatRows + gat_row;
           if (pool_tok[slot] < 0) x[k] = make_uint4(0u, 0u, 0u, 0u);   // (only here: a select between the loads would make each wait for the one before)
-          *reinterpret_cast<uint4*>(prow + slot * kPitch + gat_piece * 16) = x[k];
+          if constexpr (F32) {                         // floats 4 p + 0, 2 and 1, 3 of piece p: k-groups p % 2 and p % 2 + 2, step p / 2
+            char* dst = prow + slot * kPitch + (gat_piece & 1) * 128 + (gat_piece >> 1) * 8;
+            *reinterpret_cast<uint2*>(dst) = make_uint2(x[k].x, x[k].z);
+            *reinterpret_cast<uint2*>(dst + 256) = make_uint2(x[k].y, x[k].w);
+          } else {
+            *reinterpret_cast<uint4*>(prow + slot * kPitch + gat_piece * 16) = x[k];
+          }
         }
         if (!have_r) {
 #pragma unroll
@@ -510,7 +534,62 @@ __global__ __launch_bounds__(64 * W, (W <= 4 ? 2 : 1)) void select_lazy_kernel(L
         }
       }
       lds_barrier();
-      {
+      if constexpr (F32) {
+        // 16x16 tiles of the lower triangle, row by row, in equal shares (16x16x4 MFMAs: they add their four products one after
+        // the other, so with k = 8 s + e, 8 s + 4 + e, 8 s + e + 1, 8 s + 5 + e in the four k-groups of a step the sums have the bits of 32x32x2
+        // MFMAs over k = 8 s + e, 8 s + 4 + e.  Those take 10 tiles of 4096 cycles for four SIMDs, three of them on two; these 36 of 1024.)
+        constexpr int NT16 = P / 16 * (P / 16 + 1) / 2, MAXT = (NT16 + W - 1) / W;
+        const int c = lane & 15, kg = lane >> 4;
+        const int first = w * NT16 / W, count = (w + 1) * NT16 / W - first;
+        int I0 = 0;
+        while ((I0 + 1) * (I0 + 2) / 2 <= first) ++I0;
+        const char* const op = prow + c * kPitch + kg * 128;   // lane (row c, k-group kg): its 32 floats
+        f32x4 acc[MAXT];
+        {
+          float4 xi[8];
+          int I = I0, J = first - I0 * (I0 + 1) / 2, held = -1;
+#pragma unroll
+          for (int q = 0; q < MAXT; ++q) {
+            acc[q] = f32x4{0.f, 0.f, 0.f, 0.f};
+            if (q < count) {
+              if (I != held) {                         // (the row block's operand stays for the tiles of its row)
+#pragma unroll
+                for (int u = 0; u < 8; ++u) xi[u] = *reinterpret_cast<const float4*>(op + I * 16 * kPitch + u * 16);
+                held = I;
+              }
+#pragma unroll
+              for (int u = 0; u < 8; ++u) {
+                const float4 xj = *reinterpret_cast<const float4*>(op + J * 16 * kPitch + u * 16);
+                acc[q] = __builtin_amdgcn_mfma_f32_16x16x4f32(xj.x, xi[u].x, acc[q], 0, 0, 0);
+                acc[q] = __builtin_amdgcn_mfma_f32_16x16x4f32(xj.y, xi[u].y, acc[q], 0, 0, 0);
+                acc[q] = __builtin_amdgcn_mfma_f32_16x16x4f32(xj.z, xi[u].z, acc[q], 0, 0, 0);
+                acc[q] = __builtin_amdgcn_mfma_f32_16x16x4f32(xj.w, xi[u].w, acc[q], 0, 0, 0);
+              }
+              if (++J > I) { ++I; J = 0; }
+            }
+          }
+        }
+        lds_barrier();                                 // every wave has read its rows: the triangle takes their place
+        int I = I0, J = first - I0 * (I0 + 1) / 2;
+#pragma unroll
+        for (int q = 0; q < MAXT; ++q) {
+          if (q < count) {
+            // lane (row c of block I, kg) holds columns 4 kg .. + 3 of block J
+            const int row = I * 16 + c, col = J * 16 + 4 * kg;
+            const float rrow = pool_r[row];
+            const float4 rc = *reinterpret_cast<const float4*>(pool_r + col);
+            float4 v = make_float4(acc[q][0] * rrow * rc.x, acc[q][1] * rrow * rc.y, acc[q][2] * rrow * rc.z, acc[q][3] * rrow * rc.w);
+            if (I == J) {                              // the diagonal holds +inf: the row of a pick retires it
+              if (col == row) v.x = INFINITY;
+              if (col + 1 == row) v.y = INFINITY;
+              if (col + 2 == row) v.z = INFINITY;
+              if (col + 3 == row) v.w = INFINITY;
+            }
+            if (col <= row) *reinterpret_cast<float4*>(tri + padded_row_start(row) + col) = v;
+            if (++J > I) { ++I; J = 0; }
+          }
+        }
+      } else {
         const int hf = lane >> 5;
         f32x16 acc[NTILE];
 #pragma unroll
@@ -523,23 +602,10 @@ __global__ __launch_bounds__(64 * W, (W <= 4 ? 2 : 1)) void select_lazy_kernel(L
             const int J = tile - I * (I + 1) / 2;
             const char* pa = prow + (I * 32 + (lane & 31)) * kPitch + hf * 16;
             const char* pb = prow + (J * 32 + (lane & 31)) * kPitch + hf * 16;
-            if constexpr (F32) {
-              // 32x32x2: the lane's two k per four MFMAs are floats 8 ks + 4 hf .. + 3 of its row (one LDS request)
-#pragma unroll 4
-              for (int ks = 0; ks < 16; ++ks) {
-                const float4 xa = *reinterpret_cast<const float4*>(pb + ks * 32);
-                const float4 xb = *reinterpret_cast<const float4*>(pa + ks * 32);
-                acc[q] = __builtin_amdgcn_mfma_f32_32x32x2f32(xa.x, xb.x, acc[q], 0, 0, 0);
-                acc[q] = __builtin_amdgcn_mfma_f32_32x32x2f32(xa.y, xb.y, acc[q], 0, 0, 0);
-                acc[q] = __builtin_amdgcn_mfma_f32_32x32x2f32(xa.z, xb.z, acc[q], 0, 0, 0);
-                acc[q] = __builtin_amdgcn_mfma_f32_32x32x2f32(xa.w, xb.w, acc[q], 0, 0, 0);
-              }
-            } else {
 #pragma unroll
-              for (int ks = 0; ks < 8; ++ks)
-                acc[q] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(*reinterpret_cast<const bf16x8*>(pb + ks * 32),
-                                                                 *reinterpret_cast<const bf16x8*>(pa + ks * 32), acc[q], 0, 0, 0);
-            }
+            for (int ks = 0; ks < 8; ++ks)
+              acc[q] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(*reinterpret_cast<const bf16x8*>(pb + ks * 32),
+                                                               *reinterpret_cast<const bf16x8*>(pa + ks * 32), acc[q], 0, 0, 0);
           }
         }
         if constexpr (Cfg::kAlias) lds_barrier();      // every wave has read its rows: the triangle takes their place
@@ -712,7 +778,9 @@ __global__ __launch_bounds__(64 * W, (W <= 4 ? 2 : 1)) void select_lazy_kernel(L
                 if (kg == 0) lr2[gi * GR + sub * 16 + (lane & 15)] = 1.0f / (sqrtf(ss) + a.eps);
               }
               float pm = 0.f;                        // the floor of Eq. 2
-              for (int tl = 0; tl < tiles; ++tl) {
+              // (the picks before were met in an earlier pass, their products would come out in the same bits)
+              const int from = __builtin_amdgcn_readfirstlane(lrw_i[gi * GR + sub * 16] >> 16);
+              for (int tl = from; tl < tiles; ++tl) {
                 const char* ap = pk + (kg & 1) * kLzPickPlaneF + (tl * 16 + (lane & 15)) * kLzHalfF + (kg >> 1) * 16;
                 float4 av[LPC];
 #pragma unroll
@@ -820,6 +888,7 @@ __global__ __launch_bounds__(64 * W, (W <= 4 ? 2 : 1)) void select_lazy_kernel(L
           const float mx = lrw[pos];
           if (!have_r) { const float rx = lr2[pos]; r[k] = listed ? rx : r[k]; }
           m[k] = listed ? hw_max(m[k], mx * r[k]) : m[k];
+          if constexpr (F32) cov[k] = listed ? t >> 4 : cov[k];
           now |= pslot[k] != -1 ? 1u << k : 0u;      // pool members left the race up to date
           pslot[k] = -1;
         }
