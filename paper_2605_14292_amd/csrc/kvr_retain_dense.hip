@@ -4,7 +4,7 @@
 //            tokens per query, mean over queries             (base-score stand-in)
 //   norms    r_j = 1/(||V_j|| + eps) from the Gram diagonal  (paper Eq. 1)
 //   Gram     lower-triangular 32x32 tiles of V V^T on bf16 MFMA with fp32
-//            accumulation, scaled to cosines and parked in LDS as a padded
+//            accumulation, scaled to cosines and parked in LDS as a packed or padded
 //            triangle of fp32                                (Algorithm 1, Sims)
 //   greedy   one wave keeps s, m and the alive set in registers (token j lives
 //            in lane j%64) and runs the race of kvr_dense_common.hpp   (Eq. 2-3, Alg. 1)
@@ -61,7 +61,12 @@ template <int NT> struct DenseCfg {
   static constexpr int MAXD = (NT + W - 1) / W, MAXO = (OFFD + W - 1) / W;   // Gram tiles per wave, on the diagonal and off it
   static constexpr int ROWS = (N32 * 16 + 64 * (W - 2) - 1) / (64 * (W - 2));   // 16-byte row pieces per thread of waves 2 ..
   static constexpr int bcap(int b) { return (b + 63) & ~63; }
-  static constexpr int region = N32 * kRowPitch > padded_tri_floats(N32) * 4 ? N32 * kRowPitch : padded_tri_floats(N32) * 4;
+  // The triangle: packed, or with rows padded to 16-byte stores.  Padded rows are written faster and read with bank conflicts (a pick of 256
+  // tokens 24 cycles longer).  One head per CU waits for its picks: 2688 heads of 251 tokens, b = 101 220 us padded, 209 packed; 257 of 256, b = 128 54.8
+  // and 52.5.  Several heads share the LDS's store rate: 4096 of 192, b = 64 156 and 159, of 128 110 and 111; 8192 of 64 122 and 125.
+  static constexpr bool PACKED = NT == 8;
+  static constexpr int kTriBytes = PACKED ? dense_tri_floats(NT) * 4 : padded_tri_floats(N32) * 4;
+  static constexpr int region = N32 * kRowPitch > kTriBytes ? N32 * kRowPitch : kTriBytes;
   // triangle or staged rows | s_l[2][N32] | rinv[N32] | lists [2][order, gain][bcap] | [2][idx][bcap], 16 bits each: with 32
   // two heads of 192 tokens and more than 128 picks do not fit a CU (4096 heads, n=192, b=160 412 us; now 244, and 377 before the lists came in pairs)
   static constexpr int smem_bytes(int b) { return region + N32 * 3 * 4 + 2 * bcap(b) * (4 + 4 + 2); }
@@ -158,13 +163,17 @@ __global__ __launch_bounds__(64 * DenseCfg<NT>::W, DenseCfg<NT>::W * DenseCfg<NT
     }
     lds_barrier();                                      // every wave has read its rows: the triangle takes their place
     if (need_v) {
+      auto write_tile = [&](const f32x16& t, int I, int J) {
+        if constexpr (C::PACKED) write_cos_tile_rows(tri, rinv, t, I, J, lane);
+        else write_cos_tile_padded(tri, rinv, t, I, J, lane);
+      };
 #pragma unroll
       for (int d = 0; d < C::MAXD; ++d)
-        if (wave + W * d < NT) write_cos_tile_padded(tri, rinv, accd[d], wave + W * d, wave + W * d, lane);
+        if (wave + W * d < NT) write_tile(accd[d], wave + W * d, wave + W * d);
       int I = I0, J = o0 - I0 * (I0 - 1) / 2;
 #pragma unroll
       for (int sl = 0; sl < C::MAXO; ++sl) {
-        if (sl < cnt) write_cos_tile_padded(tri, rinv, acc[sl], I, J, lane);
+        if (sl < cnt) write_tile(acc[sl], I, J);
         if (++J == I) { ++I; J = 0; }
       }
     }
@@ -182,7 +191,7 @@ __global__ __launch_bounds__(64 * DenseCfg<NT>::W, DenseCfg<NT>::W * DenseCfg<NT
       int32_t* order_l = lists + par * 2 * bcap;
       float* s_l = s_all + par * N32;
       __builtin_amdgcn_s_setprio(3);                    // the waves that share its SIMD have time to spare
-      pick_chain<NQ, true>(s_l, tri, order_l, reinterpret_cast<float*>(order_l + bcap), n, brun, a.lambda, diverse, lane);
+      pick_chain<NQ, !C::PACKED>(s_l, tri, order_l, reinterpret_cast<float*>(order_l + bcap), n, brun, a.lambda, diverse, lane);
       sort_picks<NQ>(order_l, idx_all + par * bcap, reinterpret_cast<int32_t*>(s_l), brun, lane, nullptr);   // (the scores are dead by now)
       __builtin_amdgcn_s_setprio(0);
       lds_barrier();                                    // the triangle of h is dead
