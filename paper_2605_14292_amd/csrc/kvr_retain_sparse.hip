@@ -61,7 +61,9 @@ __global__ __launch_bounds__(kDenseThreads, (NT <= 4 ? 4 : 2)) void retain_spars
   int32_t* redi = reinterpret_cast<int32_t*>(redf + 16);         // [2][4] counts (+ 8 spare)
   int32_t* cnt = redi + 16;                                      // [S][4] survivors per slot and wave
   int32_t* off = cnt + 64;                                       // [S][4] their exclusive prefix
+  int32_t* hb = off + 64;                                        // [2] bins
   int32_t* idx_l = off + 64 + 32;
+  int32_t* hist = reinterpret_cast<int32_t*>(smem);              // [1024] (the rows come later)
   int32_t* order_l = idx_l + kSpMaxB;
   float* gain_l = reinterpret_cast<float*>(order_l + kSpMaxB);
 
@@ -97,6 +99,7 @@ __global__ __launch_bounds__(kDenseThreads, (NT <= 4 ? 4 : 2)) void retain_spars
     // ------------------------------------------------ the tokens that can ever be picked
     // Nothing can go when the finite scores spread by at most lambda: one min/max settles that.
     bool marked = false;
+    float ghi = -INFINITY, glo = INFINITY;
     {
       float hi = -INFINITY, lo = INFINITY;
 #pragma unroll
@@ -105,8 +108,8 @@ __global__ __launch_bounds__(kDenseThreads, (NT <= 4 ? 4 : 2)) void retain_spars
       hi = wave_max_uniform(hi);
       lo = -wave_max_uniform(-lo);
       if (lane == 0) { redf[par * 4 + wave] = hi; redf[8 + par * 4 + wave] = lo; }
+      *reinterpret_cast<int4*>(hist + 4 * tid) = make_int4(0, 0, 0, 0);
       lds_barrier();
-      float ghi = -INFINITY, glo = INFINITY;
 #pragma unroll
       for (int u = 0; u < 4; ++u) { ghi = hw_max(ghi, redf[par * 4 + u]); glo = fminf(glo, redf[8 + par * 4 + u]); }
       par ^= 1;
@@ -119,22 +122,46 @@ __global__ __launch_bounds__(kDenseThreads, (NT <= 4 ? 4 : 2)) void retain_spars
       uint32_t key[S];
 #pragma unroll
       for (int k = 0; k < S; ++k) key[k] = k * 256 + tid < n ? ordered_key(sv[k] + 0.0f) : 0u;
-      // largest value of the leading 16 key bits that at least `want` keys reach (0 when fewer keys exist)
-      auto kth_key16 = [&](int want) -> uint32_t {
-        uint32_t T = 0;
-        for (int bit = 31; bit >= 16; --bit) {
-          const uint32_t cand = T | (1u << bit);
-          int c = 0;
+      // A histogram of the leading 16 key bits from the lowest finite score up (two or more values a bin where 1024 bins would
+      // not reach the best one; infinities and NaNs above it fall into the last bin), summed from the top: hb[0] is the lowest bin with
+      // which b tokens are reached, hb[1] the one with which more than N32 are (-1: never).
+      // (A search bit by bit took 16 counts over all slots and as many barriers: 12 400 cycles of a head's 88 000 for n = 3001.  With the
+      // triangle's stores from one base address, the kept rows of b > 64 in one batch and twelve slots up to 3072 tokens: 1024 heads of 3001, b = 128
+      // 85.6 -> 74.0 us; 7168 of 1024 521 -> 464, with b = 64 174 -> 155; 1024 of 2900, b = 64 37.0 -> 30.0.)
+      const uint32_t kl = ordered_key(glo + 0.0f) >> 16, range = (ordered_key(ghi + 0.0f) >> 16) - kl;
+      const int sh = max(0, 22 - __clz(static_cast<int>(range)));   // range >> sh < 1024
 #pragma unroll
-          for (int k = 0; k < S; ++k) c += __popcll(__ballot(key[k] >= cand));
-          if (lane == 0) redi[par * 4 + wave] = c;
-          lds_barrier();
-          const int tot = redi[par * 4] + redi[par * 4 + 1] + redi[par * 4 + 2] + redi[par * 4 + 3];
-          par ^= 1;
-          if (tot >= want) T = cand;
+      for (int k = 0; k < S; ++k)
+        if (key[k] >> 16 >= kl) atomicAdd(&hist[min((key[k] >> 16) - kl >> sh, 1023u)], 1);   // (padding: key 0)
+      if (tid < 2) hb[tid] = -1;
+      lds_barrier();
+      {
+        const int4 c = *reinterpret_cast<const int4*>(hist + 1020 - 4 * tid);   // thread t: bins 1023 - 4 t .. 1020 - 4 t
+        const int own = c.x + c.y + c.z + c.w;
+        int v = own;
+        v += __builtin_amdgcn_update_dpp(0, v, 0x111, 0xf, 0xf, false);
+        v += __builtin_amdgcn_update_dpp(0, v, 0x112, 0xf, 0xf, false);
+        v += __builtin_amdgcn_update_dpp(0, v, 0x114, 0xf, 0xf, false);
+        v += __builtin_amdgcn_update_dpp(0, v, 0x118, 0xf, 0xf, false);
+        v += __builtin_amdgcn_update_dpp(0, v, 0x142, 0xa, 0xf, false);
+        v += __builtin_amdgcn_update_dpp(0, v, 0x143, 0xc, 0xf, false);
+        if (lane == 63) redi[par * 4 + wave] = v;
+        lds_barrier();
+        int before = v - own;                          // tokens in higher bins
+#pragma unroll
+        for (int u = 0; u < 3; ++u) before += u < wave ? redi[par * 4 + u] : 0;
+        par ^= 1;
+#pragma unroll
+        for (int i = 0; i < 2; ++i) {
+          const int want = i == 0 ? bq : N32 + 1;
+          if (before < want && before + own >= want) { // (one thread)
+            const int at = before + c.w >= want ? 3 : before + c.w + c.z >= want ? 2 : before + c.w + c.z + c.y >= want ? 1 : 0;
+            hb[i] = 1020 - 4 * tid + at;
+          }
         }
-        return T;
-      };
+      }
+      lds_barrier();
+      auto edge = [&](int bin) -> uint32_t { return kl + (static_cast<uint32_t>(bin) << sh) << 16; };   // lowest key of a bin
       // survivors per slot and wave into cnt[], their number over the workgroup returned
       auto count_kept = [&]() -> int {
         int c = 0;
@@ -149,8 +176,9 @@ __global__ __launch_bounds__(kDenseThreads, (NT <= 4 ? 4 : 2)) void retain_spars
         par ^= 1;
         return tot;
       };
-      // s_(b) from the leading 16 bits of the ordered keys: at most s_(b), so the bound only loosens
-      const float sb = key_to_float(kth_key16(bq));
+      // the lower edge of s_(b)'s bin: at most s_(b), so the bound only loosens
+      const int b0 = __builtin_amdgcn_readfirstlane(hb[0]), b1 = __builtin_amdgcn_readfirstlane(hb[1]);
+      const float sb = key_to_float(b0 < 0 ? 0u : edge(b0));
       const float thr = sb - a.lambda * 1.00001f - 1e-5f * fabsf(sb);   // fp32 cosines may exceed 1 by a few ulp
 #pragma unroll
       for (int k = 0; k < S; ++k) km[k] = __ballot(k * 256 + tid < n && !(sv[k] < thr));   // (a NaN threshold or score keeps the token)
@@ -168,14 +196,13 @@ __global__ __launch_bounds__(kDenseThreads, (NT <= 4 ? 4 : 2)) void retain_spars
         if (near > N32) ns = -1;                       // handed on
       }
       if (ns > N32) {
-        // More candidates than fit: the best-scored are kept, cut where the leading 16 key bits change (at most N32
+        // More candidates than fit: the best-scored are kept, cut at the edge of a bin (at most N32
         // of them), and the best score left out is remembered.  Pick gains never increase and a token gains at most
         // its score, so the run is valid iff that score stays below the last pick's gain, which is checked when the
         // chain is done.  That gain is at most s_(b) and in practice a good part of lambda below it: when the score
         // left out lies within a quarter of lambda of s_(b) the chain would be run in vain, and the head is handed
         // on at once (a guess about speed only: either way the picks are exact).
-        const uint32_t T2 = kth_key16(N32 + 1);       // > 0: more than N32 keys exist
-        const uint32_t cut = T2 + 0x10000u;            // (wraps to 0 only for all-ones keys, NaNs: every token then passes and the head is handed on)
+        const uint32_t cut = edge(b1 + 1);             // (b1 < 0 with NaNs only: every token passes and the head is handed on)
         float ob = -INFINITY;
 #pragma unroll
         for (int k = 0; k < S; ++k) {
@@ -201,11 +228,12 @@ __global__ __launch_bounds__(kDenseThreads, (NT <= 4 ? 4 : 2)) void retain_spars
     if (wave == 0) {
       int v = lane < 4 * S ? cnt[lane] : 0;
       const int own = v;
-#pragma unroll
-      for (int d = 1; d < 64; d <<= 1) {
-        const int o = __shfl_up(v, d, kWave);
-        if (lane >= d) v += o;
-      }
+      v += __builtin_amdgcn_update_dpp(0, v, 0x111, 0xf, 0xf, false);
+      v += __builtin_amdgcn_update_dpp(0, v, 0x112, 0xf, 0xf, false);
+      v += __builtin_amdgcn_update_dpp(0, v, 0x114, 0xf, 0xf, false);
+      v += __builtin_amdgcn_update_dpp(0, v, 0x118, 0xf, 0xf, false);
+      v += __builtin_amdgcn_update_dpp(0, v, 0x142, 0xa, 0xf, false);
+      v += __builtin_amdgcn_update_dpp(0, v, 0x143, 0xc, 0xf, false);
       off[lane] = v - own;
     }
     lds_barrier();
@@ -253,21 +281,23 @@ __global__ __launch_bounds__(kDenseThreads, (NT <= 4 ? 4 : 2)) void retain_spars
           __builtin_amdgcn_sched_barrier(0);          // keep one tile's fragment loads in flight, not all of them
 #pragma unroll
           for (int ks = 0; ks < 8; ++ks)
-            acc[q] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(frag_at(stage, I, ks, lane), frag_at(stage, J, ks, lane),
+            acc[q] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(frag_at(stage, J, ks, lane), frag_at(stage, I, ks, lane),
                                                              acc[q], 0, 0, 0);
           __builtin_amdgcn_sched_barrier(0);
-          if (I == J) {                               // squared norms sit on the diagonal
+          if (I == J) {                               // squared norms sit on the diagonal: element r of lane (l32, hf) is row 8 (r / 4) + 4 hf + r % 4
+            const int l32 = lane & 31;
+            auto pick = [](int bit, float one, float zero) { return bit ? one : zero; };   // (by value: a choice between two elements would put the array in memory)
+            float v8[8], v4[4];
 #pragma unroll
-            for (int r = 0; r < 16; ++r) {
-              const int il = (r >> 2) * 8 + hf * 4 + (r & 3);
-              if (il == (lane & 31)) rinv[I * 32 + il] = acc[q][r];
-            }
+            for (int k = 0; k < 8; ++k) v8[k] = pick(l32 & 1, acc[q][2 * k + 1], acc[q][2 * k]);
+#pragma unroll
+            for (int k = 0; k < 4; ++k) v4[k] = pick(l32 & 2, v8[2 * k + 1], v8[2 * k]);
+            const float ss = pick(l32 & 16, pick(l32 & 8, v4[3], v4[2]), pick(l32 & 8, v4[1], v4[0]));
+            if (((l32 >> 2) & 1) == hf) rinv[I * 32 + l32] = 1.0f / (sqrtf(ss) + a.eps);
           }
         }
       }
-      lds_barrier();                                // staged rows are dead from here on
-      for (int j = tid; j < N32; j += kDenseThreads) rinv[j] = 1.0f / (sqrtf(rinv[j]) + a.eps);
-      lds_barrier();
+      lds_barrier();                                // staged rows are dead from here on, the norms complete
 #pragma unroll
       for (int q = 0; q < TPWV; ++q) {
         const int tile = wave + 4 * q;
@@ -275,7 +305,7 @@ __global__ __launch_bounds__(kDenseThreads, (NT <= 4 ? 4 : 2)) void retain_spars
           int I = 0;
           while ((I + 1) * (I + 2) / 2 <= tile) ++I;
           const int J = tile - I * (I + 1) / 2;
-          write_cos_tile(tri, rinv, acc[q], I, J, lane);
+          write_cos_tile_rows(tri, rinv, acc[q], I, J, lane);
         }
       }
     }
@@ -303,7 +333,7 @@ __global__ __launch_bounds__(kDenseThreads, (NT <= 4 ? 4 : 2)) void retain_spars
       if (a.pick_gain) a.pick_gain[ob + t] = t < bt ? gain_l[t] : -INFINITY;
     }
     if ((a.K_out || a.V_out) && !redo && bt > 0)
-      compact_rows<4>(a.K, a.V, a.K_out, a.V_out, head_off, a.stride_tok, idx_l, n, bt, ob, tid, kDenseThreads);
+      compact_rows<(NT <= 4 ? 4 : 8)>(a.K, a.V, a.K_out, a.V_out, head_off, a.stride_tok, idx_l, n, bt, ob, tid, kDenseThreads);
     lds_barrier();                                   // the lists and tables are reused by the next head
   }
 }
@@ -343,6 +373,7 @@ hipError_t launch_retain_sparse(const void* K, const void* V, const float* s, co
     constexpr int per_cu = NT <= 4 ? 4 : 2;
     if (lay.n <= 1024) return go(&retain_sparse_kernel<NT, 4>, smem, per_cu);
     if (lay.n <= 2048) return go(&retain_sparse_kernel<NT, 8>, smem, per_cu);
+    if (lay.n <= 3072) return go(&retain_sparse_kernel<NT, 12>, smem, per_cu);
     return go(&retain_sparse_kernel<NT, 16>, smem, per_cu);
   };
   return small ? by_n(std::integral_constant<int, 4>{}) : by_n(std::integral_constant<int, 6>{});
