@@ -321,8 +321,46 @@ __device__ __forceinline__ void write_cos_tile(float* tri, const float* rinv, co
 }
 
 // The same into the packed triangle from the other orientation (column block J as operand A, row block I as operand B: lane (row = lane &
-// 31, hf) holds columns 8R + 4hf .. + 3 of its row).  A lane's addresses are then one base and constants, two neighbouring columns a
-// store; with one store and one address per element a tile costs the LDS pipe and the vector unit half as much again.
+// 31, hf) holds columns 8R + 4hf .. + 3 of its row), in two steps: products to cosines in registers, and the stores.  A lane's addresses are
+// one base and constants, two neighbouring columns a store; with one store and one address per element a tile costs the LDS pipe
+// and the vector unit half as much again.  A wave that has the CU's LDS nearly to itself scales all its tiles before it stores the first: a
+// read of norms behind a tile's stores waits for them (six tiles of a wave, one after the other, 6 700 cycles).
+__device__ __forceinline__ void scale_cos_tile(const float* rinv, f32x16& acc, int I, int J, int lane) {
+  const int hf = lane >> 5;
+  const float rrow = rinv[I * 32 + (lane & 31)];
+  float4 rc[4];                                       // the columns' inverse norms, all requested before the first use
+#pragma unroll
+  for (int R = 0; R < 4; ++R) rc[R] = *reinterpret_cast<const float4*>(rinv + J * 32 + 8 * R + 4 * hf);
+#pragma unroll
+  for (int R = 0; R < 4; ++R) {
+    acc[4 * R] = acc[4 * R] * rrow * rc[R].x;
+    acc[4 * R + 1] = acc[4 * R + 1] * rrow * rc[R].y;
+    acc[4 * R + 2] = acc[4 * R + 2] * rrow * rc[R].z;
+    acc[4 * R + 3] = acc[4 * R + 3] * rrow * rc[R].w;
+  }
+}
+__device__ __forceinline__ void store_cos_tile(float* tri, const f32x16& acc, int I, int J, int lane) {
+  const int hf = lane >> 5;
+  const int row = I * 32 + (lane & 31);
+  float* dst = tri + row * (row + 1) / 2 + J * 32 + 4 * hf;
+  if (I != J) {
+#pragma unroll
+    for (int R = 0; R < 4; ++R) {
+#pragma unroll
+      for (int q = 0; q < 4; ++q) dst[8 * R + q] = acc[4 * R + q];
+    }
+  } else {
+    const int last = (lane & 31) - 4 * hf;            // the row's diagonal element, counted from dst
+#pragma unroll
+    for (int R = 0; R < 4; ++R) {
+#pragma unroll
+      for (int q = 0; q < 4; ++q)
+        if (8 * R + q <= last) dst[8 * R + q] = 8 * R + q == last ? INFINITY : acc[4 * R + q];
+    }
+  }
+}
+
+// One tile, scaled and stored row quarter by row quarter: what workgroups that share a CU do better with.
 __device__ __forceinline__ void write_cos_tile_rows(float* tri, const float* rinv, const f32x16& acc, int I, int J, int lane) {
   const int hf = lane >> 5;
   const int row = I * 32 + (lane & 31);

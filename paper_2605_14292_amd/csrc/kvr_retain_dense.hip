@@ -25,15 +25,21 @@
 // the blocks with themselves, V loaded as operands: the same bits, but up to 8 % slower at 128 tokens.
 //
 // What bounds it is the chain of dependent picks, which uses one wave, times the heads a CU holds at once: one of 256
-// tokens (the triangle takes 133 of the CU's 160 KB of LDS), two of 192 (75 KB), three of 128 and four of 64 tokens
-// (registers).  n = 251, b = 101: 14.1 us of chain and 0.4 of sorting per head, then 0.6 us to stage the rows, 1.8 for the
-// Gram, 1.9 for the triangle (profile by cycle counters).  With one phase after the other a head took the chain plus
-// everything else.  Measured with one phase after the other and the compiler's race -> now, scores from 7 queries: 2688 heads,
-// n=251, b=101 414 -> 220 us; 4096 heads: n=192, b=64 213 -> 155, n=128, b=64 175 -> 111; 8192 heads, n=64, b=48 234 -> 123;
-// one head, n=128, b=64 19.0 -> 15.5, 256 heads 20.5 -> 17.  Scores far below lambda given: 4096 heads, n=128, b=64 153 -> 84.
-// Tried: the Gram beside the chain too, its operands loaded from memory in the MFMA layout (there is no room for a row
-// stage beside the triangle): the 450 gathered loads of a head of 256 tokens take 12 us whatever the prefetch depth or the
-// bytes per row and request, the address unit spending 64 cycles on each; 239 us on the first shape.
+// tokens (the triangle takes 132 of the CU's 160 KB of LDS), two of 192 (75 KB), three of 128 and four of 64 tokens
+// (registers).  Measured with one phase after the other and the compiler's race -> this pipeline, scores from 7 queries: 4096 heads:
+// n=192, b=64 213 -> 155, n=128, b=64 175 -> 111; 8192 heads, n=64, b=48 234 -> 123; one head, n=128, b=64 19.0 -> 15.5, 256
+// heads 20.5 -> 17.  Scores far below lambda given: 4096 heads, n=128, b=64 153 -> 84.
+//
+// Heads of more than 192 tokens (AHEAD): between two chains of such a head stood 0.6 us of staging, 1.8 of Gram and 1.9 of triangle beside 14.1
+// of chain (n = 251, b = 101), and only the triangle needs the place of the one before.  So the waves 2 .. 7 stage the next head's rows a
+// quarter of their columns at a time in the 16 KB beside the triangle, run the Gram and scale it to cosines while the chain runs (they meet at
+// a counter, the chain's wave is not asked), and what is left between two chains is the stores (6 700 cycles with the scaling among them, about
+// 4 000 now).  2688 heads of 251 tokens, b=101 414 us one phase after the other, 220 with the Gram between the chains, 209 with the packed triangle,
+// 194 now; 8192 of 250, b=128, tight scores given 785 -> 696; 257 of 256, b=128 54.8 -> 51.2.
+// Tried: the Gram beside the chain with its operands loaded from memory in the MFMA layout: the 450 gathered loads of a head of 256 tokens take
+// 12 us whatever the prefetch depth or the bytes per row and request, the address unit spending 64 cycles on each (239 us); and no triangle
+// at all, the cosines of 32 candidates at a time from rows of V held as operands in registers, three heads per CU (238 us: twelve waves'
+// instructions per pick are more than the idle SIMDs have room for).
 // The roles are separate loops with matching barriers, not one loop with branches: registers of one role are not carried
 // through the other.
 #include "kvr_dense_common.hpp"
@@ -58,6 +64,12 @@ template <int NT> struct DenseCfg {
   static constexpr int OCC = NT == 8 ? 1 : (NT == 6 ? 2 : (NT == 4 ? 3 : 4));   // heads per CU; up to 128 tokens the registers set it, above LDS
   static constexpr int N32 = NT * 32;
   static constexpr int OFFD = NT * (NT - 1) / 2;      // tiles of the lower triangle off its diagonal
+  // One head per CU: the Gram of the next head runs beside the chain as well, on the waves 2 .. 7, its rows staged a quarter of their columns
+  // at a time in the 16 KB that the triangle leaves.
+  static constexpr bool AHEAD = NT == 8;
+  static constexpr int GW = 6, GT = NT * (NT + 1) / 2 / GW;   // (then) waves with tiles, tiles of each
+  static constexpr int kQuarter = AHEAD ? N32 * 64 : 0;
+  static_assert(!AHEAD || GT * GW == NT * (NT + 1) / 2, "equal shares");
   static constexpr int MAXD = (NT + W - 1) / W, MAXO = (OFFD + W - 1) / W;   // Gram tiles per wave, on the diagonal and off it
   static constexpr int ROWS = (N32 * 16 + 64 * (W - 2) - 1) / (64 * (W - 2));   // 16-byte row pieces per thread of waves 2 ..
   static constexpr int bcap(int b) { return (b + 63) & ~63; }
@@ -66,11 +78,11 @@ template <int NT> struct DenseCfg {
   // and 52.5.  Several heads share the LDS's store rate: 4096 of 192, b = 64 156 and 159, of 128 110 and 111; 8192 of 64 122 and 125.
   static constexpr bool PACKED = NT == 8;
   static constexpr int kTriBytes = PACKED ? dense_tri_floats(NT) * 4 : padded_tri_floats(N32) * 4;
-  static constexpr int region = N32 * kRowPitch > kTriBytes ? N32 * kRowPitch : kTriBytes;
-  // triangle or staged rows | s_l[2][N32] | rinv[N32] | lists [2][order, gain][bcap] | [2][idx][bcap], 16 bits each: with 32
+  static constexpr int region = !AHEAD && N32 * kRowPitch > kTriBytes ? N32 * kRowPitch : kTriBytes;   // (AHEAD: rows are not staged there)
+  // triangle or staged rows | quarter of the rows | s_l[2][N32] | rinv[N32] | lists [2][order, gain][bcap] | [2][idx][bcap], 16 bits each: with 32
   // two heads of 192 tokens and more than 128 picks do not fit a CU (4096 heads, n=192, b=160 412 us; now 244, and 377 before the lists came in pairs)
-  static constexpr int smem_bytes(int b) { return region + N32 * 3 * 4 + 2 * bcap(b) * (4 + 4 + 2); }
-  static_assert(OCC * (region + N32 * 3 * 4 + 2 * N32 * (4 + 4 + 2)) <= 160 * 1024, "OCC heads fit a CU at every budget");
+  static constexpr int smem_bytes(int b) { return region + kQuarter + N32 * 3 * 4 + 16 + 2 * bcap(b) * (4 + 4 + 2); }
+  static_assert(OCC * (region + kQuarter + N32 * 3 * 4 + 16 + 2 * N32 * (4 + 4 + 2)) <= 160 * 1024, "OCC heads fit a CU at every budget");
 };
 
 template <int NT>
@@ -80,10 +92,12 @@ __global__ __launch_bounds__(64 * DenseCfg<NT>::W, DenseCfg<NT>::W * DenseCfg<NT
   extern __shared__ __align__(16) char smem[];
   char* stage = smem;
   float* tri = reinterpret_cast<float*>(smem);
-  float* s_all = reinterpret_cast<float*>(smem + C::region);   // [2][N32]
+  char* quarter = smem + C::region;                     // [N32][64 B]
+  float* s_all = reinterpret_cast<float*>(quarter + C::kQuarter);   // [2][N32]
   float* rinv = s_all + 2 * N32;                        // inverse norms of the head whose triangle is being built
   const int bcap = C::bcap(a.b);
-  int32_t* lists = reinterpret_cast<int32_t*>(rinv + N32);   // [2][2][bcap]: picks in order, gains
+  int32_t* met = reinterpret_cast<int32_t*>(rinv + N32);     // [4] how often the waves with tiles have met (AHEAD)
+  int32_t* lists = met + 4;                             // [2][2][bcap]: picks in order, gains
   uint16_t* idx_all = reinterpret_cast<uint16_t*>(lists + 4 * bcap);   // [2][bcap]: ascending indices
 
   int tid = threadIdx.x, lane = tid & 63, hf = lane >> 5, l32 = lane & 31;
@@ -105,7 +119,7 @@ __global__ __launch_bounds__(64 * DenseCfg<NT>::W, DenseCfg<NT>::W * DenseCfg<NT
   auto budget = [&](int h) -> int { return a.b_h ? __builtin_amdgcn_readfirstlane(min(max(a.b_h[h], 0), b)) : b; };
   // Staged rows -> triangle, by all waves.  A wave takes its diagonal tiles first, then its share of the others, row by row:
   // the norms (Eq. 1, from the diagonal of the Gram) are worked out under the products of its first other tile.
-  auto build_triangle = [&]() {
+  auto build_triangle = [&]() __attribute__((always_inline)) {
     lds_barrier();                                      // the rows are staged
     const int o0 = wave * C::OFFD / W, cnt = (wave + 1) * C::OFFD / W - o0;
     int I0 = 1;
@@ -164,8 +178,7 @@ __global__ __launch_bounds__(64 * DenseCfg<NT>::W, DenseCfg<NT>::W * DenseCfg<NT
     lds_barrier();                                      // every wave has read its rows: the triangle takes their place
     if (need_v) {
       auto write_tile = [&](const f32x16& t, int I, int J) {
-        if constexpr (C::PACKED) write_cos_tile_rows(tri, rinv, t, I, J, lane);
-        else write_cos_tile_padded(tri, rinv, t, I, J, lane);
+        write_cos_tile_padded(tri, rinv, t, I, J, lane);
       };
 #pragma unroll
       for (int d = 0; d < C::MAXD; ++d)
@@ -179,12 +192,92 @@ __global__ __launch_bounds__(64 * DenseCfg<NT>::W, DenseCfg<NT>::W * DenseCfg<NT
     }
     lds_barrier();                                      // triangle and scores are complete: the chain starts
   };
+  // The tiles of the waves 2 .. 7 under AHEAD, row by row: tile I (I + 1) / 2 + J is row block I, column block J.
+  f32x16 acc6[C::AHEAD ? C::GT : 1];
+  int mt = 0;                                           // how often this wave should have been met
+  auto meet = [&]() __attribute__((always_inline)) {                                   // among the waves 2 .. 7, which all come here equally often
+    asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");
+    if (lane == 0) __hip_atomic_fetch_add(met, 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
+    mt += C::GW;
+    while (__hip_atomic_load(met, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP) < mt) __builtin_amdgcn_s_sleep(1);
+    asm volatile("" ::: "memory");
+  };
+  // Rows in registers -> cosines in acc6.  Sixteen rows' pieces of one number lie on sixteen different bank groups.
+  auto gram_ahead = [&](auto store_quarter) __attribute__((always_inline)) {
+    const int first = (wave - 2) * C::GT;
+    int I0 = 0;
+    while ((I0 + 1) * (I0 + 2) / 2 <= first) ++I0;
+    const int J0 = first - I0 * (I0 + 1) / 2;
+#pragma unroll
+    for (int k = 0; k < C::GT; ++k) acc6[k] = f32x16{0};
+    auto piece = [&](int block, int p) __attribute__((always_inline)) -> bf16x8 {
+      const int row = block * 32 + l32;
+      return *reinterpret_cast<const bf16x8*>(quarter + row * 64 + ((p ^ (row >> 2)) & 3) * 16);
+    };
+#pragma unroll 1
+    for (int kq = 0; kq < 4; ++kq) {
+      store_quarter(kq);
+      meet();                                           // the quarter is staged
+      int I = I0, J = J0, held = -1;
+      bf16x8 fi[2];
+#pragma unroll
+      for (int k = 0; k < C::GT; ++k) {
+        if (I != held) { fi[0] = piece(I, hf); fi[1] = piece(I, 2 + hf); held = I; }
+        acc6[k] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(piece(J, hf), fi[0], acc6[k], 0, 0, 0);
+        acc6[k] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(piece(J, 2 + hf), fi[1], acc6[k], 0, 0, 0);
+        if (++J > I) { ++I; J = 0; }
+      }
+      meet();                                           // ... and read
+    }
+    int I = I0, J = J0;
+#pragma unroll
+    for (int k = 0; k < C::GT; ++k) {
+      if (I == J) {                                     // (as in build_triangle)
+        auto pick = [](int bit, float one, float zero) { return bit ? one : zero; };
+        float v8[8], v4[4];
+#pragma unroll
+        for (int q = 0; q < 8; ++q) v8[q] = pick(l32 & 1, acc6[k][2 * q + 1], acc6[k][2 * q]);
+#pragma unroll
+        for (int q = 0; q < 4; ++q) v4[q] = pick(l32 & 2, v8[2 * q + 1], v8[2 * q]);
+        const float ss = pick(l32 & 16, pick(l32 & 8, v4[3], v4[2]), pick(l32 & 8, v4[1], v4[0]));
+        if (((l32 >> 2) & 1) == hf) rinv[I * 32 + l32] = 1.0f / (sqrtf(ss) + a.eps);
+      }
+      if (++J > I) { ++I; J = 0; }
+    }
+    meet();                                             // the norms are complete
+    I = I0; J = J0;
+#pragma unroll
+    for (int k = 0; k < C::GT; ++k) {
+      scale_cos_tile(rinv, acc6[k], I, J, lane);
+      if (++J > I) { ++I; J = 0; }
+    }
+  };
+  // Between two chains under AHEAD: the tiles into the triangle's place.
+  auto write_ahead = [&]() __attribute__((always_inline)) {
+    lds_barrier();                                      // the triangle is dead
+    if (wave >= 2 && need_v) {
+      const int first = (wave - 2) * C::GT;
+      int I = 0;
+      while ((I + 1) * (I + 2) / 2 <= first) ++I;
+      int J = first - I * (I + 1) / 2;
+#pragma unroll
+      for (int k = 0; k < C::GT; ++k) {
+        store_cos_tile(tri, acc6[k], I, J, lane);
+        if (++J > I) { ++I; J = 0; }
+      }
+    }
+    lds_barrier();                                      // triangle and scores are complete: the chain starts
+  };
   int h = next_head(blockIdx.x);
   if (h >= a.heads) return;                             // (uniform over the workgroup)
+  if constexpr (C::AHEAD) {
+    if (tid == 0) met[0] = 0;
+    lds_barrier();
+  }
 
   if (wave == 0) {
     // ---------------------------------------------------------------- the chain
-    build_triangle();
+    if constexpr (C::AHEAD) write_ahead(); else build_triangle();
     for (int par = 0; h < a.heads; par ^= 1) {
       const int h_next = next_head(h + gridDim.x);
       const int bh = budget(h), brun = bh < 1 ? 1 : bh;
@@ -194,9 +287,13 @@ __global__ __launch_bounds__(64 * DenseCfg<NT>::W, DenseCfg<NT>::W * DenseCfg<NT
       pick_chain<NQ, !C::PACKED>(s_l, tri, order_l, reinterpret_cast<float*>(order_l + bcap), n, brun, a.lambda, diverse, lane);
       sort_picks<NQ>(order_l, idx_all + par * bcap, reinterpret_cast<int32_t*>(s_l), brun, lane, nullptr);   // (the scores are dead by now)
       __builtin_amdgcn_s_setprio(0);
-      lds_barrier();                                    // the triangle of h is dead
       h = h_next;
-      if (h < a.heads) build_triangle();
+      if constexpr (C::AHEAD) {
+        if (h < a.heads) write_ahead(); else lds_barrier();   // the triangle of h is dead
+      } else {
+        lds_barrier();                                  // the triangle of h is dead
+        if (h < a.heads) build_triangle();
+      }
     }
     return;
   }
@@ -288,7 +385,7 @@ __global__ __launch_bounds__(64 * DenseCfg<NT>::W, DenseCfg<NT>::W * DenseCfg<NT
     for (int k = 0; k < ROWS; ++k)
       vrow[k] = *reinterpret_cast<const uint4*>(Vh + min((r0 >> 4) + k * (NR / 16), n - 1) * tok_bytes);
   };
-  auto store_stage = [&]() {
+  auto store_stage = [&]() __attribute__((always_inline)) {
     if (!need_v || wave == 1) return;
 #pragma unroll
     for (int k = 0; k < ROWS; ++k) {
@@ -320,9 +417,26 @@ __global__ __launch_bounds__(64 * DenseCfg<NT>::W, DenseCfg<NT>::W * DenseCfg<NT
       fetch(hh);
     }
   };
+  // (AHEAD) the threads that hold pieces of quarter kq of the rows put them down
+  auto store_quarter = [&](int kq) __attribute__((always_inline)) {
+    if (((r0 & 15) >> 2) != kq) return;
+#pragma unroll
+    for (int k = 0; k < ROWS; ++k) {
+      const int row = (r0 >> 4) + k * (NR / 16);
+      if (row < N32) *reinterpret_cast<uint4*>(quarter + row * 64 + ((r0 ^ (row >> 2)) & 3) * 16) = vrow[k];
+    }
+  };
+  auto next_triangle = [&]() __attribute__((always_inline)) {
+    if constexpr (C::AHEAD) {
+      if (need_v && wave >= 2) gram_ahead(store_quarter);
+      write_ahead();
+    } else {
+      store_stage();
+      build_triangle();
+    }
+  };
   prepare(h, s_all);
-  store_stage();
-  build_triangle();
+  next_triangle();
   int h_prev = -1;
   for (int par = 0; h < a.heads; par ^= 1) {
     const int h_next = next_head(h + gridDim.x);
@@ -332,9 +446,8 @@ __global__ __launch_bounds__(64 * DenseCfg<NT>::W, DenseCfg<NT>::W * DenseCfg<NT
     if (h_prev >= 0) output(h_prev, par ^ 1);
     if (h_next < a.heads) {
       prepare(h_next, s_all + (par ^ 1) * N32);
-      lds_barrier();                                    // the chain of h is done, its triangle dead
-      store_stage();
-      build_triangle();
+      if constexpr (!C::AHEAD) lds_barrier();           // the chain of h is done, its triangle dead
+      next_triangle();
     } else {
       lds_barrier();
       output(h, par);

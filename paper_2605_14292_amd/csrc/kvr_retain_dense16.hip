@@ -151,10 +151,21 @@ __global__ __launch_bounds__(kD16Threads, 1) void retain_dense16_kernel(Dense16A
         }
       }
       lds_barrier();                                  // staged rows are dead from here on, the norms complete
-      write_cos_tile_rows(tri, rinv, t00, 2 * P, 2 * Q, lane);
-      write_cos_tile_rows(tri, rinv, t10, 2 * P + 1, 2 * Q, lane);
-      write_cos_tile_rows(tri, rinv, t11, 2 * P + 1, 2 * Q + 1, lane);
-      if (P != Q) write_cos_tile_rows(tri, rinv, t01, 2 * P, 2 * Q + 1, lane);
+      if constexpr (NT > 6) {                         // (26.5 -> 25.8 us; with six blocks, three units fewer, 15.7 -> 16.3)
+        scale_cos_tile(rinv, t00, 2 * P, 2 * Q, lane);
+        scale_cos_tile(rinv, t10, 2 * P + 1, 2 * Q, lane);
+        scale_cos_tile(rinv, t11, 2 * P + 1, 2 * Q + 1, lane);
+        if (P != Q) scale_cos_tile(rinv, t01, 2 * P, 2 * Q + 1, lane);
+        store_cos_tile(tri, t00, 2 * P, 2 * Q, lane);
+        store_cos_tile(tri, t10, 2 * P + 1, 2 * Q, lane);
+        store_cos_tile(tri, t11, 2 * P + 1, 2 * Q + 1, lane);
+        if (P != Q) store_cos_tile(tri, t01, 2 * P, 2 * Q + 1, lane);
+      } else {
+        write_cos_tile_rows(tri, rinv, t00, 2 * P, 2 * Q, lane);
+        write_cos_tile_rows(tri, rinv, t10, 2 * P + 1, 2 * Q, lane);
+        write_cos_tile_rows(tri, rinv, t11, 2 * P + 1, 2 * Q + 1, lane);
+        if (P != Q) write_cos_tile_rows(tri, rinv, t01, 2 * P, 2 * Q + 1, lane);
+      }
     } else {
       lds_barrier();
     }
