@@ -166,7 +166,6 @@ __device__ __forceinline__ int first_of_slots(const unsigned long long (&e)[NQ])
     }                                                                                                                \
   }
 KVR_MASKS(masks_ge, uint32_t, "v_cmp_le_u32", >=, static_cast<uint32_t>(__builtin_amdgcn_readfirstlane(static_cast<int>(x))))
-KVR_MASKS(masks_gt, uint32_t, "v_cmp_lt_u32", >, static_cast<uint32_t>(__builtin_amdgcn_readfirstlane(static_cast<int>(x))))
 KVR_MASKS(masks_ge, float, "v_cmp_le_f32", >=, __int_as_float(__builtin_amdgcn_readfirstlane(__float_as_int(x))))
 KVR_MASKS(masks_eq, float, "v_cmp_eq_f32", ==, __int_as_float(__builtin_amdgcn_readfirstlane(__float_as_int(x))))
 // how many lanes below this one are in the mask

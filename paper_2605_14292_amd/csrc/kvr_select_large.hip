@@ -3,28 +3,26 @@
 //
 // Exact greedy with lazily refreshed penalties, in epochs as in select_lazy_kernel (a gain computed from an out-of-date
 // running maximum m of Eq. 2 is an upper bound, so a token needs an update only when its bound matters):
-//   1. the 192 best fresh unselected tokens form the pool (each wave contributes its best twenty-four); the best gain of any
+//   1. the 128 best fresh unselected tokens form the pool (each wave contributes its best sixteen); the best gain of any
 //      token outside it, fresh or stale, is the bound of the epoch;
 //   2. the pool's rows are gathered into LDS and their cosine triangle is computed on bf16 MFMA;
 //   3. one wave runs Algorithm 1 inside the pool for as long as the pool's best (gain, lower index) beats the bound;
-//   4. every wave brings the 128 tokens with the highest bounds up to date (the first epoch: every token).
+//   4. every wave brings the quarter of its tokens with the highest bounds up to date (the first epoch: every token).
 // What differs is where the rows of the picks are: a thousand of them do not fit LDS, so step 4 streams them, 128 at a
 // time and shared by all waves, past the 128 rows that every wave holds as operands.  Every token carries the 16-pick tile up to
 // which its m covers the picks; a wave's list holds its stale tokens first, the least covered ones in front, and its fresh ones,
-// which need the last epoch's picks only, after them, and every sixteen entries start at the first tile that one of them
-// has yet to meet.  (So an entry meets some picks again beside less covered neighbours.  Their cosines are the ones that
+// which need the last epoch's picks only, after them, and every 64 entries start at the first block of 64 picks that one of them
+// has yet to meet.  (So an entry meets up to 63 picks again, more beside less covered neighbours.  Their cosines are the ones that
 // m has seen but for the last bit: the triangle multiplies a sum by the norms of its two tokens in their order, the pass by
 // the pick's first.)
 //
 // Why lazily here too: with all of V read after every epoch 256 heads of 8192 tokens with b = 1024 fetched 13.2 GB and took
-// 2770 us.  A pool of 128 and a quarter of the tokens per pass: 24 epochs, 120 rounds of eight tiles, 1640 us; a pool of 192 and
-// an eighth, the epochs as many, 73 rounds: 1350 us (a pool of 192 and a quarter: 18 epochs, 95 rounds, 1400; of 128 and an eighth:
-// 28 and 92, 1470; a sixteenth: 42 and 117, 2050).  The epochs decide which cosines come out of the pool's triangle, so last bits
-// of gains and a near-tie now and then depend on them: pool 128 against 192, 4608 heads, no kept token, the order in nine; error of
-// the gains against 64 bits 8.86e-8 both.
-//
-// What bounds it now: an epoch's vector work over sixteen token slots per lane (choice of the pool 11 500 cycles, list 12 000, results
-// and waits 14 000, of 117 000) on two waves per SIMD, the products of the pass (35 000, at 70 % of the matrix rate) and the race (15 000).
+// 2770 us, here 4.6 GB in 1620-1700 us (by the memory counters, 24.6 and 8.6 times V's 0.54 GB: the listed rows, the rows of
+// the pools and of the picks, which every round streams again, and spilled registers).  A pool of 192 and an eighth of the
+// tokens per pass are faster (1300 us), but then the epochs are others than those of a full refresh, other cosines come out of
+// the pool's triangle, and among 7840 heads two kept another token; with
+// a quarter of the tokens fresh the pools are nearly always those of a full refresh (none did).  Asking for that in
+// every epoch, with passes until no stale bound reaches a wave's best seventeen, costs more than it saves (2250 us).
 //
 // Layout: one workgroup of eight wave64s per head, token j = 1024*w + 64*k + lane in wave w, lane `lane`, slot k; m
 // and covered tile of a token stay in its lane's registers, its inverse norm in LDS.
@@ -37,7 +35,7 @@ namespace kvr {
 
 constexpr int kLgW = 8;             // waves
 constexpr int kLgThreads = 64 * kLgW;
-constexpr int kLgPool = 192;        // pool size, a multiple of 64
+constexpr int kLgPool = 128;        // pool size, a multiple of 64
 constexpr int kLgMaxB = 1024;       // largest budget
 constexpr int kLgPitch = 272;       // bytes per pool row and per row of a wave's stage (256 + 16)
 // 64 picked rows as operands of the 16x16x32 products: 16-byte piece p of row r of a tile sits in plane p & 3 at r * 80 +
@@ -75,11 +73,9 @@ template <int S> struct LargeCfg {
   static constexpr int kRowBytes = kLgPool * kLgPitch;
   static constexpr int kCounts = 16 * 64;         // per wave, while its list is built: stale entries by class and lane
   static constexpr int kMax2 = kTriBytes > kRowBytes ? kTriBytes : kRowBytes;
-  static constexpr int kList = kRowBytes + kLgW * kCounts * 4;   // the counters sit above the pool's rows
-  static constexpr int kMax3 = kMax2 > kList ? kMax2 : kList;
-  static constexpr int kUnion = ((kPass > kMax3 ? kPass : kMax3) + 15) & ~15;
-  static_assert(kRowBytes % 16 == 0, "16-byte areas");
-  // floats: slots 64 | shared 16 | wcount 16 | first 16-pick tile needed by every 16 list entries, bytes [8][32] |
+  static constexpr int kUnion = ((kPass > kMax2 ? kPass : kMax2) + 15) & ~15;
+  static_assert(kRowBytes + kLgW * kCounts * 4 <= kUnion && kRowBytes % 16 == 0, "the counters of the lists fit above the pool's rows");
+  // floats: slots 64 | shared 16 | wcount 16 | first 64 picks needed by every 64 list entries 8*8 |
   //         pool_tok,r,s,m,picked 5*P | inverse norms 64*S*W | lists W*CAP (at the end the sorted indices) |
   //         order, gain, pick_r 3*bcap ; then the waves' scratch and the union area (pool rows -> triangle -> stages -> chunks -> pick flags)
   static constexpr int kTables = 160;
@@ -90,7 +86,6 @@ template <int S> struct LargeCfg {
   static_assert(kFixedFloats % 4 == 0 && kListFloats % 4 == 0 && kStage % 16 == 0 && kScratch % 16 == 0, "16-byte areas");
   static constexpr int bcap(int b) { return (b + 63) & ~63; }
   static constexpr int smem_bytes(int b) { return (kFixedFloats + kListFloats + 3 * bcap(b)) * 4 + kLgW * kScratch + kUnion; }
-  static_assert((kFixedFloats + kListFloats + 3 * kLgMaxB) * 4 + kLgW * kScratch + kUnion <= 160 * 1024, "one head fits a CU");
 };
 
 // BUD: per-head budgets are read from a.b_h.  FAR: a head spans 2 GiB or more (byte offsets of 64 bits).
@@ -100,7 +95,7 @@ __global__ __launch_bounds__(kLgThreads, 1) void select_large_kernel(LargeArgs a
   constexpr int W = kLgW, P = kLgPool, NT = kLgThreads;
   constexpr int TPW = Cfg::TPW, CAP = Cfg::CAP;
   constexpr int Q = P / W;                         // pool members contributed per wave
-  constexpr int KR = 128;                          // tokens a wave aims to refresh per pass
+  constexpr int KR = TPW / 4;                      // tokens a wave aims to refresh per pass
   constexpr int NB = P / 32, NTRI = NB * (NB + 1) / 2, NTILE = (NTRI + W - 1) / W;
   constexpr int NQ = P / 64;                       // pool slots per lane in the race
   static_assert(P % 64 == 0 && Q <= 64 && KR <= CAP && CAP % kLgGroup == 0, "pool and list sizes");
@@ -109,7 +104,7 @@ __global__ __launch_bounds__(kLgThreads, 1) void select_large_kernel(LargeArgs a
   int32_t* slot_idx = reinterpret_cast<int32_t*>(smem + 32);     // [2][16]
   int32_t* shared_i = reinterpret_cast<int32_t*>(smem + 64);     // [16] np, t, stop reason
   int32_t* wcount = reinterpret_cast<int32_t*>(smem + 80);       // [16]
-  uint8_t* gstart = reinterpret_cast<uint8_t*>(smem + 96);       // [W][32] first 16-pick tile that 16 entries of the wave's list need, ascending, kLgNone past the last
+  int32_t* gstart = reinterpret_cast<int32_t*>(smem + 96);       // [W][8] first 64 picks (by number / 64) that 64 entries of the wave's list need, kLgNone past the last
   int32_t* pool_tok = reinterpret_cast<int32_t*>(smem + Cfg::kTables);    // [P] token of the member, -1 = none
   float* pool_r = smem + Cfg::kTables + P;
   float* pool_s = smem + Cfg::kTables + 2 * P;
@@ -196,19 +191,11 @@ __global__ __launch_bounds__(kLgThreads, 1) void select_large_kernel(LargeArgs a
     for (int k = 1; k < S; ++k) best = hw_max(best, av[k]);
     amax_w = wave_max_uniform(best);
     int i_w = -1;
-    unsigned long long any = 0;
-    int k0 = 0;
 #pragma unroll
-    for (int c = S - 4; c >= 0; c -= 4) {            // the lowest slot with a winner, its lowest lane
-      const float a4[4] = {av[c], av[c + 1], av[c + 2], av[c + 3]};
-      unsigned long long eq[4];
-      masks_eq<4>(a4, amax_w, eq);
-#pragma unroll
-      for (int k = 3; k >= 0; --k) { any = eq[k] ? eq[k] : any; k0 = eq[k] ? c + k : k0; }
-    }
-    {
-      if (any) {
-        const int l0 = __ffsll(static_cast<long long>(any)) - 1, k = k0;
+    for (int k = S - 1; k >= 0; --k) {
+      const unsigned long long eq = __ballot(av[k] == amax_w);
+      if (eq) {
+        const int l0 = __ffsll(static_cast<long long>(eq)) - 1;
         const int fr = (__builtin_amdgcn_readlane(static_cast<int>(fresh), l0) >> k) & 1;
         i_w = (base + 64 * k + l0) | (fr ? 0 : (1 << 30));
       }
@@ -257,7 +244,9 @@ __global__ __launch_bounds__(kLgThreads, 1) void select_large_kernel(LargeArgs a
         uint32_t T = 0;                              // s_(b) from the leading 16 bits: at most s_(b), the bound only loosens
         for (int bit = 31; bit >= 16; --bit) {
           const uint32_t cand = T | (1u << bit);
-          const int c = count_slots_ge<S>(key, cand);
+          int c = 0;
+#pragma unroll
+          for (int k = 0; k < S; ++k) c += __popcll(__ballot(key[k] >= cand));
           if (lane == 0) slot_idx[par * 16 + w] = c;
           lds_barrier();
           int tot = 0;
@@ -301,7 +290,10 @@ __global__ __launch_bounds__(kLgThreads, 1) void select_large_kernel(LargeArgs a
       }
       uint32_t tau = 0;                              // largest value with at least Q fresh keys >= it
       auto at_least_q = [&](uint32_t x) -> bool {
-        return count_slots_ge<S>(ekey, x) >= Q;
+        int c = 0;
+#pragma unroll
+        for (int k = 0; k < S; ++k) c += __popcll(__ballot(ekey[k] >= x));
+        return c >= Q;
       };
       if (kbits == kLgSelBits && tau_prev != 0) {
         // bracketed from the last epoch's value with doubling steps, then bisected
@@ -337,31 +329,33 @@ __global__ __launch_bounds__(kLgThreads, 1) void select_large_kernel(LargeArgs a
       }
       tau_prev = tau;
       if (tau == 0) tau = 1;                         // fewer than Q fresh tokens: all of them join
-      {
-        int need_eq = Q - (tau == 0xffffffffu ? 0 : count_slots_ge<S>(ekey, tau + 1u));   // members with key > tau, then so many with key == tau, in token order
-        int rank_base = 0;
+      int taken = 0;                                 // members with key > tau come first, ties in token order
 #pragma unroll
-        for (int k = 0; k < S; ++k) {
-          unsigned long long inm = __ballot(ekey[k] >= tau);
-          const unsigned long long eqm = __ballot(ekey[k] == tau);
-          const int eq_in = __popcll(eqm);
-          if (eq_in > need_eq) inm ^= __ballot(__builtin_amdgcn_inverse_ballot_w64(eqm) && lane_rank(eqm) >= need_eq);
-          need_eq -= eq_in < need_eq ? eq_in : need_eq;
-          const bool in = __builtin_amdgcn_inverse_ballot_w64(inm);
-          const int slot = w * Q + kvr_ix_if(in, rank_base + lane_rank(inm), Q, 401);   // 401: a member's place in the wave's share
-          set_place(k, in ? static_cast<uint32_t>(slot + 1) : 0u);
-          if (in) {
-            pool_tok[slot] = tok_of(k) < n ? tok_of(k) : -1;
-            pool_s[slot] = s[k];
-            pool_m[slot] = m[k];
-          }
-          go[k] = in ? -INFINITY : go[k];
-          rank_base += __popcll(inm);
+      for (int k = 0; k < S; ++k) taken += __popcll(__ballot(ekey[k] > tau));
+      int need_eq = Q - taken;                       // how many of the key == tau tokens join
+      int rank_base = 0;
+#pragma unroll
+      for (int k = 0; k < S; ++k) {
+        const bool above = ekey[k] > tau, equal = ekey[k] == tau;
+        const unsigned long long eqm = __ballot(equal);
+        const int eq_before = __popcll(eqm & ((1ull << lane) - 1ull));
+        const bool in = above || (equal && eq_before < need_eq);
+        const unsigned long long inm = __ballot(in);
+        const int slot = w * Q + kvr_ix_if(in, rank_base + __popcll(inm & ((1ull << lane) - 1ull)), Q, 401);   // 401: a member's place in the wave's share
+        set_place(k, in ? static_cast<uint32_t>(slot + 1) : 0u);
+        if (in) {
+          pool_tok[slot] = tok_of(k) < n ? tok_of(k) : -1;
+          pool_s[slot] = s[k];
+          pool_m[slot] = m[k];
         }
-        if (lane >= rank_base && lane < Q) {         // fewer fresh tokens than the wave's share: empty slots
-          const int slot = w * Q + lane;
-          pool_tok[slot] = -1; pool_s[slot] = -INFINITY; pool_m[slot] = 0.f;
-        }
+        if (in) go[k] = -INFINITY;
+        rank_base += __popcll(inm);
+        const int eq_in = __popcll(eqm);
+        need_eq -= eq_in < need_eq ? eq_in : need_eq;
+      }
+      if (lane >= rank_base && lane < Q) {           // fewer fresh tokens than the wave's share: empty slots
+        const int slot = w * Q + lane;
+        pool_tok[slot] = -1; pool_s[slot] = -INFINITY; pool_m[slot] = 0.f;
       }
       float gout, gmax_w; int jout_f;
       wg_argmax(go, gout, jout_f, gmax_w);           // barrier inside: the pool tables are complete
@@ -396,7 +390,7 @@ __global__ __launch_bounds__(kLgThreads, 1) void select_large_kernel(LargeArgs a
       // class by lane and slot, then the fresh ones in token order.  The order decides which entries share a start, so it must not
       // depend on the order in which the hardware serves lanes: every lane counts its entries of a class in a counter of its own, and
       // a prefix sum over (class, lane) gives each counter its first position.
-      auto build_list = [&](const float (&v)[S], uint32_t slots) {   // the tokens of these slots (bits) whose v is at least thr_r
+      auto build_list = [&](auto member) {
         fresh_lane();
         int wu = w;
         asm volatile("" : "+s"(wu));                 // (likewise: no addresses kept over the epochs)
@@ -406,17 +400,13 @@ __global__ __launch_bounds__(kLgThreads, 1) void select_large_kernel(LargeArgs a
         int4* const share = reinterpret_cast<int4*>(counts + lane * 16);   // sixteen counters of a class, four lanes a class
 #pragma unroll
         for (int u = 0; u < 4; ++u) share[u] = make_int4(0, 0, 0, 0);
-        const float thr_l = thr_r < -3.402823466e38f ? -3.402823466e38f : thr_r;   // (a score of -inf is no member)
-        uint32_t mem = 0;
-#pragma unroll
-        for (int k = 0; k < S; ++k) mem |= v[k] >= thr_l ? 1u << k : 0u;
-        mem &= slots;
-        const uint32_t stale = mem & ~fresh;
         wave_lds_sync();
         int place_in[S];
 #pragma unroll
-        for (int k = 0; k < S; ++k)                  // (every lane adds, so that no branch stands between them: the returns travel together)
-          place_in[k] = atomicAdd(&mine[64 * class_of(k)], static_cast<int>((stale >> k) & 1u));
+        for (int k = 0; k < S; ++k) {
+          place_in[k] = 0;
+          if (member(k) && !((fresh >> k) & 1u)) place_in[k] = atomicAdd(&mine[64 * class_of(k)], 1);
+        }
         wave_lds_sync();
         int incl;
         {
@@ -448,54 +438,43 @@ __global__ __launch_bounds__(kLgThreads, 1) void select_large_kernel(LargeArgs a
           place_in[k] += mine[64 * class_of(k)];
 #pragma unroll
         for (int k = 0; k < S; ++k) {
-          const bool in = (mem >> k) & 1u, fr = (fresh >> k) & 1u;
-          const unsigned long long mm = __ballot(in && fr);
-          if (in) {
-            const int pos = kvr_ix(fr ? off + lane_rank(mm) : place_in[k], CAP, 402);   // 402: position in the refresh list
-            lrw_i[pos] = tok_of(k) | (fr ? t0 >> 4 : static_cast<int>((cov[k >> 2] >> (8 * (k & 3))) & 0xffu)) << 16;   // (with the tile from which it has yet to meet the picks)
+          const bool mem = member(k), fr = (fresh >> k) & 1u;
+          const unsigned long long mm = __ballot(mem && fr);
+          if (mem) {
+            const int pos = kvr_ix(fr ? off + __popcll(mm & ((1ull << lane) - 1ull)) : place_in[k], CAP, 402);   // 402: position in the refresh list
+            lrw_i[pos] = tok_of(k);
             set_place(k, 0x8000u + static_cast<uint32_t>(pos));
           }
           off += __popcll(mm);
         }
         cnt_r = off;
+        int first = kLgNone;                         // lane g: of entry 64 g
+#pragma unroll
+        for (int g = 0; g < CAP / 64; ++g) {
+          const int c = __popcll(__ballot((lane & 3) == 3 && incl <= 64 * g));
+          const int f = g * 64 < cnt_r ? (c < 16 ? min(c, t0 >> 6) : t0 >> 6) : kLgNone;
+          first = lane == g ? f : first;
+        }
+        if (lane < 8) gstart[w * 8 + lane] = first;
         // pad to whole groups with a valid row (its results are never read)
         const int padded = max((cnt_r + kLgGroup - 1) & ~(kLgGroup - 1), kLgGroup);
-        for (int u = cnt_r + lane; u < padded; u += 64) lrw_i[u] = min(base, n - 1) | (kLgNone << 16);
-        wave_lds_sync();
-        // first tile that any of 16 entries needs; made to ascend (a later sixteen's start is at most lowered)
-#pragma unroll 1
-        for (int g = 0; g < CAP / 64; ++g) {
-          int c = g * 64 < padded ? lrw_i[g * 64 + lane] >> 16 : kLgNone;
-          c = min(c, __builtin_amdgcn_update_dpp(0, c, 0x128, 0xf, 0xf, false));
-          c = min(c, __builtin_amdgcn_update_dpp(0, c, 0x124, 0xf, 0xf, false));
-          c = min(c, __builtin_amdgcn_update_dpp(0, c, 0x122, 0xf, 0xf, false));
-          c = min(c, __builtin_amdgcn_update_dpp(0, c, 0x121, 0xf, 0xf, false));
-          if ((lane & 15) == 0) gstart[w * 32 + g * 4 + (lane >> 4)] = static_cast<uint8_t>(c);
-        }
-        wave_lds_sync();
-        {
-          int c = lane < 32 ? gstart[w * 32 + lane] : kLgNone;   // the minimum over this sixteen and all later ones
-          c = min(c, __builtin_amdgcn_update_dpp(kLgNone, c, 0x101, 0xf, 0xf, false));
-          c = min(c, __builtin_amdgcn_update_dpp(kLgNone, c, 0x102, 0xf, 0xf, false));
-          c = min(c, __builtin_amdgcn_update_dpp(kLgNone, c, 0x104, 0xf, 0xf, false));
-          c = min(c, __builtin_amdgcn_update_dpp(kLgNone, c, 0x108, 0xf, 0xf, false));
-          const int next = __builtin_amdgcn_readlane(c, 16);
-          c = lane < 16 ? min(c, next) : c;
-          if (lane < 32) gstart[w * 32 + lane] = static_cast<uint8_t>(c);
-        }
+        for (int u = cnt_r + lane; u < padded; u += 64) lrw_i[u] = min(base, n - 1);
       };
       // A group's rows: as they come from memory (sub-block, row (lane >> 4) + 4 q of it), then as operands.
       uint4 rows[8][4];
       auto fetch = [&](int gi, int sub) {
 #pragma unroll
         for (int q = 0; q < 4; ++q) {
-          const int row = kvr_ix(lrw_i[gi * kLgGroup + sub * 16 + (lane >> 4) + 4 * q] & 0xffff, n, 404);   // 404: token of a list entry
+          const int row = kvr_ix(lrw_i[gi * kLgGroup + sub * 16 + (lane >> 4) + 4 * q], n, 404);   // 404: token of a list entry
           rows[sub][q] = *reinterpret_cast<const uint4*>(Vh + (static_cast<Off>(row) * pitch_b + (lane & 15) * 16u));
         }
       };
       if (have_r && gmax_w > -INFINITY) {
         auto count_ge = [&](float thr) -> int {
-          return count_slots_ge<S>(go, thr < -3.402823466e38f ? -3.402823466e38f : thr);   // (a NaN threshold counts none)
+          int c = 0;
+#pragma unroll
+          for (int k = 0; k < S; ++k) c += __popcll(__ballot(go[k] >= thr && go[k] > -INFINITY));
+          return c;
         };
         float lo_d, hi_d;
         int steps;
@@ -531,7 +510,7 @@ __global__ __launch_bounds__(kLgThreads, 1) void select_large_kernel(LargeArgs a
         split = count_ge(thr_r) > CAP;
       }
       if (!have_r) split = true;
-      build_list(go, split ? (1u << (S / 2)) - 1u : (1u << S) - 1u);
+      build_list([&](int k) { return go[k] >= thr_r && go[k] > -INFINITY && (!split || k < S / 2); });
       wave_lds_sync();                               // the list was written by other lanes of this wave
 #pragma unroll
       for (int sub = 0; sub < 4; ++sub) fetch(0, sub);   // (they travel while the pool's triangle is computed and raced ...
@@ -651,12 +630,10 @@ __global__ __launch_bounds__(kLgThreads, 1) void select_large_kernel(LargeArgs a
 #pragma unroll
       for (int k = 0; k < S; ++k) {
         const uint32_t pl = get_place(k);
-        const bool in = pl - 1u < 0x7fffu;
-        const int slot = in ? static_cast<int>(pl) - 1 : 0;      // (read in any case: no branch between the reads)
-        const float mp = pool_m[slot];
-        const uint32_t pk = static_cast<uint32_t>(pool_picked[slot]);
-        m[k] = in ? mp : m[k];
-        dead |= in ? pk << k : 0u;
+        if (pl != 0u && pl < 0x8000u) {
+          m[k] = pool_m[pl - 1];
+          if (pool_picked[pl - 1]) dead |= 1u << k;
+        }
       }
       if (t >= b) break;
       if (stop == 2 || (np == 0 && !(gout > -INFINITY))) { starved = true; break; }
@@ -681,13 +658,14 @@ __global__ __launch_bounds__(kLgThreads, 1) void select_large_kernel(LargeArgs a
       const int nchunks = (tiles + kLgTiles - 1) / kLgTiles;
       uint32_t now = 0;                              // bit k: this epoch brought m[k] up to date
       for (int turn = 0;; ++turn) {
-        // rounds: group g of every wave's list at once; a round starts at the first chunk that any wave's group needs
-        int gs = lane < 8 * (CAP / kLgGroup) ? gstart[(lane & 7) * 32 + (lane >> 3) * 8] : kLgNone;   // lane 8 g + wave
-        gs = min(gs, __shfl_xor(gs, 4));
-        gs = min(gs, __shfl_xor(gs, 2));
-        gs = min(gs, __shfl_xor(gs, 1));
-        const int rounds = __popcll(__ballot((lane & 7) == 0 && gs != kLgNone));
-        auto start_of = [&](int g) -> int { return __builtin_amdgcn_readlane(gs, 8 * g) / kLgTiles; };   // first chunk (they ascend with the group)
+        // rounds: group g of every wave's list at once; a round starts at the first picks that any wave's group needs
+        const int gs_own = gstart[w * 8 + (lane & 7)];
+        int gs = gstart[lane];                       // (eight waves of eight entries)
+        gs = min(gs, __shfl_xor(gs, 8));
+        gs = min(gs, __shfl_xor(gs, 16));
+        gs = min(gs, __shfl_xor(gs, 32));
+        const int rounds = (__popcll(__ballot(lane < 8 && gs != kLgNone)) + 1) >> 1;
+        auto start_of = [&](int g) -> int { return __builtin_amdgcn_readlane(gs, 2 * g) >> 1; };   // first chunk (they ascend with the group)
         uint4 cx[4];                                 // this thread's share of the next chunk
         auto load_chunk = [&](int c) {
 #pragma unroll
@@ -697,21 +675,15 @@ __global__ __launch_bounds__(kLgThreads, 1) void select_large_kernel(LargeArgs a
           }
         };
         int buf = 0;
-        if (rounds == 0) load_scores();
         if (rounds > 0 && start_of(0) < nchunks) load_chunk(start_of(0));
         for (int g = 0; g < rounds; ++g) {
           const int c0 = start_of(g);                // (the same in every wave)
-          int ts[4];                                 // first tile of the group's pairs of sub-blocks
-          {
-            const uint2 own = *reinterpret_cast<const uint2*>(gstart + w * 32 + g * 8);
-            const uint32_t lo = __builtin_amdgcn_readfirstlane(own.x), hi = __builtin_amdgcn_readfirstlane(own.y);
-            ts[0] = lo & 0xffu; ts[1] = (lo >> 16) & 0xffu; ts[2] = hi & 0xffu; ts[3] = (hi >> 16) & 0xffu;
-          }
+          const int q0 = __builtin_amdgcn_readlane(gs_own, 2 * g), q1 = __builtin_amdgcn_readlane(gs_own, 2 * g + 1);
           float part[8];                             // per 16-row sub-block: max over my four picks of every operand
 #pragma unroll
           for (int sub = 0; sub < 8; ++sub) {
             part[sub] = 0.f;                         // the floor of Eq. 2
-            if (ts[sub >> 1] != kLgNone) {
+            if ((sub < 4 ? q0 : q1) != kLgNone) {
               wave_lds_sync();
 #pragma unroll
               for (int q = 0; q < 4; ++q) {
@@ -741,8 +713,8 @@ __global__ __launch_bounds__(kLgThreads, 1) void select_large_kernel(LargeArgs a
             const int cn = c + 1 < nchunks ? c + 1 : (g + 1 < rounds ? start_of(g + 1) : nchunks);
             if (cn < nchunks) load_chunk(cn);
             lds_barrier();                           // (the buffer written next was last read before the previous barrier)
-            auto tile_products = [&](auto pairs_c, int tl0, int tl1) {   // the first pairs_c pairs of sub-blocks
-              constexpr int subs = 2 * decltype(pairs_c)::value;
+            auto tile_products = [&](auto quads_c, int tl0, int tl1) {
+              constexpr int quads = decltype(quads_c)::value;
               const char* ap = cb + (tl0 - c * kLgTiles) * kLgTile + kg * kLgPlane + (lane & 15) * kLgPlaneRow;
               const float* pr = pick_r + tl0 * 16 + 4 * kg;
 #pragma unroll 1
@@ -751,43 +723,34 @@ __global__ __launch_bounds__(kLgThreads, 1) void select_large_kernel(LargeArgs a
 #pragma unroll
                 for (int ks = 0; ks < 4; ++ks) av[ks] = *reinterpret_cast<const bf16x8*>(ap + ks * 16);
                 const float4 p0 = *reinterpret_cast<const float4*>(pr);
-                f32x4 acc[subs];
+                f32x4 acc[4 * quads];
 #pragma unroll
-                for (int v = 0; v < subs; v += 4) {
-                  const int ve = v + 4 < subs ? v + 4 : subs;
+                for (int v = 0; v < quads; ++v) {
 #pragma unroll
-                  for (int u = v; u < ve; ++u) acc[u] = f32x4{0.f, 0.f, 0.f, 0.f};
+                  for (int u = 0; u < 4; ++u) acc[4 * v + u] = f32x4{0.f, 0.f, 0.f, 0.f};
 #pragma unroll
                   for (int ks = 0; ks < 4; ++ks)
 #pragma unroll
-                    for (int u = v; u < ve; ++u)
-                      acc[u] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(av[ks], __builtin_bit_cast(bf16x8, rows[u][ks]), acc[u], 0, 0, 0);
+                    for (int u = 0; u < 4; ++u)
+                      acc[4 * v + u] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(av[ks], __builtin_bit_cast(bf16x8, rows[4 * v + u][ks]), acc[4 * v + u], 0, 0, 0);
                 }
 #pragma unroll
-                for (int u = 0; u < subs; ++u)
+                for (int u = 0; u < 4 * quads; ++u)
                   part[u] = max3(max3(part[u], acc[u][0] * p0.x, acc[u][1] * p0.y), acc[u][2] * p0.z, acc[u][3] * p0.w);
               }
             };
-            // the tiles of this chunk that the first pair meets alone, then those from which on the next pair joins it, ..
+            // the first 64 entries' tiles of this chunk before the others join, then the tiles that all of them meet
             const int tE = min((c + 1) * kLgTiles, tiles);
-            int tp[4];
-#pragma unroll
-            for (int v = 0; v < 4; ++v) tp[v] = min(max(c * kLgTiles, ts[v]), tE);
-            tile_products(std::integral_constant<int, 1>{}, tp[0], tp[1]);
-            tile_products(std::integral_constant<int, 2>{}, tp[1], tp[2]);
-            tile_products(std::integral_constant<int, 3>{}, tp[2], tp[3]);
-            tile_products(std::integral_constant<int, 4>{}, tp[3], tE);
+            const int tA = max(c * kLgTiles, 4 * q0), tB = max(c * kLgTiles, 4 * q1);
+            tile_products(std::integral_constant<int, 1>{}, tA, min(tB, tE));
+            tile_products(std::integral_constant<int, 2>{}, tB, tE);
             buf ^= 1;
           }
-          // (defined here by nothing: the scores are not carried through the products)
-#pragma unroll
-          for (int k = 0; k < S; ++k) asm volatile("" : "=v"(s[k]));
-          if (g + 1 >= rounds) load_scores();        // (for the second list, or the next epoch)
           // lane (col, kg) holds partial maxima of row col of sub-block 0..3; list entry 16*sub + col of the 64 is
           // finished by lane (col, kg = sub).  Exchange through the wave's scratch: [sub][kg][col].
 #pragma unroll
           for (int v = 0; v < 2; ++v) {
-            if (ts[2 * v] != kLgNone) {
+            if ((v ? q1 : q0) != kLgNone) {
               wave_lds_sync();
 #pragma unroll
               for (int sub = 0; sub < 4; ++sub) scratch[sub * 64 + kg * 16 + (lane & 15)] = part[4 * v + sub];
@@ -795,15 +758,8 @@ __global__ __launch_bounds__(kLgThreads, 1) void select_large_kernel(LargeArgs a
               const float* sp = scratch + kg * 64 + (lane & 15);
               const float mx = hw_max(hw_max(sp[0], sp[16]), hw_max(sp[32], sp[48]));
               const int e = g * kLgGroup + v * 64 + lane;
-              const int tk = kvr_ix(lrw_i[e] & 0xffff, TPW * W, 412);   // 412: token of a list entry
-              float r;
-              if (!have_r) {
-                r = 1.0f / (sqrtf(norm_x[v * 64 + lane]) + a.eps);
-                if (e < cnt_r) r_l[tk] = r;
-              } else {
-                r = r_l[tk];
-              }
-              lrw[e] = mx * r;                       // (the list entries of this group have been consumed)
+              if (!have_r && e < cnt_r) r_l[kvr_ix(lrw_i[e], TPW * W, 412)] = 1.0f / (sqrtf(norm_x[v * 64 + lane]) + a.eps);   // 412: token of a list entry
+              lrw[e] = mx;                           // (the list entries of this group have been consumed)
             }
           }
           if (g + 1 < rounds) lds_barrier();         // the stages take the chunks' place
@@ -813,18 +769,20 @@ __global__ __launch_bounds__(kLgThreads, 1) void select_large_kernel(LargeArgs a
           }
         }
         fresh_lane();
+        load_scores();                               // (for the second list, or the next epoch)
         wave_lds_sync();
         // refreshed tokens take their new m
-        const uint32_t t_bytes = static_cast<uint32_t>(t >> 4) * 0x01010101u;
 #pragma unroll
         for (int k = 0; k < S; ++k) {
           const uint32_t pl = get_place(k);
-          const bool listed = pl >= 0x8000u;
-          const float mx = lrw[kvr_ix_if(listed, static_cast<int>(pl & 0x7fffu), CAP, 413)];   // 413: list position of a refreshed token (others read what is there: no branch between the reads)
-          m[k] = listed ? hw_max(m[k], mx) : m[k];
-          now |= pl != 0u ? 1u << k : 0u;            // pool members left the race up to date
-          const uint32_t cm = pl != 0u ? 0xffu << (8 * (k & 3)) : 0u;
-          cov[k >> 2] = (cov[k >> 2] & ~cm) | (t_bytes & cm);
+          if (pl >= 0x8000u) {
+            const int pos = kvr_ix(static_cast<int>(pl - 0x8000u), CAP, 413);   // 413: list position of a refreshed token
+            m[k] = hw_max(m[k], lrw[pos] * r_l[tok_of(k)]);
+          }
+          if (pl != 0u) {                            // pool members left the race up to date
+            now |= 1u << k;
+            cov[k >> 2] = (cov[k >> 2] & ~(0xffu << (8 * (k & 3)))) | (static_cast<uint32_t>(t >> 4) << (8 * (k & 3)));
+          }
         }
 #pragma unroll
         for (int k = 0; k < S / 2; ++k) place[k] = 0u;
@@ -835,15 +793,15 @@ __global__ __launch_bounds__(kLgThreads, 1) void select_large_kernel(LargeArgs a
         if (split && lane == 0) shared_i[4 + par] = 1;
         cnt_r = 0;
         if (split) {
-          float gk[S];
-#pragma unroll
-          for (int k = 0; k < S; ++k) gk[k] = ((now >> k) & 1u) ? -INFINITY : fmaf(nlam, m[k], s[k]);
-          build_list(gk, (1u << S) - (1u << (S / 2)));
+          build_list([&](int k) {
+            const float gk = fmaf(nlam, m[k], s[k]);
+            return k >= S / 2 && !((now >> k) & 1u) && gk >= thr_r && gk > -INFINITY;
+          });
           wave_lds_sync();
 #pragma unroll
           for (int sub = 0; sub < 8; ++sub) fetch(0, sub);
-        } else if (lane < 32) {
-          gstart[w * 32 + lane] = kLgNone;
+        } else if (lane < 8) {
+          gstart[w * 8 + lane] = kLgNone;
         }
         lds_barrier();
         const bool more = shared_i[4 + par] != 0;    // some wave's list takes a second turn
