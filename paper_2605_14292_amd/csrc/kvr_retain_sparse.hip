@@ -43,6 +43,17 @@ __host__ __device__ constexpr int sparse_smem_bytes(int NT) {
   return dense_region_a(NT) + NT * 32 * 4 * 3 + 192 * 4 + kSpMaxB * 4 * 3;
 }
 
+// inclusive prefix sum over the lanes
+__device__ __forceinline__ int wave_prefix(int v) {
+  v += __builtin_amdgcn_update_dpp(0, v, 0x111, 0xf, 0xf, false);
+  v += __builtin_amdgcn_update_dpp(0, v, 0x112, 0xf, 0xf, false);
+  v += __builtin_amdgcn_update_dpp(0, v, 0x114, 0xf, 0xf, false);
+  v += __builtin_amdgcn_update_dpp(0, v, 0x118, 0xf, 0xf, false);
+  v += __builtin_amdgcn_update_dpp(0, v, 0x142, 0xa, 0xf, false);
+  v += __builtin_amdgcn_update_dpp(0, v, 0x143, 0xc, 0xf, false);
+  return v;
+}
+
 // NT: capacity 32*NT survivors.  S: score slots per thread, n <= 256*S.
 template <int NT, int S>
 __global__ __launch_bounds__(kDenseThreads, (NT <= 4 ? 4 : 2)) void retain_sparse_kernel(SparseArgs a) {
@@ -87,7 +98,6 @@ __global__ __launch_bounds__(kDenseThreads, (NT <= 4 ? 4 : 2)) void retain_spars
     int tid = tid0;
     asm volatile("" : "+v"(tid));                    // (per-lane LDS addresses are recomputed per head, not kept in registers)
     const int lane = tid & 63, hf = lane >> 5;
-    const unsigned long long below = (1ull << lane) - 1ull;
     float sv[S];
 #pragma unroll
     for (int k = 0; k < S; ++k) sv[k] = spre[k];
@@ -119,32 +129,25 @@ __global__ __launch_bounds__(kDenseThreads, (NT <= 4 ? 4 : 2)) void retain_spars
     unsigned long long km[S];
     float excl = -INFINITY;                          // best score among the candidates left out (none: -inf)
     if (!marked) {
-      uint32_t key[S];
+      auto key = [&](int k) -> uint32_t {             // (padding is below every finite score)
+        float x = sv[k];
+        if constexpr (S > 12) asm volatile("" : "+v"(x));   // sixteen keys are worked out where they are used, fewer are kept: 155.4 -> 152.8 us on 2048 heads of 4096, b = 128
+        return ordered_key(x + 0.0f);
+      };
+      // s_(b) and the cut, both to the leading 16 key bits.  A histogram in 1024 bins of 2^sh values of these bits from `from` up (what is
+      // above falls into the last bin, what is below is left out), summed from the top: hb[0] is the bin in which b tokens are reached,
+      // hb[1] the one in which N32 + 1 are (-1: never).
+      // (A search bit by bit took 16 counts over all slots and as many barriers: 12 400 cycles of a head's 88 000 for n = 3001.)
+      auto histogram = [&](uint32_t from, int sh) {
 #pragma unroll
-      for (int k = 0; k < S; ++k) key[k] = k * 256 + tid < n ? ordered_key(sv[k] + 0.0f) : 0u;
-      // A histogram of the leading 16 key bits from the lowest finite score up (two or more values a bin where 1024 bins would
-      // not reach the best one; infinities and NaNs above it fall into the last bin), summed from the top: hb[0] is the lowest bin with
-      // which b tokens are reached, hb[1] the one with which more than N32 are (-1: never).
-      // (A search bit by bit took 16 counts over all slots and as many barriers: 12 400 cycles of a head's 88 000 for n = 3001.  With the
-      // triangle's stores from one base address, the kept rows of b > 64 in one batch and twelve slots up to 3072 tokens: 1024 heads of 3001, b = 128
-      // 85.6 -> 74.0 us; 7168 of 1024 521 -> 464, with b = 64 174 -> 155; 1024 of 2900, b = 64 37.0 -> 30.0.)
-      const uint32_t kl = ordered_key(glo + 0.0f) >> 16, range = (ordered_key(ghi + 0.0f) >> 16) - kl;
-      const int sh = max(0, 22 - __clz(static_cast<int>(range)));   // range >> sh < 1024
-#pragma unroll
-      for (int k = 0; k < S; ++k)
-        if (key[k] >> 16 >= kl) atomicAdd(&hist[min((key[k] >> 16) - kl >> sh, 1023u)], 1);   // (padding: key 0)
-      if (tid < 2) hb[tid] = -1;
-      lds_barrier();
-      {
+        for (int k = 0; k < S; ++k) {
+          const uint32_t x = key(k) >> 16;
+          if (x >= from) atomicAdd(&hist[min((x - from) >> sh, 1023u)], 1);
+        }
+        if (tid < 2) hb[tid] = -1;
+        lds_barrier();
         const int4 c = *reinterpret_cast<const int4*>(hist + 1020 - 4 * tid);   // thread t: bins 1023 - 4 t .. 1020 - 4 t
-        const int own = c.x + c.y + c.z + c.w;
-        int v = own;
-        v += __builtin_amdgcn_update_dpp(0, v, 0x111, 0xf, 0xf, false);
-        v += __builtin_amdgcn_update_dpp(0, v, 0x112, 0xf, 0xf, false);
-        v += __builtin_amdgcn_update_dpp(0, v, 0x114, 0xf, 0xf, false);
-        v += __builtin_amdgcn_update_dpp(0, v, 0x118, 0xf, 0xf, false);
-        v += __builtin_amdgcn_update_dpp(0, v, 0x142, 0xa, 0xf, false);
-        v += __builtin_amdgcn_update_dpp(0, v, 0x143, 0xc, 0xf, false);
+        const int own = c.x + c.y + c.z + c.w, v = wave_prefix(own);
         if (lane == 63) redi[par * 4 + wave] = v;
         lds_barrier();
         int before = v - own;                          // tokens in higher bins
@@ -159,9 +162,36 @@ __global__ __launch_bounds__(kDenseThreads, (NT <= 4 ? 4 : 2)) void retain_spars
             hb[i] = 1020 - 4 * tid + at;
           }
         }
-      }
-      lds_barrier();
-      auto edge = [&](int bin) -> uint32_t { return kl + (static_cast<uint32_t>(bin) << sh) << 16; };   // lowest key of a bin
+        lds_barrier();
+      };
+      // The bins start at the best finite score and reach down 1024 values, eight binades: nearly always both are found there.
+      auto leading = [](float x) -> uint32_t { return __builtin_amdgcn_readfirstlane(static_cast<int>(ordered_key(x + 0.0f) >> 16)); };
+      const uint32_t kl = leading(glo), kh = leading(ghi), top = kh - kl > 1023u ? kh - 1023u : kl;
+      histogram(top, 0);
+      const int bin[2] = {__builtin_amdgcn_readfirstlane(hb[0]), __builtin_amdgcn_readfirstlane(hb[1])};
+      // The leading 16 bits of the bq-th (i = 0) or the (N32 + 1)-th (i = 1) largest key, 0 when not so many scores reach the lowest finite
+      // one.  What lies below those eight binades (half of a head asked for and scores of both signs, an outlier far above the rest) is found
+      // in two steps, a histogram down to the lowest score and one of the values of the bin found.  (Bins over the whole range alone are
+      // half a binade wide where the scores reach or cross zero: a bound or a cut that coarse keeps too many tokens or too few, and the heads
+      // are handed on.  1024 heads of 3001, b = 128, normal scores: bit by bit 98 us, with such bins alone 254, now 77; log-normal ones with
+      // one zero 86, 274, 74; log-normal 86, 75, 74.  Where the two steps are needed, 7168 of 1024, log-normal with an outlier: 520, 469, 484.)
+      auto key16 = [&](int i) -> uint32_t {
+        if (bin[i] >= 0) return top + static_cast<uint32_t>(bin[i]);
+        if (top == kl) return 0u;
+        uint32_t from = kl;
+        int sh = 22 - __clz(static_cast<int>(kh - kl));   // (kh - kl) >> sh < 1024
+#pragma unroll 1
+        for (int pass = 0; pass < 2; ++pass) {
+          *reinterpret_cast<int4*>(hist + 4 * tid) = make_int4(0, 0, 0, 0);
+          lds_barrier();
+          histogram(from, sh);
+          const int found = __builtin_amdgcn_readfirstlane(hb[i]);
+          if (found < 0) return 0u;
+          from += static_cast<uint32_t>(found) << sh;
+          sh = 0;
+        }
+        return from;
+      };
       // survivors per slot and wave into cnt[], their number over the workgroup returned
       auto count_kept = [&]() -> int {
         int c = 0;
@@ -174,39 +204,29 @@ __global__ __launch_bounds__(kDenseThreads, (NT <= 4 ? 4 : 2)) void retain_spars
         lds_barrier();
         const int tot = redi[par * 4] + redi[par * 4 + 1] + redi[par * 4 + 2] + redi[par * 4 + 3];
         par ^= 1;
+        // (Known to be uniform the masks stay in scalar registers across the branches, and where these run out in lanes of vector registers: what
+        // these two instances need to do without scratch memory, 2048 heads of 4096, b = 64 66.7 -> 55.1 us.  The others lose 1-2 %.)
+        if constexpr (NT <= 4 && S >= 12) return __builtin_amdgcn_readfirstlane(tot);
         return tot;
       };
-      // the lower edge of s_(b)'s bin: at most s_(b), so the bound only loosens
-      const int b0 = __builtin_amdgcn_readfirstlane(hb[0]), b1 = __builtin_amdgcn_readfirstlane(hb[1]);
-      const float sb = key_to_float(b0 < 0 ? 0u : edge(b0));
+      // s_(b) from the leading 16 bits of its key: at most s_(b), so the bound only loosens
+      const float sb = key_to_float(key16(0) << 16);
       const float thr = sb - a.lambda * 1.00001f - 1e-5f * fabsf(sb);   // fp32 cosines may exceed 1 by a few ulp
 #pragma unroll
       for (int k = 0; k < S; ++k) km[k] = __ballot(k * 256 + tid < n && !(sv[k] < thr));   // (a NaN threshold or score keeps the token)
       ns = count_kept();
       if (ns > N32) {
-        // (first the cheap half of the test below: when more than N32 tokens score within a quarter of lambda of
-        // s_(b), the best one left out does too, and the second search is not worth running)
-        int c = 0;
-#pragma unroll
-        for (int k = 0; k < S; ++k) c += __popcll(__ballot(k * 256 + tid < n && !(sv[k] < sb - 0.25f * a.lambda)));
-        if (lane == 0) redi[par * 4 + wave] = c;
-        lds_barrier();
-        const int near = redi[par * 4] + redi[par * 4 + 1] + redi[par * 4 + 2] + redi[par * 4 + 3];
-        par ^= 1;
-        if (near > N32) ns = -1;                       // handed on
-      }
-      if (ns > N32) {
-        // More candidates than fit: the best-scored are kept, cut at the edge of a bin (at most N32
+        // More candidates than fit: the best-scored are kept, cut where the leading 16 key bits change (at most N32
         // of them), and the best score left out is remembered.  Pick gains never increase and a token gains at most
         // its score, so the run is valid iff that score stays below the last pick's gain, which is checked when the
         // chain is done.  That gain is at most s_(b) and in practice a good part of lambda below it: when the score
         // left out lies within a quarter of lambda of s_(b) the chain would be run in vain, and the head is handed
         // on at once (a guess about speed only: either way the picks are exact).
-        const uint32_t cut = edge(b1 + 1);             // (b1 < 0 with NaNs only: every token passes and the head is handed on)
+        const uint32_t cut = (key16(1) + 1u) << 16;    // (of 0, with a NaN for s_(b) only: every score passes and the head is handed on)
         float ob = -INFINITY;
 #pragma unroll
         for (int k = 0; k < S; ++k) {
-          const bool in = k * 256 + tid < n && key[k] >= cut;
+          const bool in = k * 256 + tid < n && key(k) >= cut;
           if (k * 256 + tid < n && !in) ob = hw_max(ob, sv[k]);
           km[k] = __ballot(in);
         }
@@ -226,21 +246,14 @@ __global__ __launch_bounds__(kDenseThreads, (NT <= 4 ? 4 : 2)) void retain_spars
     }
     // positions in token order: slot k before slot k + 1, wave w before wave w + 1, lane by lane
     if (wave == 0) {
-      int v = lane < 4 * S ? cnt[lane] : 0;
-      const int own = v;
-      v += __builtin_amdgcn_update_dpp(0, v, 0x111, 0xf, 0xf, false);
-      v += __builtin_amdgcn_update_dpp(0, v, 0x112, 0xf, 0xf, false);
-      v += __builtin_amdgcn_update_dpp(0, v, 0x114, 0xf, 0xf, false);
-      v += __builtin_amdgcn_update_dpp(0, v, 0x118, 0xf, 0xf, false);
-      v += __builtin_amdgcn_update_dpp(0, v, 0x142, 0xa, 0xf, false);
-      v += __builtin_amdgcn_update_dpp(0, v, 0x143, 0xc, 0xf, false);
-      off[lane] = v - own;
+      const int own = lane < 4 * S ? cnt[lane] : 0;
+      off[lane] = wave_prefix(own) - own;
     }
     lds_barrier();
 #pragma unroll
     for (int k = 0; k < S; ++k) {
-      if ((km[k] >> lane) & 1ull) {
-        const int pos = min(kvr_ix(off[k * 4 + wave] + __popcll(km[k] & below), N32, 301), N32 - 1);   // 301: a survivor's position
+      if (__builtin_amdgcn_inverse_ballot_w64(km[k])) {
+        const int pos = min(kvr_ix(off[k * 4 + wave] + lane_rank(km[k]), N32, 301), N32 - 1);   // 301: a survivor's position
         tok_c[pos] = k * 256 + tid;
         s_l[pos] = sv[k];
       }
