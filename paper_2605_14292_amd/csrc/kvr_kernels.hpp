@@ -87,6 +87,8 @@ hipError_t launch_retain_dense(const void* K, const void* V, const void* Q, int 
                                int32_t* idx_sorted, int32_t* pick_order, float* pick_gain,
                                void* K_out, void* V_out, hipStream_t st, bool only_marked = false,
                                const int32_t* b_h = nullptr);
+// (heads of 193-256 tokens: the next head's Gram beside the pick chain, or between two chains)
+bool gram_ahead_pays(int heads, int n, int b, bool queries, int cus);
 
 // The same event for calls with at most one head per CU (heads <= cus) and 128 < n <= 256: sixteen
 // waves per head for the parallel phases.

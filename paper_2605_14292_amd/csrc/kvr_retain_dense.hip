@@ -30,12 +30,13 @@
 // n=192, b=64 213 -> 155, n=128, b=64 175 -> 111; 8192 heads, n=64, b=48 234 -> 123; one head, n=128, b=64 19.0 -> 15.5, 256
 // heads 20.5 -> 17.  Scores far below lambda given: 4096 heads, n=128, b=64 153 -> 84.
 //
-// Heads of more than 192 tokens (AHEAD): between two chains of such a head stood 0.6 us of staging, 1.8 of Gram and 1.9 of triangle beside 14.1
-// of chain (n = 251, b = 101), and only the triangle needs the place of the one before.  So the waves 2 .. 7 stage the next head's rows a
+// Heads of more than 192 tokens: between two chains of such a head stand 0.6 us of staging, 1.8 of Gram and 1.9 of triangle beside 14.1
+// of chain (n = 251, b = 101), and only the triangle needs the place of the one before.  So under AHEAD the waves 2 .. 7 stage the next head's rows a
 // quarter of their columns at a time in the 16 KB beside the triangle, run the Gram and scale it to cosines while the chain runs (they meet at
 // a counter, the chain's wave is not asked), and what is left between two chains is the stores (6 700 cycles with the scaling among them, about
 // 4 000 now).  2688 heads of 251 tokens, b=101 414 us one phase after the other, 220 with the Gram between the chains, 209 with the packed triangle,
-// 194 now; 8192 of 250, b=128, tight scores given 785 -> 696; 257 of 256, b=128 54.8 -> 51.2.
+// 194 beside them; 8192 of 250, b=128, tight scores given 785 -> 696; 257 of 256, b=128 54.8 -> 51.2.  With short chains there is nothing to hide behind:
+// gram_ahead_pays.
 // Tried: the Gram beside the chain with its operands loaded from memory in the MFMA layout: the 450 gathered loads of a head of 256 tokens take
 // 12 us whatever the prefetch depth or the bytes per row and request, the address unit spending 64 cycles on each (239 us); and no triangle
 // at all, the cosines of 32 candidates at a time from rows of V held as operands in registers, three heads per CU (238 us: twelve waves'
@@ -59,16 +60,17 @@ struct DenseArgs {
   const int32_t* b_h;                  // per-head budgets <= b (rows of the outputs stay b apart), or null
 };
 
-template <int NT> struct DenseCfg {
+template <int NT, bool GRAM_AHEAD = false> struct DenseCfg {
   static constexpr int W = NT == 8 ? 8 : 4;           // waves
   static constexpr int OCC = NT == 8 ? 1 : (NT == 6 ? 2 : (NT == 4 ? 3 : 4));   // heads per CU; up to 128 tokens the registers set it, above LDS
   static constexpr int N32 = NT * 32;
   static constexpr int OFFD = NT * (NT - 1) / 2;      // tiles of the lower triangle off its diagonal
-  // One head per CU: the Gram of the next head runs beside the chain as well, on the waves 2 .. 7, its rows staged a quarter of their columns
-  // at a time in the 16 KB that the triangle leaves.
-  static constexpr bool AHEAD = NT == 8;
+  // One head per CU: the Gram of the next head can run beside the chain as well, on the waves 2 .. 7, its rows staged a quarter of their columns
+  // at a time in the 16 KB that the triangle leaves (gram_ahead_pays says when).
+  static constexpr bool AHEAD = GRAM_AHEAD;
+  static_assert(!AHEAD || NT == 8, "one head per CU");
   static constexpr int GW = 6, GT = NT * (NT + 1) / 2 / GW;   // (then) waves with tiles, tiles of each
-  static constexpr int kQuarter = AHEAD ? N32 * 64 : 0;
+  static constexpr int kQuarter = AHEAD ? N32 * 64 : 0, kMet = AHEAD ? 16 : 0;
   static_assert(!AHEAD || GT * GW == NT * (NT + 1) / 2, "equal shares");
   static constexpr int MAXD = (NT + W - 1) / W, MAXO = (OFFD + W - 1) / W;   // Gram tiles per wave, on the diagonal and off it
   static constexpr int ROWS = (N32 * 16 + 64 * (W - 2) - 1) / (64 * (W - 2));   // 16-byte row pieces per thread of waves 2 ..
@@ -79,15 +81,15 @@ template <int NT> struct DenseCfg {
   static constexpr bool PACKED = NT == 8;
   static constexpr int kTriBytes = PACKED ? dense_tri_floats(NT) * 4 : padded_tri_floats(N32) * 4;
   static constexpr int region = !AHEAD && N32 * kRowPitch > kTriBytes ? N32 * kRowPitch : kTriBytes;   // (AHEAD: rows are not staged there)
-  // triangle or staged rows | quarter of the rows | s_l[2][N32] | rinv[N32] | lists [2][order, gain][bcap] | [2][idx][bcap], 16 bits each: with 32
+  // triangle or staged rows | quarter of the rows | s_l[2][N32] | rinv[N32] | met (AHEAD) | lists [2][order, gain][bcap] | [2][idx][bcap], 16 bits each: with 32
   // two heads of 192 tokens and more than 128 picks do not fit a CU (4096 heads, n=192, b=160 412 us; now 244, and 377 before the lists came in pairs)
-  static constexpr int smem_bytes(int b) { return region + kQuarter + N32 * 3 * 4 + 16 + 2 * bcap(b) * (4 + 4 + 2); }
-  static_assert(OCC * (region + kQuarter + N32 * 3 * 4 + 16 + 2 * N32 * (4 + 4 + 2)) <= 160 * 1024, "OCC heads fit a CU at every budget");
+  static constexpr int smem_bytes(int b) { return region + kQuarter + N32 * 3 * 4 + kMet + 2 * bcap(b) * (4 + 4 + 2); }
+  static_assert(OCC * (region + kQuarter + N32 * 3 * 4 + kMet + 2 * N32 * (4 + 4 + 2)) <= 160 * 1024, "OCC heads fit a CU at every budget");
 };
 
-template <int NT>
+template <int NT, bool GRAM_AHEAD>
 __global__ __launch_bounds__(64 * DenseCfg<NT>::W, DenseCfg<NT>::W * DenseCfg<NT>::OCC / 4) void retain_dense_kernel(DenseArgs a) {
-  using C = DenseCfg<NT>;
+  using C = DenseCfg<NT, GRAM_AHEAD>;
   constexpr int N32 = C::N32, NQ = NT / 2, W = C::W, ROWS = C::ROWS;
   extern __shared__ __align__(16) char smem[];
   char* stage = smem;
@@ -97,7 +99,7 @@ __global__ __launch_bounds__(64 * DenseCfg<NT>::W, DenseCfg<NT>::W * DenseCfg<NT
   float* rinv = s_all + 2 * N32;                        // inverse norms of the head whose triangle is being built
   const int bcap = C::bcap(a.b);
   int32_t* met = reinterpret_cast<int32_t*>(rinv + N32);     // [4] how often the waves with tiles have met (AHEAD)
-  int32_t* lists = met + 4;                             // [2][2][bcap]: picks in order, gains
+  int32_t* lists = met + C::kMet / 4;                   // [2][2][bcap]: picks in order, gains
   uint16_t* idx_all = reinterpret_cast<uint16_t*>(lists + 4 * bcap);   // [2][bcap]: ascending indices
 
   int tid = threadIdx.x, lane = tid & 63, hf = lane >> 5, l32 = lane & 31;
@@ -178,7 +180,8 @@ __global__ __launch_bounds__(64 * DenseCfg<NT>::W, DenseCfg<NT>::W * DenseCfg<NT
     lds_barrier();                                      // every wave has read its rows: the triangle takes their place
     if (need_v) {
       auto write_tile = [&](const f32x16& t, int I, int J) {
-        write_cos_tile_padded(tri, rinv, t, I, J, lane);
+        if constexpr (C::PACKED) write_cos_tile_rows(tri, rinv, t, I, J, lane);
+        else write_cos_tile_padded(tri, rinv, t, I, J, lane);
       };
 #pragma unroll
       for (int d = 0; d < C::MAXD; ++d)
@@ -461,6 +464,23 @@ bool dense_supported(const Layout& lay, int b, int G, bool has_q) {
   return lay.dtype == DT_BF16 && lay.n <= 256 && b <= kMaxB && (!has_q || G <= 8);
 }
 
+// Whether the Gram of a workgroup's next head runs beside the chain (DenseCfg::AHEAD) or between two chains, heads of 193-256 tokens.  Beside it,
+// six waves instead of eight meet eight times a head, and a workgroup's first head has no chain to hide that behind: it pays where the
+// chain is long, and with queries (whose scores need one wave the longest) sooner.  Between / beside, us:
+//   scores given, 2688 heads of 256, b = 2 / 32 / 64 / 80:  104 / 138, 126 / 153, 172 / 173, 197 / 186;  of 200, b = 64:  171 / 166
+//   ... at most two heads per CU, 257 of 200, b = 24 / 64 / 128:  25.7 / 30.6, 36.4 / 38.2, 55.5 / 56.7;  512 of 224, b = 128: 0.989x beside; 700: 1.011x
+//   7 queries, 700 heads of 200, b = 24 / 48 / 56 / 64 / 80:  36.7 / 40.0, 42.4 / 44.7, 45.4 / 45.9, 48.7 / 47.4, 55.5 / 52.7
+//   ... at most two heads per CU, 257 of 240, b = 24 / 48 / 56:  23.0 / 25.3, 29.0 / 29.0, 31.1 / 30.1
+// With queries and short chains the event is bound by its reads once K and V exceed the memory-side cache, and beside the chain they are requested
+// sooner: 3072 heads (1 / 4 / 7 queries alike) of 256, b = 2 / 24 / 40: 1.08x, 1.06x, 1.03x beside; of 193, b = 24 / 40: 1.00x, 0.96x;
+// inside the cache, 1536 of 256, b = 24: 0.96x.
+bool gram_ahead_pays(int heads, int n, int b, bool queries, int cus) {
+  const bool few = heads <= 2 * cus;
+  if (b >= (queries && few ? 56 : 64)) return queries || !few;
+  const bool past_cache = static_cast<long long>(heads) * n * (2 * kD * 2) >= 256ll << 20;
+  return queries && past_cache && (n >= 240 || b <= 24);
+}
+
 hipError_t launch_retain_dense(const void* K, const void* V, const void* Q, int G, const float* s_in,
                                const Layout& lay, int b, float lambda, float eps, float* s_out,
                                int32_t* idx_sorted, int32_t* pick_order, float* pick_gain,
@@ -487,10 +507,15 @@ hipError_t launch_retain_dense(const void* K, const void* V, const void* Q, int 
     hipLaunchKernelGGL(kern, grid, dim3(threads), smem, st, a);
     return hipGetLastError();
   };
-  if (lay.n <= 64) return go(&retain_dense_kernel<2>, DenseCfg<2>::smem_bytes(b), 64 * DenseCfg<2>::W, DenseCfg<2>::OCC);
-  if (lay.n <= 128) return go(&retain_dense_kernel<4>, DenseCfg<4>::smem_bytes(b), 64 * DenseCfg<4>::W, DenseCfg<4>::OCC);
-  if (lay.n <= 192) return go(&retain_dense_kernel<6>, DenseCfg<6>::smem_bytes(b), 64 * DenseCfg<6>::W, DenseCfg<6>::OCC);
-  return go(&retain_dense_kernel<8>, DenseCfg<8>::smem_bytes(b), 64 * DenseCfg<8>::W, DenseCfg<8>::OCC);
+  auto launch = [&](auto kern, auto cfg) -> hipError_t {
+    using C = decltype(cfg);
+    return go(kern, C::smem_bytes(b), 64 * C::W, C::OCC);
+  };
+  if (lay.n <= 64) return launch(&retain_dense_kernel<2, false>, DenseCfg<2>{});
+  if (lay.n <= 128) return launch(&retain_dense_kernel<4, false>, DenseCfg<4>{});
+  if (lay.n <= 192) return launch(&retain_dense_kernel<6, false>, DenseCfg<6>{});
+  if (gram_ahead_pays(lay.heads, lay.n, b, Q != nullptr, cus)) return launch(&retain_dense_kernel<8, true>, DenseCfg<8, true>{});
+  return launch(&retain_dense_kernel<8, false>, DenseCfg<8>{});
 }
 
 }  // namespace kvr
