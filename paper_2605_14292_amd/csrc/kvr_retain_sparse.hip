@@ -384,6 +384,9 @@ hipError_t launch_retain_sparse(const void* K, const void* V, const float* s, co
     constexpr int NT = decltype(nt)::value;
     constexpr int smem = sparse_smem_bytes(NT);
     constexpr int per_cu = NT <= 4 ? 4 : 2;
+    // Score slots by length, in steps of 1024 tokens: a slot that no token of the head is in costs registers and a compare per count.  2049-3072 tokens
+    // with sixteen slots / twelve: 1024 heads of 3001, b = 128 76.2 / 74.5 us, 2048 of 2500, b = 64 54.3 / 52.8; 1025-1536 with eight / six would be 0.3-1.5 %
+    // (7168 of 1300, b = 64 168.4 / 166.8), for which two more instances are not built.
     if (lay.n <= 1024) return go(&retain_sparse_kernel<NT, 4>, smem, per_cu);
     if (lay.n <= 2048) return go(&retain_sparse_kernel<NT, 8>, smem, per_cu);
     if (lay.n <= 3072) return go(&retain_sparse_kernel<NT, 12>, smem, per_cu);

@@ -366,9 +366,11 @@ hipError_t launch_score(const void* K, const void* Q, int G, const Layout& lay, 
   // the logits of a head (G x n floats) wait in LDS
   const bool fits = static_cast<long long>(G) * lay.n <= (G <= 8 ? 24576 : 31488);
   // Logits that fill a CU's LDS: one workgroup of sixteen waves per CU still reads K once where score_wide_kernel reads it twice.
-  // Few heads leave CUs idle here, while the other kernel splits a head over several.  Two passes / one, us, 4 queries: 256 heads of 8192
+  // Few heads leave CUs idle here, while the other kernel splits a head over several (hence the two heads to five CUs).  Two passes / one, us, 4 queries: 256 heads of 8192
   // tokens 196 / 101, 448 354 / 180, 128 86 / 68, 112 75 / 67, 96 65 / 67, 32 32 / 67; 256 of 5500 with 7 queries 136 / 72.  (Scores' error against 64
   // bits, 2-norm, 256 heads of 8192: 3.6e-7 / 1.3e-7.)
+  // The line at 4096 tokens is not one of speed: shorter heads whose logits fill the LDS (7 queries from 3513 tokens on, 8 from 3073) would gain as
+  // well, 256 heads of 4096 with 7 queries 78 / 48, 112 44.0 / 39.7, 256 of 3300 with 8 62 / 43, 64 of 4096 30.9 / 31.0.  Their scores keep the bits that two passes give.
   const bool whole_cu = !fits && lay.n > 4096 && G <= 8 && (G * lay.n + 2 * 16 * 8) * 4 <= 160 * 1024 && 5 * lay.heads > 2 * cu_count();
   if (lay.dtype == DT_BF16 && G <= 32 && (fits || whole_cu)) {
     const int gq = G <= 8 ? 8 : 32;

@@ -67,7 +67,7 @@ __global__ __launch_bounds__(kF32Threads, 1) void select_dense_f32_kernel(F32Arg
   int32_t* meta = tok_c + N32;                                         // [0] its size, 0 = not reduced
 
   const int tid = threadIdx.x;
-  const int lane = tid & 63, hf = lane >> 5;
+  const int lane = tid & 63;
   const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
   const int h = blockIdx.x;
   const int n = a.n, b = a.b;

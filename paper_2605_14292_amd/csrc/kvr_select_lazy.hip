@@ -27,8 +27,8 @@
 // pick.  On the benchmark inputs an epoch serves 5-50 picks and a head reads its rows about
 // 2.7 times (once per epoch with a full pass).  Nothing is approximated.
 //
-// F32 rows (the flat-signature mode's mean rows, fp32 caches) run the same epochs with the fp32 MFMAs (32x32x2 for
-// the pool's Gram, 16x16x4 for the passes); their 512-byte rows leave no room for a stage, so the rows of a pass are
+// F32 rows (the flat-signature mode's mean rows, fp32 caches) run the same epochs with the fp32 MFMA (16x16x4,
+// in the passes and for the pool's Gram); their 512-byte rows leave no room for a stage, so the rows of a pass are
 // loaded straight into the operand layout.
 //
 // Layout: one workgroup per head, W wave64s, token j = 64*S*w + 64*k + lane in
