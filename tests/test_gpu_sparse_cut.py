@@ -1,6 +1,7 @@
-"""retain_sparse_kernel's search for s_(b) and its cut at the capacity, by a histogram of the leading 16 key bits, where it can go
-wrong: keys over more values than it has bins, all in one bin, ties over the threshold, exactly as many survivors as places and one
-more; at the edges of the 4-, 8-, 12- and 16-slot instances.  Every pick against Eq. 2 in fp64 on the path's own prefix."""
+"""retain_sparse_kernel's search for s_(b) by a histogram of the leading 16 key bits, where it can go wrong: keys over more values than
+it has bins, all in one bin and a low score, crowds of equal scores over the threshold, exactly as many survivors as places (which fit) and
+one more (which are handed on); at the edges of the 4-, 8-, 12- and 16-slot instances.  Every pick against Eq. 2 in fp64 on the path's own prefix.
+Heads that are cut at the capacity, and which heads the kernel finishes by itself: test_gpu_sparse_search.py."""
 import pytest
 import torch
 

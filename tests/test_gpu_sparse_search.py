@@ -3,6 +3,7 @@ wherever the scores lie (positive, of both signs, with zeros, with an outlier fa
 kernel for long heads.  The same decisions from sorted scores on the CPU; a head that is cut is finished when the best score left out stays
 below the last gain of the oracle's run on what is kept."""
 import ctypes
+import dataclasses
 
 import numpy as np
 import pytest
@@ -125,3 +126,21 @@ def test_heads_of_one_workgroup(b):
     alone = [_run_alone(K[h:h + 1], V[h:h + 1].to(DEV), s[h:h + 1].to(DEV), b) for h in range(heads - 20, heads)]
     for h, one in zip(range(heads - 20, heads), alone):
         assert torch.equal(out.idx_sorted[h], one.idx_sorted[0]) and (not done[h] or torch.equal(out.pick_order[h], one.pick_order[0]))
+
+
+def test_a_full_size_event_with_scores_of_both_signs():
+    """7168 heads of 1024 tokens, b = 128, all of them cut: whether sampled heads are finished, their picks one by one, kept rows of all."""
+    w = dataclasses.replace(W.WORKLOADS["c5"], scores="given", G=1)
+    data = W.generate(w, seed=11, device=DEV)
+    K, V, s = data["K"], data["V"], data["s"].log()              # (the generator's scores are log-normal)
+    alone = _run_alone(K, V, s, 128)
+    done = (alone.idx_sorted[:, 0] != -1)
+    out = B.kvr_retain(K, V, 128, LAM, EPS, s=s)
+    torch.cuda.synchronize()
+    assert torch.equal(out.pick_order[done], alone.pick_order[done])
+    rows = out.idx_sorted.long().unsqueeze(-1).expand(-1, -1, 128)
+    assert torch.equal(out.V_out, torch.gather(V, 1, rows)) and torch.equal(out.K_out, torch.gather(K, 1, rows))
+    for h in range(0, w.heads, 241):
+        assert finishes(s[h].cpu().numpy(), W.to_f64(V[h]), 128, 192) == ("cut", bool(done[h]))
+        P.check_head(W.to_f64(s[h]), W.to_f64(V[h]), 128, LAM, EPS, out.pick_order[h].cpu().numpy(), out.pick_gain[h].cpu().numpy(),
+                     out.idx_sorted[h].cpu().numpy())
