@@ -33,8 +33,8 @@
 // Heads of more than 192 tokens: between two chains of such a head stand 0.6 us of staging, 1.8 of Gram and 1.9 of triangle beside 14.1
 // of chain (n = 251, b = 101), and only the triangle needs the place of the one before.  So under AHEAD the waves 2 .. 7 stage the next head's rows a
 // quarter of their columns at a time in the 16 KB beside the triangle, run the Gram and scale it to cosines while the chain runs (they meet at
-// a counter, the chain's wave is not asked), and what is left between two chains is the stores (6 700 cycles with the scaling among them, about
-// 4 000 now).  2688 heads of 251 tokens, b=101 414 us one phase after the other, 220 with the Gram between the chains, 209 with the packed triangle,
+// a counter, the chain's wave is not asked), and what is left between two chains is the stores (6 700 cycles with the scaling among them, 4 600 now, beside
+// 32 500 of chain and 900 of sorting).  2688 heads of 251 tokens, b=101 414 us one phase after the other, 220 with the Gram between the chains, 209 with the packed triangle,
 // 194 beside them; 8192 of 250, b=128, tight scores given 785 -> 696; 257 of 256, b=128 54.8 -> 51.2.  With short chains there is nothing to hide behind:
 // gram_ahead_pays.
 // Tried: the Gram beside the chain with its operands loaded from memory in the MFMA layout: the 450 gathered loads of a head of 256 tokens take
